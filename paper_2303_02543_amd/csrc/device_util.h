@@ -22,6 +22,53 @@ __device__ __forceinline__ X &at_mut(void *base, uint32_t byte_off) {
     return *reinterpret_cast<X *>(reinterpret_cast<char *>(base) + byte_off);
 }
 
+// Load of a 4-, 8- or 16-byte value at a 32-bit byte offset from a
+// wave-uniform base, through a buffer descriptor made of the base: a
+// scalar base and one vector register, with no vector address arithmetic.
+// (Given a pointer plus a zero-extended offset, the compiler hoists the
+// extension out of a loop, holds 64-bit offsets and adds them for every
+// access.)  The descriptor covers 4 GiB from the base; offsets are in bounds
+// by construction.
+template <typename X>
+__device__ __forceinline__ X buffer_get(const void *base, uint32_t off) {
+    static_assert(sizeof(X) == 4 || sizeof(X) == 8 || sizeof(X) == 16, "4, 8 or 16 bytes");
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, -1, 0x00020000);
+    X x;
+    if constexpr (sizeof(X) == 16) {
+        const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+        __builtin_memcpy(&x, &t, 16);
+    } else if constexpr (sizeof(X) == 8) {
+        const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+        __builtin_memcpy(&x, &t, 8);
+    } else {
+        const unsigned int t = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+        __builtin_memcpy(&x, &t, 4);
+    }
+    return x;
+}
+
+// 16-byte store at a 32-bit byte offset from a wave-uniform base through a
+// buffer descriptor: lanes that have nothing to store pass kNoStore, and
+// `on` = false (uniform) drops the whole store, both by the descriptor's
+// bounds check.  So the store is issued on every path, and the compiler's
+// waits for later loads can count it: a store under a branch is not counted,
+// and every wait for a load then also waits for the stores before it.
+constexpr uint32_t kBufferBytes = 0xfffff000u;  // offsets stay below this
+constexpr uint32_t kNoStore = 0xfffffff0u;
+template <typename X>
+__device__ __forceinline__ void buffer_put16(void *base, uint32_t off, bool on, const X &v) {
+    static_assert(sizeof(X) == 16, "16-byte stores only");
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 t;
+    __builtin_memcpy(&t, &v, 16);
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc(base, 0, on ? kBufferBytes : 0u, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, 0);
+}
+
 // 16-byte store with the non-temporal hint (the line is not kept in the
 // caches on its way to memory).
 template <typename X>

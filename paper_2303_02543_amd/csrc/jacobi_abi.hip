@@ -347,16 +347,22 @@ int check_handle(jacobi_t h) {
     return JACOBI_OK;
 }
 
+// Compute units of the current device (0: unknown).
+int cu_count() {
+    int cus = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return cus;
+}
+
 // Tile height that makes one march launch fill the GPU in `rounds` whole
 // rounds of resident waves: the smallest height whose tiles (edge bands and
 // outer strips included) number at most rounds x (waves per CU x CUs).
 int balanced_rows(const jacobi_s *h, int depth, int mode, int rounds) {
     if (h->g.ndim != 2) return 64;
-    int cus = 0, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-        return 64;
+    const int cus = cu_count();
+    if (cus <= 0) return 64;
     const int wpc = h->dtype == JACOBI_F32 ? jac::march2d_waves_per_cu<float>(depth, mode)
                                            : jac::march2d_waves_per_cu<double>(depth, mode);
     if (wpc <= 0) return 64;
@@ -383,10 +389,10 @@ int balanced_rows(const jacobi_s *h, int depth, int mode, int rounds) {
 // Defaults before any tuning: the fastest schedules measured on MI355X for
 // a 2D FP32 8192^2 grid with a residual every 50 sweeps (depth 13: passes of
 // 13, 13, 12, 12), with a tile height that fills the GPU in one round of
-// resident waves, and for a 512^3 grid in 64^3 blocks (depth 4, the deepest
-// 3D pass: 836 / 475 GLUP/s in FP32 / FP64 against 381 / 190 at depth 1).
+// resident waves, and for a 512^3 grid in 64^3 blocks (depth 5, the deepest
+// 3D pass).
 int default_depth(const jacobi_s *h) {
-    if (h->g.ndim == 3) return 4;
+    if (h->g.ndim == 3) return 5;
     return h->dtype == JACOBI_F32 ? 13 : 4;
 }
 
@@ -450,24 +456,27 @@ int do_halo(jacobi_t h) {
     return JACOBI_OK;
 }
 
-// z planes per work item of the 3D pass: 32 (FP32) / 64 (FP64) measured
-// fastest at depth 4 on 512^3 (16 .. 128 tried; shorter segments repeat the
-// 2(T-1) warm-up planes more often, longer ones leave too few work items).
-int zseg_of(const jacobi_s *h) {
-    return h->rows > 0 ? h->rows : h->dtype == JACOBI_F32 ? 32 : 64;
+// Plan of a 3D pass of `depth` sweeps with the handle's z segment (or the
+// plan's own); its residual partials always fit the workspace's.
+template <typename R>
+int plan3d(const jacobi_s *h, int depth, jac::M3Plan *pl) {
+    const int cus = cu_count();
+    if (!jac::march3d_plan<R>(h->g, depth, h->rows, cus > 0 ? cus : 256, h->lay.part_cap, pl))
+        return fail(JACOBI_E_INVAL, "partials overflow");
+    return JACOBI_OK;
 }
 
 template <typename R>
 int do_residual(jacobi_t h, double *out) {
     const void *b = h->has_source ? h->b : nullptr;
     if (h->g.ndim == 3) {
-        const int64_t nw = jac::march3d_work_items<R>(h->g, zseg_of(h));
-        if ((size_t)nw > h->lay.part_cap) return fail(JACOBI_E_INVAL, "partials overflow");
-        int64_t nwork = 0;
-        HIP_TRY(jac::launch_march3d<R>(h->g, h->u[h->cur], nullptr, b, h->partials, zseg_of(h),
-                                       h->stream, &nwork),
+        jac::M3Plan pl;
+        int rc = plan3d<R>(h, 1, &pl);
+        if (rc) return rc;
+        HIP_TRY(jac::launch_march3d<R>(h->g, h->u[h->cur], nullptr, b, h->partials, pl, h->stream,
+                                       1),
                 "residual launch");
-        HIP_TRY(jac::launch_residual_final(h->partials, (int)nwork, out, h->stream),
+        HIP_TRY(jac::launch_residual_final(h->partials, (int)pl.partials, out, h->stream),
                 "residual launch");
         return JACOBI_OK;
     }
@@ -558,7 +567,6 @@ int do_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos = true) {
     if (h->g.ndim == 3 && !explicit_halo && n > 0) {
         // fused 3D passes of up to `depth` sweeps each, split as evenly as
         // possible; the first also sums the residual of its input
-        const int zseg = zseg_of(h);
         const int depth = h->depth > 0 ? h->depth : default_depth(h);
         int64_t left = n;
         bool first = true;
@@ -566,18 +574,18 @@ int do_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos = true) {
             const int64_t passes = (left + depth - 1) / depth;
             const int t = (int)((left + passes - 1) / passes);
             double *part = (first && res_first) ? h->partials : nullptr;
-            if (part && (size_t)jac::march3d_work_items<R>(h->g, zseg, t) > h->lay.part_cap)
-                return fail(JACOBI_E_INVAL, "partials overflow");
-            int rc = prof_begin(h);
+            jac::M3Plan pl;
+            int rc = plan3d<R>(h, t, &pl);
             if (rc) return rc;
-            int64_t nwork = 0;
-            HIP_TRY(jac::launch_march3d<R>(h->g, h->u[h->cur], h->u[h->cur ^ 1], b, part, zseg,
-                                           h->stream, &nwork, h->flags & JACOBI_FLAG_NT_STORES, t),
+            rc = prof_begin(h);
+            if (rc) return rc;
+            HIP_TRY(jac::launch_march3d<R>(h->g, h->u[h->cur], h->u[h->cur ^ 1], b, part, pl,
+                                           h->stream, t),
                     "sweep launch");
             rc = prof_end(h, t);
             if (rc) return rc;
             if (part)
-                HIP_TRY(jac::launch_residual_final(part, (int)nwork, res_first, h->stream),
+                HIP_TRY(jac::launch_residual_final(part, (int)pl.partials, res_first, h->stream),
                         "residual launch");
             first = false;
             h->cur ^= 1;
@@ -1304,8 +1312,13 @@ int jacobi_get_tuning(jacobi_t h, int *t_depth, int *rows, int *flags) {
         *rows = h->rows;
     else if (h->halo > 0 && h->g.ndim == 3)
         *rows = h->g.e[2] + 2 * (h->halo - 1);  // deep-halo passes: one z segment per block
-    else
-        *rows = h->g.ndim == 3 ? zseg_of(h) : default_rows(h);
+    else if (h->g.ndim == 3) {
+        jac::M3Plan pl;
+        rc = h->dtype == JACOBI_F32 ? plan3d<float>(h, *t_depth, &pl) : plan3d<double>(h, *t_depth, &pl);
+        if (rc) return rc;
+        *rows = pl.zseg;
+    } else
+        *rows = default_rows(h);
     *flags = h->flags;
     return JACOBI_OK;
 }

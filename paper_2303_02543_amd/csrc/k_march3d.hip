@@ -8,30 +8,41 @@
 //   s = ((W + E) + (S + N)) + (B + F);  u' = (s + b) * fl(1/6)
 // with no FMA contraction, so every schedule gives the same bits.
 //
-// A workgroup of 8 waves holds 32 rows by 16 lanes x V elements along x (one
-// 16-lane row of a wave per grid row; 64 columns in FP32, 32 in FP64) and
-// marches along z through a segment of planes.  For the 64^3 blocks of the
-// workloads a wave's 4 rows lie in one block, so every load instruction reads
-// neighbouring rows of one block.  Each plane of the state and the source is
-// loaded once, from whichever block owns it -- the exchange of halo cells
-// between blocks happens inside these loads -- and pushed through T levels:
-// at the step that loads plane z + 1, level s computes plane z - s + 1 from
-// the planes z - s .. z - s + 2 of level s - 1, each lane keeping three planes
-// of every level in registers.  The rows y - 1 and y + 1 come from the
-// workgroup's LDS copy of level s - 1's plane, which that level computed one
-// step earlier, so one barrier per step serves every level (two LDS buffers
-// alternate by step).  x neighbours come from DPP shifts within each 16-lane
-// row; level 1 also reads the cells just outside the tile (one scalar load
-// per row end) and the two rows just outside it (one load each), so it is
-// valid on the whole tile, and level s on the tile less s - 1 cells on every
-// side in x and y.  Level T is the pass's output on the inner tile: rows
-// T-1 .. 32-T, columns A0 .. A0+OW-1 (chunk-aligned).  A z segment costs
-// 2(T-1) extra planes of warm-up.
+// A workgroup of 8 waves holds a tile of 64 (FP32) / 32 (FP64) columns by
+// H = 32 RY rows and marches along z through a segment of planes.  A lane holds
+// 16 bytes of RY consecutive rows; 16 lanes span the tile's width and a wave 4 RY rows.  Each
+// plane of the state and the source is loaded from whichever block owns it
+// -- the exchange of halo cells between blocks happens inside these loads --
+// and pushed through T levels: at step z, level s computes plane z - s + 1
+// from the planes z - s .. z - s + 2 of level s - 1, held in registers.
+// x neighbours come from DPP shifts within each 16-lane row, y neighbours
+// from the lane's own rows and, at its first and last row, from the LDS copy
+// of level s - 1's boundary rows that their lanes wrote one step earlier (two
+// buffers alternate by step, one barrier per step serves every level).
+// Level 1 reads the rows just outside a lane's own from memory instead (the
+// L1 holds them: the neighbouring lane loads the same rows), so its
+// arithmetic runs before the barrier.  Level s is valid on the tile less
+// s - 1 cells on every side, except where the tile ends at the domain's ring:
+// there the ring values (x: the lane's edge cell; y: the halo rows of the
+// LDS buffers, handed from level to level) keep every level valid up to the
+// ring.  So the first and last tile of an axis need no halo beyond the ring,
+// and k tiles of 64 columns at depth 5 cover 56 k + 8 columns.
 //
-// The Dirichlet ring keeps its values at every level: a level on a ring
-// plane (z = -1 or n_z) copies its input; tiles that reach the ring in x or
-// y copy the input on every ring cell.  Rows, columns and planes beyond the
-// ring are read from clamped in-bounds addresses and never reach an output.
+// A segment that ends in the middle of an unrolled group ends the wave there:
+// leaving through the loop would merge the register rings of the group's
+// steps (copies of every plane, and waits for the loads in flight).
+//
+// What bounds it: memory.  The state's plane z + 2, and the source, edge cells
+// and outer rows of plane z + 1, are requested at step z and used one step
+// later, and a step takes 2.6 us whatever the depth (512^3 FP32, one workgroup
+// per CU: depth 3 467 us per pass, depth 4 464, depth 5 470, 4.1 TB/s of counter
+// traffic, 1.25x the algorithmic bytes).  So the deepest pass and the largest
+// tile the registers and the LDS hold win: 64 rows at two rows per lane, one
+// workgroup of 8 waves per CU.  Smaller tiles with two workgroups per CU (32
+// rows: 724 us at depth 5), loads two steps ahead (475 us) and non-temporal
+// stores (516 us) were slower.  Per pass of 512^3 (this kernel at depth 5, and
+// the kernel of 32-row tiles without prefetch at depth 4 before it): FP32 1428
+// and 856 G updates/s, FP64 608 and 480.
 #include <hip/hip_runtime.h>
 
 #include "device_util.h"
@@ -42,20 +53,24 @@ namespace jac {
 
 constexpr int kM3Waves = 8;              // waves per work item (workgroup)
 constexpr int kM3Threads = 64 * kM3Waves;
-constexpr int kM3Rows = 4 * kM3Waves;    // rows held per work item (4 per wave)
 
-template <typename R, int T>
+template <typename R, int T, int RY>
 struct M3 {
-    static constexpr int V = 16 / (int)sizeof(R);
+    static constexpr int V = 16 / (int)sizeof(R);            // columns per lane
     static constexpr int W = 16 * V;                         // columns held per work item
-    static constexpr int A0 = V * ((T - 1 + V - 1) / V);     // first output column (chunk-aligned)
-    static constexpr int OW = V * ((W - (T - 1) - A0) / V);  // output columns per work item
-    static constexpr int OY = kM3Rows - 2 * (T - 1);         // output rows per work item
-    static constexpr int U = 6;   // steps per unrolled group: ring slots mod 3, LDS buffers mod 2
+    static constexpr int H = 4 * RY * kM3Waves;              // rows held per work item
+    static constexpr int A0 = V * ((T - 1 + V - 1) / V);     // halo columns (chunk-aligned)
+    static constexpr int OW = W - 2 * A0;                    // output columns of an inner strip
+    static constexpr int OY = H - 2 * (T - 1);               // output rows of an inner row group
+    static constexpr int U = 6;   // steps per unrolled group: plane slots mod 6 / 3 / 2
     static constexpr int NL = T > 1 ? T - 1 : 1;             // levels 1 .. T-1 held in registers
     static_assert(T >= 1 && T + 1 <= U, "source ring holds T + 1 planes");
     static_assert(OW > 0 && OY > 0, "tile too small for this depth");
 };
+
+// LDS copies of levels 1 .. T-1: [level][step parity][row + 1][lane of the row]
+template <typename R, int T, int RY>
+using M3Sh = Chunk<R, M3<R, T, RY>::V> (*)[2][M3<R, T, RY>::H + 2][16];
 
 // Element offset of the z part (block layer and plane) of a global plane z.
 __device__ __forceinline__ int64_t plane_part(const Geom &g, int zblk, int zloc) {
@@ -81,254 +96,390 @@ __device__ __forceinline__ int64_t src_xy_part(const Geom &g, int x, int y) {
 
 // Plane cursor: global plane q (any integer), advanced one plane at a time;
 // off / soff are the element offsets of plane q clamped to [-1, n_z] in the
-// state buffers and (0 for the ring planes) in the source (the ring planes
-// stand in for the planes beyond them).
+// state buffers and to [0, n_z - 1] in the source.  Moving into the next
+// block layer adds the layer's step less the planes already counted.
 struct ZCur {
-    int q, blk, loc;
+    int q, loc, left;  // global plane, plane within the block, blocks after this one
     int64_t off, soff;
-    __device__ __forceinline__ void set(const Geom &g) {
-        off = plane_part(g, blk, loc);
-        soff = q >= 0 && q < g.n[2] ? src_plane_part(g, blk, loc) : 0;
-    }
     __device__ __forceinline__ void init(const Geom &g, int q0) {
         q = q0;
+        int blk;
         owner(q0 < -1 ? -1 : q0 > g.n[2] ? g.n[2] : q0, g.e[2], g.nb[2], blk, loc);
-        set(g);
+        left = g.nb[2] - 1 - blk;
+        off = plane_part(g, blk, loc);
+        int sblk, sloc;
+        owner(q0 < 0 ? 0 : q0 > g.n[2] - 1 ? g.n[2] - 1 : q0, g.e[2], g.nb[2], sblk, sloc);
+        soff = src_plane_part(g, sblk, sloc);
     }
     __device__ __forceinline__ void advance(const Geom &g) {
+        const int64_t layer = (int64_t)g.nb[1] * g.nb[0];
+        const int64_t splane = (int64_t)g.e[1] * g.e[0];
         const bool moves = q >= -1 && q < g.n[2];
+        const bool smoves = q >= 0 && q < g.n[2] - 1;
+        const bool wrap = loc + 1 >= g.e[2] && left > 0;
+        const int64_t d = wrap ? layer * g.bstride - (g.e[2] - 1) * g.plane : g.plane;
+        const int64_t sd = wrap ? layer * g.sstride - (g.e[2] - 1) * splane : splane;
+        off += moves ? d : 0;
+        soff += smoves ? sd : 0;
+        loc = moves ? (wrap ? 0 : loc + 1) : loc;
+        left -= moves && wrap ? 1 : 0;
         ++q;
-        if (moves) {
-            ++loc;
-            if (loc >= g.e[2] && blk < g.nb[2] - 1) {
-                ++blk;
-                loc = 0;
-                set(g);
-            } else {
-                off += g.plane;
-                soff = q >= 0 && q < g.n[2] ? (q == 0 ? src_plane_part(g, blk, loc)
-                                                      : soff + (int64_t)g.e[1] * g.e[0])
-                                            : 0;
-            }
-        }
     }
 };
 
-// Per-lane constants of a work item.
+// Per-lane constants of a work item.  Offsets are bytes from the start of a
+// plane; OFF is 32 bits unless a z layer of blocks spans 4 GiB or more.
+template <typename OFF, int RY>
 struct M3Lane {
-    int64_t c_off, h_off, e_off, b_off;  // own row, halo row (loaders), edge cell, source
-    int k;                               // LDS row slot of the lane's own row (1 .. 16)
-    int hk;                              // LDS slot of the lane's halo load (0, 17; own slot: none)
-    bool ld, lde, ldb;                   // lane loads interior/east-ring, edge, source
-    bool upd[8];                         // element is an interior cell
-    bool mine[8];                        // element is an output cell of this work item
-    bool out_lane;                       // the whole chunk is output (interior tiles)
+    OFF c[RY], up, dn, e[RY], b[RY];  // own rows, rows y-1 / y+1, edge cells, source rows
+    uint32_t st[RY];                  // own rows' whole-chunk stores (kNoStore: none)
+    int lr, cx;                       // LDS row slot of the first own row, lane within the row
+    int nxr;                          // interior columns from the lane's first on (EDGE)
+    int nyr;                          // interior rows from the lane's first on (EDGE)
+    int o0, o1;                       // own rows [o0, o1) are outputs (0 .. RY)
+    bool out_lane;                    // the lane's columns are outputs (EDGE: those < nxr)
+    bool ylo, yhi;                    // lane keeps the ring row below / above its rows
+    bool wring;                       // the wave has such lanes (uniform)
 };
 
-template <typename R, int T>
+template <typename R, int T, int RY>
 struct M3Regs {
-    using S = M3<R, T>;
-    Chunk<R, S::V> l0[3];       // level 0: planes by plane index mod 3
-    Chunk<R, S::V> halo[3];     // level-0 halo row (loader lanes)
-    R edge[3];                  // level-0 cell just outside the tile (row ends)
-    Chunk<R, S::V> bq[S::U];    // source planes by plane index mod U
-    Chunk<R, S::V> lv[S::NL][3];  // levels 1 .. T-1: planes by step mod 3
-    double acc;                 // residual partial (level 1)
+    using S = M3<R, T, RY>;
+    R l0[S::U][RY][S::V];      // level 0: planes by plane mod 6 (four live)
+    R up[2][S::V], dn[2][S::V];  // level 0: rows y-1 / y+1 by plane mod 2
+    R ed[S::U][RY];            // level 0: cell just outside the tile (row ends)
+    R bq[S::U][RY][S::V];      // source planes by plane mod 6
+    R lv[S::NL][2][RY][S::V];  // levels 1 .. T-1: the two newest planes, by step mod 2
+    R zm[2][RY][S::V];         // the plane before them, read back from LDS, by level mod 2
+    R so[2][S::V], no[2][S::V];  // outer rows read from LDS, by level mod 2
+    int64_t off[S::U];         // state offsets of planes z - T + 1 .. z + 2, by plane mod 6
+    double acc;                // residual partial (level 1)
 };
 
-template <typename R, int T>
-using M3Sh = Chunk<R, 16 / sizeof(R)> (*)[2][kM3Rows + 2][16];
-
-// Store a register chunk into LDS element by element (one 16-byte write).
-template <typename R, int V>
-__device__ __forceinline__ void lds_put(Chunk<R, V> &dst, const Chunk<R, V> &src) {
+// A lane's chunk / cell at byte offset `off` from a uniform base.  32-bit
+// offsets go through a buffer descriptor of the plane (scalar base, vector
+// offset): no address arithmetic and one register per offset.
+template <typename R, int V, typename OFF>
+__device__ __forceinline__ void m3_get(R (&dst)[V], const R *base, OFF off) {
     Chunk<R, V> t;
+    if constexpr (sizeof(OFF) == 4)
+        t = buffer_get<Chunk<R, V>>(base, off);
+    else
+        t = *reinterpret_cast<const Chunk<R, V> *>(reinterpret_cast<const char *>(base) + off);
 #pragma unroll
-    for (int v = 0; v < V; ++v) t.v[v] = src.v[v];
-    dst = t;
+    for (int v = 0; v < V; ++v) dst[v] = t.v[v];
+}
+template <typename R, typename OFF>
+__device__ __forceinline__ R m3_get1(const R *base, OFF off) {
+    if constexpr (sizeof(OFF) == 4)
+        return buffer_get<R>(base, off);
+    else
+        return *reinterpret_cast<const R *>(reinterpret_cast<const char *>(base) + off);
 }
 
-// Issue the loads of plane lc.q into slot J1 (level 0, halo, edge) and
-// source slot JB, then advance the cursor.
-template <typename R, int T, bool EDGE, bool SRC, int J1, int JB>
-__device__ __forceinline__ void m3_load(const Geom &g, const R *__restrict__ uin,
-                                        const R *__restrict__ bsrc, const M3Lane &L,
-                                        M3Regs<R, T> &m, ZCur &lc) {
-    constexpr int V = M3<R, T>::V;
-    using C = Chunk<R, V>;
-    const int64_t pp = lc.off;
-    // element-wise copies keep every ring slot in registers
-    const C c = *reinterpret_cast<const C *>(uin + pp + L.c_off);
-    // every lane loads (non-loader lanes their own row again), so no load
-    // sits under a per-lane branch
-    const C h = *reinterpret_cast<const C *>(uin + pp + L.h_off);
-    const R e = uin[pp + L.e_off];
+// Own rows of the cursor's plane into plane slot S6, then advance.
+template <typename R, int T, int RY, int S6, typename OFF>
+__device__ __forceinline__ void m3_load_own(const Geom &g, const R *__restrict__ uin,
+                                            const M3Lane<OFF, RY> &L, M3Regs<R, T, RY> &m,
+                                            ZCur &lc) {
+    m.off[S6] = lc.off;
+    const R *p = uin + lc.off;
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-        m.l0[J1].v[v] = (EDGE && !L.ld) ? (R)0 : c.v[v];
-        m.halo[J1].v[v] = (EDGE && !L.ld) ? (R)0 : h.v[v];
-    }
-    m.edge[J1] = (EDGE && !L.lde) ? (R)0 : e;
-    if constexpr (SRC) {
-        const C b = *reinterpret_cast<const C *>(bsrc + lc.soff + L.b_off);
-#pragma unroll
-        for (int v = 0; v < V; ++v) m.bq[JB].v[v] = (EDGE && !L.ldb) ? (R)0 : b.v[v];
-    }
+    for (int j = 0; j < RY; ++j) m3_get<R, M3<R, T, RY>::V>(m.l0[S6][j], p, L.c[j]);
     lc.advance(g);
 }
 
+// Outer rows, edge cells and source of the plane at (off, soff) into slots.
+template <typename R, int T, int RY, bool SRC, int S6, int S2, typename OFF>
+__device__ __forceinline__ void m3_load_rest(const R *__restrict__ uin,
+                                             const R *__restrict__ bsrc, int64_t off,
+                                             int64_t soff, const M3Lane<OFF, RY> &L,
+                                             M3Regs<R, T, RY> &m) {
+    const R *p = uin + off;
+    m3_get<R, M3<R, T, RY>::V>(m.up[S2], p, L.up);
+    m3_get<R, M3<R, T, RY>::V>(m.dn[S2], p, L.dn);
+#pragma unroll
+    for (int j = 0; j < RY; ++j)
+        m.ed[S6][j] = m3_get1<R>(p, L.e[j]);
+    if constexpr (SRC) {
+#pragma unroll
+        for (int j = 0; j < RY; ++j) m3_get<R, M3<R, T, RY>::V>(m.bq[S6][j], bsrc + soff, L.b[j]);
+    }
+}
+
+template <typename R, int V>
+__device__ __forceinline__ void lds_put(Chunk<R, V> &dst, const R (&src)[V]) {
+    Chunk<R, V> t;
+#pragma unroll
+    for (int v = 0; v < V; ++v) t.v[v] = src[v];
+    dst = t;
+}
+template <typename R, int V>
+__device__ __forceinline__ void lds_get(const Chunk<R, V> &src, R (&dst)[V]) {
+    const Chunk<R, V> t = src;
+#pragma unroll
+    for (int v = 0; v < V; ++v) dst[v] = t.v[v];
+}
+
+// What level S takes from LDS: the outer rows of plane z - S + 1 of level
+// S - 1, written one step ago, and the lane's own rows of plane z - S, written
+// two steps ago (kept there instead of in registers: a level then holds two
+// planes, not three).  Read one
+// level ahead of their use, so that the LDS latency overlaps the arithmetic of
+// the level in between, and before level S - 1 overwrites plane z - S.
+template <typename R, int T, int RY, int J, int S, typename OFF>
+__device__ __forceinline__ void m3_read_rows(const M3Lane<OFF, RY> &L, M3Regs<R, T, RY> &m,
+                                             M3Sh<R, T, RY> sh) {
+    constexpr int V = M3<R, T, RY>::V;
+    lds_get<R, V>(sh[S - 2][J & 1][L.lr - 1][L.cx], m.so[S & 1]);
+    lds_get<R, V>(sh[S - 2][J & 1][L.lr + RY][L.cx], m.no[S & 1]);
+#pragma unroll
+    for (int j = 0; j < RY; ++j)
+        lds_get<R, V>(sh[S - 2][(J + 1) & 1][L.lr + j][L.cx], m.zm[S & 1][j]);
+}
+
 // Level S of step J (z = base + J): plane p = z - S + 1 of level S from the
-// planes p-1, p, p+1 of level S-1 (registers) and the rows y-1, y+1 of plane
-// p of level S-1 (LDS buffer J & 1).
-template <typename R, int T, int MODE, bool EDGE, bool RES, int J, int S>
-__device__ __forceinline__ void m3_level(const Geom &g, R *__restrict__ uout, const M3Lane &L,
-                                         M3Regs<R, T> &m, M3Sh<R, T> sh, const int z,
-                                         const int oz0, const int oz1, ZCur &sc, bool nt) {
-    using M = M3<R, T>;
-    constexpr int V = M::V;
+// planes p-1, p, p+1 of level S-1.  EDGE: the tile holds ring columns or rows,
+// or its first / last column borders the ring.
+template <typename R, int T, int RY, int MODE, bool EDGE, bool RES, int J, int S,
+          typename OFF>
+__device__ __forceinline__ void m3_level(const Geom &g, R *__restrict__ uout,
+                                         const M3Lane<OFF, RY> &L, M3Regs<R, T, RY> &m,
+                                         M3Sh<R, T, RY> sh, const int z, const int oz0,
+                                         const int oz1, const int64_t out_off) {
+    using M = M3<R, T, RY>;
+    constexpr int V = M::V, U = M::U;
     constexpr bool SRC = MODE == 1;
-    using C = Chunk<R, V>;
     if constexpr (S <= T) {
         const int p = z - S + 1;
-        const int cx = threadIdx.x & 15;
-        C zm, zc, zp;
-        R eo = (R)0;
-        if constexpr (S == 1) {
-            zm = m.l0[(J + 2) % 3];
-            zc = m.l0[J % 3];
-            zp = m.l0[(J + 1) % 3];
-            eo = m.edge[J % 3];
-        } else {
-            zm = m.lv[S - 2][(J + 1) % 3];  // step J - 2
-            zc = m.lv[S - 2][(J + 2) % 3];  // step J - 1
-            zp = m.lv[S - 2][J % 3];        // this step
-        }
-        const C so = sh[S - 1][J & 1][L.k - 1][cx];
-        const C no = sh[S - 1][J & 1][L.k + 1][cx];
-        C bb;
-        if constexpr (SRC) bb = m.bq[(J - S + 1 + M::U) % M::U];
-        const R left = row_shift_up(eo, zc.v[V - 1]);
-        const R right = row_shift_down(eo, zc.v[0]);
-        const R w = (R)1 / (R)6;
-        const bool pin = p >= 0 && p < g.n[2];
-        const bool res_plane = RES && S == 1 && p >= oz0 && p < oz1;
-        C out;
+        constexpr int SP = (J - S + 1 + U) % U;  // slot of plane p (level 0 data)
+        R zm[RY][V], zc[RY][V], zp[RY][V], so[V], no[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const R Wv = v > 0 ? zc.v[v - 1] : left;
-            const R Ev = v < V - 1 ? zc.v[v + 1] : right;
-            const R s = ((Wv + Ev) + (so.v[v] + no.v[v])) + (zm.v[v] + zp.v[v]);
-            R o = SRC ? (s + bb.v[v]) * w : s * w;
-            if (res_plane) {
-                // residual of the input state, FP64 from widened values
-                const double sd = (((double)Wv + (double)Ev) + ((double)so.v[v] + (double)no.v[v])) +
-                                  ((double)zm.v[v] + (double)zp.v[v]);
-                const double bd = SRC ? (double)bb.v[v] : 0.0;
-                const double r = bd - (6.0 * (double)zc.v[v] - sd);
-                m.acc += L.mine[v] ? r * r : 0.0;
-            }
-            // ring cells and cells beyond the ring keep their values
-            if constexpr (EDGE) o = L.upd[v] ? o : zc.v[v];
-            out.v[v] = o;
-        }
-        if (!pin) out = zc;  // a ring plane (or beyond) keeps its values
-        if constexpr (S < T) {
-            m.lv[S - 1][J % 3] = out;
-        } else {
-            if (uout && p >= oz0 && p < oz1) {
-                R *q = uout + sc.off + L.c_off;
-                if (!EDGE) {
-                    if (L.out_lane) {
-                        if (nt)
-                            store_nt16(reinterpret_cast<C *>(q), out);
-                        else
-                            *reinterpret_cast<C *>(q) = out;
-                    }
+        for (int j = 0; j < RY; ++j)
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                if constexpr (S == 1) {
+                    zm[j][v] = m.l0[(J + U - 1) % U][j][v];
+                    zc[j][v] = m.l0[J % U][j][v];
+                    zp[j][v] = m.l0[(J + 1) % U][j][v];
                 } else {
+                    zm[j][v] = m.zm[S & 1][j][v];               // step J - 2
+                    zc[j][v] = m.lv[S - 2][(J + 1) % 2][j][v];  // step J - 1
+                    zp[j][v] = m.lv[S - 2][J % 2][j][v];        // this step
+                }
+            }
+        if constexpr (S == 1) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                so[v] = m.up[J % 2][v];
+                no[v] = m.dn[J % 2][v];
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                so[v] = m.so[S & 1][v];
+                no[v] = m.no[S & 1][v];
+            }
+            if constexpr (S < T) {
+                m3_read_rows<R, T, RY, J, S + 1>(L, m, sh);
+                // keep the reads ahead of this level's arithmetic
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const R w = (R)1 / (R)6;
+        const bool res_plane = RES && S == 1 && p >= oz0 && p < oz1;
+        R out[RY][V];
+#pragma unroll
+        for (int j = 0; j < RY; ++j) {
+            // the cell outside the tile: needed by level 1, and by every
+            // level where it is the domain's ring
+            const R eo = (S == 1 || EDGE) ? m.ed[SP][j] : (R)0;
+            const R left = row_shift_up(eo, zc[j][V - 1]);
+            const R right = row_shift_down(eo, zc[j][0]);
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const R Wv = v > 0 ? zc[j][v - 1] : left;
+                const R Ev = v < V - 1 ? zc[j][v + 1] : right;
+                const R Sv = j > 0 ? zc[j - 1][v] : so[v];
+                const R Nv = j < RY - 1 ? zc[j + 1][v] : no[v];
+                const R s = ((Wv + Ev) + (Sv + Nv)) + (zm[j][v] + zp[j][v]);
+                R o = SRC ? (s + m.bq[SP][j][v]) * w : s * w;
+                if constexpr (RES && S == 1) {
+                    if (res_plane) {
+                        // residual of the input state, FP64 from widened values
+                        const double sd = (((double)Wv + (double)Ev) + ((double)Sv + (double)Nv)) +
+                                          ((double)zm[j][v] + (double)zp[j][v]);
+                        const double bd = SRC ? (double)m.bq[SP][j][v] : 0.0;
+                        const double r = bd - (6.0 * (double)zc[j][v] - sd);
+                        const bool mine = L.out_lane && j >= L.o0 && j < L.o1 &&
+                                          (!EDGE || v < L.nxr);
+                        m.acc += mine ? r * r : 0.0;
+                    }
+                }
+                // ring cells and cells beyond the ring keep their values
+                if constexpr (EDGE) o = (v < L.nxr && j < L.nyr) ? o : zc[j][v];
+                out[j][v] = o;
+            }
+        }
+        // the empty asm keeps the arithmetic above in one block with its DPP
+        // shifts; without it the compiler moves it under the test below and
+        // cannot fold the shifts into the additions
+#pragma unroll
+        for (int j = 0; j < RY; ++j)
+#pragma unroll
+            for (int v = 0; v < V; ++v) asm("" : "+v"(out[j][v]));
+        if (__builtin_expect(p < 0 || p >= g.n[2], 0)) {  // a ring plane (or beyond) keeps its values
+#pragma unroll
+            for (int j = 0; j < RY; ++j)
+#pragma unroll
+                for (int v = 0; v < V; ++v) out[j][v] = zc[j][v];
+        }
+        if constexpr (S < T) {
+#pragma unroll
+            for (int j = 0; j < RY; ++j)
+#pragma unroll
+                for (int v = 0; v < V; ++v) m.lv[S - 1][J % 2][j][v] = out[j][v];
+        } else {
+            const bool on = uout && p >= oz0 && p < oz1;
+            if constexpr (sizeof(OFF) == 4) {
+#pragma unroll
+                for (int j = 0; j < RY; ++j) {
+                    Chunk<R, V> t;
+#pragma unroll
+                    for (int v = 0; v < V; ++v) t.v[v] = out[j][v];
+                    buffer_put16(uout + out_off, L.st[j], on, t);
+                }
+            }
+            // chunks that hold the east ring column are stored cell by cell
+            // (with 64-bit offsets, every chunk)
+            if (on && L.out_lane && (sizeof(OFF) != 4 || (EDGE && L.nxr < V))) {
+                R *q = uout + out_off;
+#pragma unroll
+                for (int j = 0; j < RY; ++j) {
+                    if (j < L.o0 || j >= L.o1) continue;
+                    R *d = reinterpret_cast<R *>(reinterpret_cast<char *>(q) + L.c[j]);
 #pragma unroll
                     for (int v = 0; v < V; ++v)
-                        if (L.mine[v]) q[v] = out.v[v];
+                        if (v < L.nxr) d[v] = out[j][v];
                 }
             }
         }
-        m3_level<R, T, MODE, EDGE, RES, J, S + 1>(g, uout, L, m, sh, z, oz0, oz1, sc, nt);
+        if constexpr (S == 1 && T > 1) {
+            __syncthreads();
+            m3_read_rows<R, T, RY, J, 2>(L, m, sh);
+        }
+        if constexpr (S < T) {
+            // this plane's boundary rows for the neighbouring lanes' next
+            // step; where the tile ends at the ring in y, also the ring row,
+            // handed on from this level's own neighbour row
+            auto &rows = sh[S - 1][(J + 1) & 1];
+            if constexpr (RY > 1) lds_put<R, V>(rows[L.lr + RY - 1][L.cx], out[RY - 1]);
+            lds_put<R, V>(rows[L.lr][L.cx], out[0]);
+            if (L.wring) {
+                if (L.ylo) lds_put<R, V>(rows[L.lr - 1][L.cx], so);
+                if (L.yhi) lds_put<R, V>(rows[L.lr + RY][L.cx], no);
+            }
+        }
+        m3_level<R, T, RY, MODE, EDGE, RES, J, S + 1>(g, uout, L, m, sh, z, oz0, oz1, out_off);
     }
 }
 
-template <typename R, int T, int MODE, bool EDGE, bool RES, int J>
+template <typename R, int T, int RY, int MODE, bool EDGE, bool RES, int J,
+          typename OFF>
 __device__ __forceinline__ void m3_steps(const Geom &g, const R *__restrict__ uin,
                                          R *__restrict__ uout, const R *__restrict__ bsrc,
-                                         const M3Lane &L, M3Regs<R, T> &m, M3Sh<R, T> sh,
-                                         const int base, const int zend, const int oz0,
-                                         const int oz1, ZCur &lc, ZCur &sc, bool nt) {
-    using M = M3<R, T>;
+                                         double *__restrict__ res_slot,
+                                         const M3Lane<OFF, RY> &L, M3Regs<R, T, RY> &m,
+                                         M3Sh<R, T, RY> sh, const int base, const int zend,
+                                         const int oz0, const int oz1, ZCur &lc, int64_t &soff1) {
+    using M = M3<R, T, RY>;
     constexpr bool SRC = MODE == 1;
-    if constexpr (J < M::U) {
+    constexpr int U = M::U;
+    if constexpr (J < U) {
         const int z = base + J;
-        if (z > zend) return;
-        const int cx = threadIdx.x & 15;
-        // plane z + 1 of level 0, its halo row, edge cell and source
-        m3_load<R, T, EDGE, SRC, (J + 1) % 3, (J + 1) % M::U>(g, uin, bsrc, L, m, lc);
-        // level 0's plane z and levels 1 .. T-1's planes of the previous step
-        // go to LDS buffer J & 1 for their y neighbours
-        lds_put(sh[0][J & 1][L.k][cx], m.l0[J % 3]);
-        lds_put(sh[0][J & 1][L.hk][cx], m.halo[J % 3]);  // non-loaders: their own row again
-#pragma unroll
-        for (int s = 1; s < T; ++s) lds_put(sh[s][J & 1][L.k][cx], m.lv[s - 1][(J + 2) % 3]);
-        __syncthreads();
-        m3_level<R, T, MODE, EDGE, RES, J, 1>(g, uout, L, m, sh, z, oz0, oz1, sc, nt);
-        sc.advance(g);
-        m3_steps<R, T, MODE, EDGE, RES, J + 1>(g, uin, uout, bsrc, L, m, sh, base, zend, oz0, oz1,
-                                               lc, sc, nt);
+        if (z > zend) {
+            if constexpr (RES) {
+                const double a = wave_sum(m.acc);
+                if ((threadIdx.x & 63) == 0) *res_slot = a;
+            }
+            __builtin_amdgcn_endpgm();
+        }
+        // the cursor is at plane z + 2; soff1 is plane z + 1
+        const int64_t out_off = m.off[(J - T + 1 + U) % U], soff2 = lc.soff;
+        m3_load_rest<R, T, RY, SRC, (J + 1) % U, (J + 1) % 2>(uin, bsrc, m.off[(J + 1) % U], soff1,
+                                                             L, m);
+        m3_load_own<R, T, RY, (J + 2) % U>(g, uin, L, m, lc);
+        soff1 = soff2;
+        m3_level<R, T, RY, MODE, EDGE, RES, J, 1>(g, uout, L, m, sh, z, oz0, oz1, out_off);
+        m3_steps<R, T, RY, MODE, EDGE, RES, J + 1>(g, uin, uout, bsrc, res_slot, L, m, sh, base,
+                                                  zend, oz0, oz1, lc, soff1);
     }
 }
 
-template <typename R, int T, int MODE, bool EDGE, bool RES>
+template <typename R, int T, int RY, int MODE, bool EDGE, bool RES, typename OFF>
 __device__ __forceinline__ void m3_body(const Geom &g, const R *__restrict__ uin,
                                         R *__restrict__ uout, const R *__restrict__ bsrc,
-                                        double *__restrict__ res_slot, const M3Lane &L, int oz0,
-                                        int oz1, bool nt, M3Sh<R, T> sh) {
-    using M = M3<R, T>;
-    constexpr int V = M::V;
+                                        double *__restrict__ res_slot, const M3Lane<OFF, RY> &L,
+                                        int oz0, int oz1, M3Sh<R, T, RY> sh) {
+    using M = M3<R, T, RY>;
+    constexpr int V = M::V, U = M::U;
     constexpr bool SRC = MODE == 1;
-    M3Regs<R, T> m;
+    M3Regs<R, T, RY> m;
 #pragma unroll
     for (int s = 0; s < M::NL; ++s)
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
+        for (int k = 0; k < 2; ++k)
 #pragma unroll
-            for (int v = 0; v < V; ++v) m.lv[s][k].v[v] = (R)0;
+            for (int j = 0; j < RY; ++j)
+#pragma unroll
+                for (int v = 0; v < V; ++v) m.lv[s][k][j][v] = (R)0;
     m.acc = 0.0;
-    // steps zs .. zend: level T computes planes oz0 .. oz1-1; planes zs-1 and
-    // zs are loaded before the first step
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+#pragma unroll
+        for (int j = 0; j < RY; ++j) {
+            m.ed[k][j] = (R)0;
+#pragma unroll
+            for (int v = 0; v < V; ++v) m.bq[k][j][v] = (R)0;
+        }
+    // steps zs .. zend: level T computes planes oz0 .. oz1-1; planes zs-1 ..
+    // zs+1 and the rest of plane zs are loaded before the first step
     const int zs = oz0 - T + 1;
     const int zend = oz1 + T - 2;
-    ZCur lc, sc;
+    ZCur lc;
     lc.init(g, zs - 1);
-    m3_load<R, T, EDGE, SRC, 2, M::U - 1>(g, uin, bsrc, L, m, lc);
-    m3_load<R, T, EDGE, SRC, 0, 0>(g, uin, bsrc, L, m, lc);
-    sc.init(g, zs - T + 1);  // the plane level T computes at the first step
-    for (int base = zs; base <= zend; base += M::U)
-        m3_steps<R, T, MODE, EDGE, RES, 0>(g, uin, uout, bsrc, L, m, sh, base, zend, oz0, oz1, lc,
-                                           sc, nt);
-    if (RES) {
-        const double a = wave_sum(m.acc);
-        if ((threadIdx.x & 63) == 0) *res_slot = a;
-    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) m.off[k] = lc.off;
+    m3_load_own<R, T, RY, U - 1>(g, uin, L, m, lc);
+    int64_t soff1 = lc.soff;
+    m3_load_own<R, T, RY, 0>(g, uin, L, m, lc);
+    m3_load_rest<R, T, RY, SRC, 0, 0>(uin, bsrc, m.off[0], soff1, L, m);
+    soff1 = lc.soff;
+    m3_load_own<R, T, RY, 1>(g, uin, L, m, lc);
+    for (int base = zs;; base += U)
+        m3_steps<R, T, RY, MODE, EDGE, RES, 0>(g, uin, uout, bsrc, res_slot, L, m, sh, base, zend,
+                                              oz0, oz1, lc, soff1);
+}
+
+// Strips of columns and groups of rows covering n cells: `hold` cells held
+// per tile, `out` of them outputs of an inner tile; the first and last tile
+// also output the (hold - out) / 2 cells next to the ring.
+__host__ __device__ inline int m3_tiles(int n, int hold, int out) {
+    const int rest = n - (hold - out);
+    return rest <= out ? 1 : (rest + out - 1) / out;
 }
 
 // Work item (one workgroup of 8 waves) number `item` of a grid cut into
 // ngrp row groups (fastest), nstrips column strips and z segments of `zseg`
-// output planes; wave q takes rows y0+4q .. y0+4q+3.  The residual partials
-// are per wave: work item i owns partials 8i .. 8i+7 (res points at them).
-template <typename R, int T, int MODE, bool RES>
+// output planes.  The residual partials are per wave: work item i owns
+// partials 8i .. 8i+7 (res points at them).
+template <typename R, int T, int RY, int MODE, bool RES, typename OFF>
 __device__ __forceinline__ void m3_item(const Geom &g, const R *__restrict__ uin,
                                         R *__restrict__ uout, const R *__restrict__ bsrc,
                                         double *__restrict__ res, int item, int nstrips, int ngrp,
-                                        int zseg, int nt, M3Sh<R, T> sh) {
-    using M = M3<R, T>;
-    constexpr int V = M::V;
-    constexpr int W = M::W;
+                                        int zseg, M3Sh<R, T, RY> sh) {
+    using M = M3<R, T, RY>;
+    constexpr int V = M::V, W = M::W, H = M::H;
     const int grp = item % ngrp;
     const int rest = item / ngrp;
     const int strip = rest % nstrips;
@@ -337,89 +488,82 @@ __device__ __forceinline__ void m3_item(const Geom &g, const R *__restrict__ uin
     const int lane = threadIdx.x & 63;
     const int ry = lane >> 4, cx = lane & 15;
     const int nx = g.n[0], ny = g.n[1];
-    const int a = strip * M::OW - M::A0;  // first column held
+    const int a = strip * M::OW;           // first column held
     const int c = a + cx * V;
-    const int y0 = grp * M::OY - (T - 1);  // first row held
-    const int kk = 4 * wv + ry;            // row within the tile
+    const int y0 = grp * M::OY;            // first row held
+    const int kk = (4 * wv + ry) * RY;     // the lane's first row within the tile
     const int yy = y0 + kk;
     auto clampy = [&](int y) { return y < -1 ? -1 : y > ny ? ny : y; };
-    M3Lane L;
-    L.k = 1 + kk;
+    M3Lane<OFF, RY> L;
+    L.cx = cx;
+    L.lr = 1 + kk;
     // chunk holds interior cells or ring / outside cells at in-bounds addresses
-    L.ld = c <= nx;
-    const int cl = L.ld ? c : 0;
-    L.c_off = xy_part(g, cl, clampy(yy));
-    L.hk = L.k;
-    L.h_off = L.c_off;
-    if (wv == 0 && ry == 0) {
-        L.hk = 0;
-        L.h_off = xy_part(g, cl, clampy(y0 - 1));
-    } else if (wv == kM3Waves - 1 && ry == 3) {
-        L.hk = kM3Rows + 1;
-        L.h_off = xy_part(g, cl, clampy(y0 + kM3Rows));
-    }
+    const int cl = c <= nx ? c : 0;
     // the first / last lane of each 16-lane row fetch the cells just west /
     // east of the tile; the others re-read their own first cell
     const int xe = cx == 0 ? a - 1 : cx == 15 ? a + W : c;
-    L.lde = xe >= -1 && xe <= nx && (cx == 0 || cx == 15 || L.ld);
-    L.e_off = xy_part(g, L.lde ? xe : 0, clampy(yy));
-    const bool row_in = yy >= 0 && yy < ny;
-    L.ldb = c >= 0 && c < nx && row_in;
-    L.b_off = src_xy_part(g, L.ldb ? c : 0, L.ldb ? yy : 0);
-    const bool out_row = kk >= T - 1 && kk < T - 1 + M::OY;
-    L.out_lane = out_row && cx * V >= M::A0 && cx * V < M::A0 + M::OW;
+    const int xel = xe <= nx ? xe : 0;
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
-        L.upd[v] = v < V && row_in && c + v >= 0 && c + v < nx;
-        L.mine[v] = L.upd[v] && L.out_lane;
+    for (int j = 0; j < RY; ++j) {
+        const int y = clampy(yy + j);
+        L.c[j] = (OFF)(xy_part(g, cl, y) * (int64_t)sizeof(R));
+        L.e[j] = (OFF)(xy_part(g, xel, y) * (int64_t)sizeof(R));
+        const bool lb = c < nx && yy + j < ny;
+        L.b[j] = (OFF)(src_xy_part(g, lb ? c : 0, lb ? yy + j : 0) * (int64_t)sizeof(R));
     }
+    L.up = (OFF)(xy_part(g, cl, clampy(yy - 1)) * (int64_t)sizeof(R));
+    L.dn = (OFF)(xy_part(g, cl, clampy(yy + RY)) * (int64_t)sizeof(R));
+    L.nxr = nx - c;
+    L.nyr = ny - yy;
+    // output rows and columns: less T-1 rows / A0 columns where the tile
+    // continues beyond, up to the ring where it does not
+    const int ylo = grp == 0 ? 0 : T - 1;
+    const int yhi = grp == ngrp - 1 ? ny - y0 : H - (T - 1);
+    L.o0 = ylo - kk;
+    L.o1 = yhi - kk;
+    const int xlo = strip == 0 ? 0 : M::A0;
+    const int xhi = strip == nstrips - 1 ? nx - a : W - M::A0;
+    L.out_lane = cx * V >= xlo && cx * V < xhi;
+#pragma unroll
+    for (int j = 0; j < RY; ++j)
+        L.st[j] = L.out_lane && j >= L.o0 && j < L.o1 && L.nxr >= V ? (uint32_t)L.c[j] : kNoStore;
+    // the ring row y = -1 lies just below the first tile, y = ny just above
+    // a tile that ends with row ny - 1
+    L.ylo = y0 == 0 && kk == 0;
+    L.yhi = y0 + H == ny && kk + RY == H;
+    L.wring = (y0 == 0 && wv == 0) || (y0 + H == ny && wv == kM3Waves - 1);
     const int oz0 = zs * zseg;
     const int oz1 = oz0 + zseg < g.n[2] ? oz0 + zseg : g.n[2];
     double *slot = RES ? res + (int64_t)item * kM3Waves + wv : nullptr;
-    const bool edge = a < 0 || a + W > nx || y0 < 0 || y0 + kM3Rows > ny;
-    const bool ntb = nt != 0;
+    const bool edge = a == 0 || a + W >= nx || y0 + H > ny;
     if (edge)
-        m3_body<R, T, MODE, true, RES>(g, uin, uout, bsrc, slot, L, oz0, oz1, ntb, sh);
+        m3_body<R, T, RY, MODE, true, RES>(g, uin, uout, bsrc, slot, L, oz0, oz1, sh);
     else
-        m3_body<R, T, MODE, false, RES>(g, uin, uout, bsrc, slot, L, oz0, oz1, ntb, sh);
+        m3_body<R, T, RY, MODE, false, RES>(g, uin, uout, bsrc, slot, L, oz0, oz1, sh);
 }
 
-// Waves per SIMD the pass kernels are compiled for.  FP32 at depths up to 4:
-// four (two workgroups per CU; their planes take at most 68 KiB of LDS), so
-// that one workgroup's waves compute while the other's wait at the per-step
-// barrier.  This caps the kernels at 128 VGPRs, which the FP32 Poisson pass
-// with the folded residual (131 otherwise, one workgroup per CU) meets
-// without spilling: 512^3 FP32 went from 0.672 to 0.627 ms per depth-4 pass.
-// In FP64 the cap spilled registers and was 1% slower, so FP64 and depth 5
-// keep two (the least an eight-wave workgroup implies).
-template <typename R, int T>
-constexpr int m3_waves_per_simd() {
-    return sizeof(R) == 4 && T <= 4 ? 4 : 2;
-}
-
-template <typename R, int T, int MODE, bool RES>
-__global__ __launch_bounds__(kM3Threads) __attribute__((amdgpu_waves_per_eu(m3_waves_per_simd<R, T>()))) void k_march3d(Geom g, const R *__restrict__ uin,
-                                                 R *__restrict__ uout,
-                                                 const R *__restrict__ bsrc,
-                                                 double *__restrict__ res, int nstrips, int ngrp,
-                                                 int zseg, int nitems, int nt) {
-    // per level 0 .. T-1: two plane buffers of rows y0-1 .. y0+kM3Rows
-    __shared__ Chunk<R, M3<R, T>::V> sh[T][2][kM3Rows + 2][16];
+template <typename R, int T, int RY, int MODE, bool RES, typename OFF>
+__global__ __launch_bounds__(kM3Threads) __attribute__((amdgpu_waves_per_eu(2)))
+void k_march3d(Geom g, const R *__restrict__ uin, R *__restrict__ uout,
+               const R *__restrict__ bsrc, double *__restrict__ res, int nstrips, int ngrp,
+               int zseg, int nitems) {
+    using M = M3<R, T, RY>;
+    __shared__ Chunk<R, M::V> sh[M::NL][2][M::H + 2][16];
     const int item = xcd_logical_block(blockIdx.x, gridDim.x);
     if (item >= nitems) return;  // whole workgroup
-    m3_item<R, T, MODE, RES>(g, uin, uout, bsrc, res, item, nstrips, ngrp, zseg, nt, sh);
+    m3_item<R, T, RY, MODE, RES, OFF>(g, uin, uout, bsrc, res, item, nstrips, ngrp, zseg, sh);
 }
 
 // Batched pass: the work items of many grids in one launch (one descriptor
 // each; the deep-halo form runs every block as its own grid).  Work item w
 // belongs to grid gi with prefix[gi] <= w < prefix[gi+1]; every grid's input
 // is u[0] and its output u[1].
-template <typename R, int T, int MODE>
-__global__ __launch_bounds__(kM3Threads) __attribute__((amdgpu_waves_per_eu(m3_waves_per_simd<R, T>()))) void k_march3d_batch(const BatchGrid *__restrict__ grids,
-                                                       const int *__restrict__ prefix,
-                                                       int ngrids, int zseg, int nitems) {
-    using M = M3<R, T>;
-    __shared__ Chunk<R, M::V> sh[T][2][kM3Rows + 2][16];
+template <typename R, int T, int RY, int MODE>
+__global__ __launch_bounds__(kM3Threads) __attribute__((amdgpu_waves_per_eu(2)))
+void k_march3d_batch(const BatchGrid *__restrict__ grids, const int *__restrict__ prefix,
+                     int ngrids, int zseg, int nitems) {
+    using M = M3<R, T, RY>;
+    __shared__ Chunk<R, M::V> sh[M::NL][2][M::H + 2][16];
     const int w = xcd_logical_block(blockIdx.x, gridDim.x);
     if (w >= nitems) return;  // whole workgroup
     int lo = 0, hi = ngrids;
@@ -429,41 +573,39 @@ __global__ __launch_bounds__(kM3Threads) __attribute__((amdgpu_waves_per_eu(m3_w
     }
     const int gi = lo;
     const Geom g = grids[gi].g;
-    const int nstrips = (g.n[0] + M::OW - 1) / M::OW;
-    const int ngrp = (g.n[1] + M::OY - 1) / M::OY;
-    m3_item<R, T, MODE, false>(g, (const R *)grids[gi].u[0], (R *)grids[gi].u[1],
-                               (const R *)grids[gi].b, nullptr, w - prefix[gi], nstrips, ngrp, zseg,
-                               0, sh);
+    const int nstrips = m3_tiles(g.n[0], M::W, M::OW);
+    const int ngrp = m3_tiles(g.n[1], M::H, M::OY);
+    m3_item<R, T, RY, MODE, false, uint64_t>(g, (const R *)grids[gi].u[0], (R *)grids[gi].u[1],
+                                        (const R *)grids[gi].b, nullptr, w - prefix[gi], nstrips,
+                                        ngrp, zseg, sh);
 }
 
-template <typename R, int T>
-static void m3_shape(const Geom &g, int zseg, int &nstrips, int &ngrp, int &nzs) {
-    using M = M3<R, T>;
-    nstrips = (g.n[0] + M::OW - 1) / M::OW;
-    ngrp = (g.n[1] + M::OY - 1) / M::OY;
-    nzs = (g.n[2] + zseg - 1) / zseg;
-}
+// ---- host side -------------------------------------------------------------
+// The kernels of each depth T are compiled in an object of their own (this
+// file built with JAC_MARCH3D_DEPTH=T); the object built without it holds the
+// depth dispatch and the schedule rule.
 
 template <typename R, int T>
-static int64_t m3_work_items(const Geom &g, int zseg) {
-    int ns, ng, nz;
-    m3_shape<R, T>(g, zseg, ns, ng, nz);
-    return kM3Waves * (int64_t)ns * ng * nz;
-}
-
+hipError_t m3_launch_t(const Geom &g, const void *uin, void *uout, const void *b, double *res,
+                       const M3Plan &pl, hipStream_t st);
 template <typename R, int T>
-static hipError_t m3_launch(const Geom &g, const void *uin, void *uout, const void *b,
-                            double *res, int zseg, hipStream_t st, int64_t *nwork_out, int nt) {
-    int ns, ng, nz;
-    m3_shape<R, T>(g, zseg, ns, ng, nz);
-    const int64_t nwaves = kM3Waves * (int64_t)ns * ng * nz;
-    if (nwork_out) *nwork_out = nwaves;
-    if (nwaves > 0x7fffffff - 3) return hipErrorInvalidValue;
-    const int items = (int)(nwaves / kM3Waves);
+hipError_t m3b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, bool src, int zseg,
+                        int nitems, hipStream_t st);
+
+// Rows held per lane in the taller of the two tile heights (64 rows).
+constexpr int kM3Ry = 2;
+
+#ifdef JAC_MARCH3D_DEPTH
+
+template <typename R, int T, int RY, typename OFF>
+static hipError_t m3_launch_ry(const Geom &g, const void *uin, void *uout, const void *b,
+                               double *res, const M3Plan &pl, hipStream_t st) {
+    const int items = (int)pl.items;
     const R *bb = (const R *)b;
 #define JAC_M3(MODEV, RESV)                                                                   \
-    hipLaunchKernelGGL((k_march3d<R, T, MODEV, RESV>), dim3(items), dim3(kM3Threads), 0, st, g,      \
-                       (const R *)uin, (R *)uout, bb, res, ns, ng, zseg, items, nt)
+    hipLaunchKernelGGL((k_march3d<R, T, RY, MODEV, RESV, OFF>), dim3(items), dim3(kM3Threads), 0, \
+                       st, g, (const R *)uin, (R *)uout, bb, res, pl.nstrips, pl.ngrp, pl.zseg, \
+                       items)
     if (b && res)
         JAC_M3(1, true);
     else if (b)
@@ -477,76 +619,134 @@ static hipError_t m3_launch(const Geom &g, const void *uin, void *uout, const vo
 }
 
 template <typename R, int T>
-static hipError_t m3b_launch(const BatchGrid *grids, const int *prefix, int ngrids, bool src,
-                             int zseg, int nitems, hipStream_t st) {
+hipError_t m3_launch_t(const Geom &g, const void *uin, void *uout, const void *b, double *res,
+                       const M3Plan &pl, hipStream_t st) {
+    if (pl.wide) return m3_launch_ry<R, T, 1, uint64_t>(g, uin, uout, b, res, pl, st);
+    if (pl.ry == kM3Ry)
+        return m3_launch_ry<R, T, kM3Ry, uint32_t>(g, uin, uout, b, res, pl, st);
+    return m3_launch_ry<R, T, 1, uint32_t>(g, uin, uout, b, res, pl, st);
+}
+
+template <typename R, int T>
+hipError_t m3b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, bool src, int zseg,
+                        int nitems, hipStream_t st) {
+    constexpr int RY = kM3Ry;
     if (nitems <= 0) return hipSuccess;
     if (src)
-        hipLaunchKernelGGL((k_march3d_batch<R, T, 1>), dim3(nitems), dim3(kM3Threads), 0, st, grids,
-                           prefix, ngrids, zseg, nitems);
+        hipLaunchKernelGGL((k_march3d_batch<R, T, RY, 1>), dim3(nitems),
+                           dim3(kM3Threads), 0, st, grids, prefix, ngrids, zseg, nitems);
     else
-        hipLaunchKernelGGL((k_march3d_batch<R, T, 0>), dim3(nitems), dim3(kM3Threads), 0, st, grids,
-                           prefix, ngrids, zseg, nitems);
+        hipLaunchKernelGGL((k_march3d_batch<R, T, RY, 0>), dim3(nitems),
+                           dim3(kM3Threads), 0, st, grids, prefix, ngrids, zseg, nitems);
     return hipGetLastError();
 }
 
+#define JAC_M3_INSTANTIATE(R, T)                                                                \
+    template hipError_t m3_launch_t<R, T>(const Geom &, const void *, void *, const void *,      \
+                                          double *, const M3Plan &, hipStream_t);                \
+    template hipError_t m3b_launch_t<R, T>(const BatchGrid *, const int *, int, bool, int, int,  \
+                                           hipStream_t);
+JAC_M3_INSTANTIATE(float, JAC_MARCH3D_DEPTH)
+JAC_M3_INSTANTIATE(double, JAC_MARCH3D_DEPTH)
+
+#else  // dispatch object
+
 int march3d_max_depth() { return 5; }
+
+// Tile counts of one pass at depth T with RY rows per lane.
+template <typename R>
+static void m3_shape(const Geom &g, int T, int ry, int &nstrips, int &ngrp) {
+    const int v = 16 / (int)sizeof(R), w = 16 * v, h = 32 * ry;
+    const int a0 = v * ((T - 1 + v - 1) / v);
+    nstrips = m3_tiles(g.n[0], w, w - 2 * a0);
+    ngrp = m3_tiles(g.n[1], h, h - 2 * (T - 1));
+}
+
+// The lane offsets of a plane are 32-bit byte offsets from the start of a
+// z layer of blocks.
+static bool m3_wide(const Geom &g, size_t es) {
+    const double blk = (double)(g.bstride > g.sstride ? g.bstride : g.sstride);
+    const double span = ((double)g.nb[0] * g.nb[1] - 1.0) * blk +
+                        (double)(g.plane > (int64_t)g.e[0] * g.e[1] ? g.plane : (int64_t)g.e[0] * g.e[1]);
+    return (span + g.ax + 64.0) * (double)es >= (double)kBufferBytes;
+}
+
+template <typename R>
+bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Plan *out) {
+    if (depth < 1 || depth > march3d_max_depth()) return false;
+    const int nz = g.n[2];
+    M3Plan best;
+    double best_cost = 1e300;
+    const bool wide = m3_wide(g, sizeof(R));
+    for (int ry = 1; ry <= (wide ? 1 : kM3Ry); ++ry) {
+        M3Plan p;
+        p.ry = ry;
+        p.wide = wide;
+        m3_shape<R>(g, depth, ry, p.nstrips, p.ngrp);
+        const int64_t tiles = (int64_t)p.nstrips * p.ngrp;
+        // relative time of one plane step of a tile of this height
+        const double step = ry == 2 ? 1.8 : 1.0;
+        const int smin = zseg > 0 ? (nz + zseg - 1) / zseg : 1;
+        const int smax = zseg > 0 ? smin : (nz + 3) / 4;
+        for (int s = smin; s <= smax; ++s) {
+            p.zseg = zseg > 0 ? zseg : (nz + s - 1) / s;
+            const int64_t segs = (nz + p.zseg - 1) / p.zseg;
+            p.items = tiles * segs;
+            p.partials = kM3Waves * p.items;
+            if ((size_t)p.partials > cap || p.partials > 0x7fffffff - 3) break;
+            const double rounds = (double)((p.items + cus - 1) / cus);
+            const double cost = rounds * step * (p.zseg + 2 * (depth - 1) + 3);
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = p;
+            }
+            if (rounds > 16) break;
+        }
+    }
+    *out = best;
+    return best_cost < 1e300;
+}
+
+#define JAC_M3_SWITCH(depth, F, R, ...)                   \
+    switch (depth) {                                      \
+    case 1: return F<R, 1>(__VA_ARGS__);                  \
+    case 2: return F<R, 2>(__VA_ARGS__);                  \
+    case 3: return F<R, 3>(__VA_ARGS__);                  \
+    case 4: return F<R, 4>(__VA_ARGS__);                  \
+    case 5: return F<R, 5>(__VA_ARGS__);                  \
+    default: return hipErrorInvalidValue;                 \
+    }
 
 template <typename R>
 int64_t march3d_batch_items(const Geom &g, int zseg, int depth) {
-    const int64_t w = march3d_work_items<R>(g, zseg, depth);
-    return w < 0 ? w : w / kM3Waves;
+    if (depth < 1 || depth > march3d_max_depth()) return -1;
+    int ns, ng;
+    m3_shape<R>(g, depth, kM3Ry, ns, ng);
+    return (int64_t)ns * ng * ((g.n[2] + zseg - 1) / zseg);
 }
 
 template <typename R>
 hipError_t launch_march3d_batch(const BatchGrid *grids, const int *prefix, int ngrids, bool src,
                                 int depth, int zseg, int nitems, hipStream_t st) {
-    switch (depth) {
-    case 1: return m3b_launch<R, 1>(grids, prefix, ngrids, src, zseg, nitems, st);
-    case 2: return m3b_launch<R, 2>(grids, prefix, ngrids, src, zseg, nitems, st);
-    case 3: return m3b_launch<R, 3>(grids, prefix, ngrids, src, zseg, nitems, st);
-    case 4: return m3b_launch<R, 4>(grids, prefix, ngrids, src, zseg, nitems, st);
-    case 5: return m3b_launch<R, 5>(grids, prefix, ngrids, src, zseg, nitems, st);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-// Residual partials of one pass (one per wave, 4 per work item).
-template <typename R>
-int64_t march3d_work_items(const Geom &g, int zseg, int depth) {
-    switch (depth) {
-    case 1: return m3_work_items<R, 1>(g, zseg);
-    case 2: return m3_work_items<R, 2>(g, zseg);
-    case 3: return m3_work_items<R, 3>(g, zseg);
-    case 4: return m3_work_items<R, 4>(g, zseg);
-    case 5: return m3_work_items<R, 5>(g, zseg);
-    default: return -1;
-    }
+    JAC_M3_SWITCH(depth, m3b_launch_t, R, grids, prefix, ngrids, src, zseg, nitems, st)
 }
 
 template <typename R>
 hipError_t launch_march3d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
-                          int zseg, hipStream_t st, int64_t *nwork_out, int nt, int depth) {
-    switch (depth) {
-    case 1: return m3_launch<R, 1>(g, uin, uout, b, res, zseg, st, nwork_out, nt);
-    case 2: return m3_launch<R, 2>(g, uin, uout, b, res, zseg, st, nwork_out, nt);
-    case 3: return m3_launch<R, 3>(g, uin, uout, b, res, zseg, st, nwork_out, nt);
-    case 4: return m3_launch<R, 4>(g, uin, uout, b, res, zseg, st, nwork_out, nt);
-    case 5: return m3_launch<R, 5>(g, uin, uout, b, res, zseg, st, nwork_out, nt);
-    default: return hipErrorInvalidValue;
-    }
+                          const M3Plan &pl, hipStream_t st, int depth) {
+    JAC_M3_SWITCH(depth, m3_launch_t, R, g, uin, uout, b, res, pl, st)
 }
 
-template int64_t march3d_batch_items<float>(const Geom &, int, int);
-template int64_t march3d_batch_items<double>(const Geom &, int, int);
-template hipError_t launch_march3d_batch<float>(const BatchGrid *, const int *, int, bool, int, int,
-                                                int, hipStream_t);
-template hipError_t launch_march3d_batch<double>(const BatchGrid *, const int *, int, bool, int,
-                                                 int, int, hipStream_t);
-template int64_t march3d_work_items<float>(const Geom &, int, int);
-template int64_t march3d_work_items<double>(const Geom &, int, int);
-template hipError_t launch_march3d<float>(const Geom &, const void *, void *, const void *,
-                                          double *, int, hipStream_t, int64_t *, int, int);
-template hipError_t launch_march3d<double>(const Geom &, const void *, void *, const void *,
-                                           double *, int, hipStream_t, int64_t *, int, int);
+#define JAC_M3_DISPATCH(R)                                                                       \
+    template bool march3d_plan<R>(const Geom &, int, int, int, size_t, M3Plan *);                \
+    template int64_t march3d_batch_items<R>(const Geom &, int, int);                             \
+    template hipError_t launch_march3d_batch<R>(const BatchGrid *, const int *, int, bool, int,  \
+                                                int, int, hipStream_t);                          \
+    template hipError_t launch_march3d<R>(const Geom &, const void *, void *, const void *,      \
+                                          double *, const M3Plan &, hipStream_t, int);
+JAC_M3_DISPATCH(float)
+JAC_M3_DISPATCH(double)
+
+#endif  // JAC_MARCH3D_DEPTH
 
 }  // namespace jac

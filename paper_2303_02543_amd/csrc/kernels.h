@@ -86,16 +86,26 @@ hipError_t launch_march2d_batch(const BatchGrid *grids, const int *prefix, int n
 template <typename R>
 int64_t march2d_batch_work(const Geom &g, int depth, int rows);
 
+// Schedule of one 3D pass: rows per lane (tile height 32 ry), tiles, output
+// planes per work item, work items, residual partials (8 per work item), and
+// whether the lanes need 64-bit offsets.
+struct M3Plan {
+    int ry, nstrips, ngrp, zseg;
+    int64_t items, partials;
+    bool wide;
+};
+// Plan of a pass of `depth` sweeps; zseg: output planes per work item (0:
+// chosen here, for `cus` compute units); cap: most residual partials.  false:
+// no such pass.
+template <typename R>
+bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Plan *out);
+int march3d_max_depth();
 // `depth` 3D sweeps in one pass over the whole grid (k_march3d.hip), reading
-// face neighbours' cells from their owning blocks; zseg output planes per
-// work item.  uout may be NULL (residual only); res: one partial per wave
-// (8 per work item) or NULL.  depth in 1 .. march3d_max_depth().
+// face neighbours' cells from their owning blocks.  uout may be NULL (residual
+// only); res: pl.partials doubles or NULL.
 template <typename R>
 hipError_t launch_march3d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
-                          int zseg, hipStream_t st, int64_t *nwork, int nt = 0, int depth = 1);
-template <typename R>
-int64_t march3d_work_items(const Geom &g, int zseg, int depth = 1);
-int march3d_max_depth();
+                          const M3Plan &pl, hipStream_t st, int depth);
 
 // Batched 3D pass (k_march3d.hip): the work items of every grid of a
 // descriptor table in one launch, each grid read from u[0] and written to
