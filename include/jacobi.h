@@ -248,7 +248,9 @@ int jacobi_solve_noalloc(int ndim, const int64_t *grid, const int64_t *blocks, i
  * Choose the sweep schedule.  t_depth: sweeps per pass (temporal blocking,
  * 1..jacobi_max_depth(); 0 = library default; a depth without a compiled
  * kernel is run as passes of the nearest smaller compiled depths).
- * rows (0 = default): rows per interior tile of the 2D pass (>= 8; tiles
+ * rows (0 = default: the library's tile height, or, where it expects them to
+ * be faster, 2D passes on tiles held in registers, which do up to 16 sweeps
+ * at once when t_depth is 0 too): rows per interior tile of the 2D pass (>= 8; tiles
  * that reach the grid's boundary ring get fewer rows, derived from this
  * height, because they run a slower edge step), z planes per work item of
  * the 3D pass (>= 8), or, with JACOBI_FLAG_EXPLICIT_HALO on a 2D grid, rows
@@ -363,8 +365,9 @@ int jacobi_batch_solve(jacobi_batch_t b, double rel_tol, int64_t max_sweeps, int
 int jacobi_forward_ckpt(jacobi_t h, int64_t K, int64_t C, void *ckpt);
 
 /* Gradients of a loss L(u_K) after K sweeps with respect to the source and
- * the whole initial state, in one call; the adjoint sweeps run in segments of
- * C >= 1 (any C gives the same bits).
+ * the whole initial state, in one call; C >= 1 is the checkpoint interval of the
+ * forward run; the adjoint sweeps read no checkpoint, so any C gives the same
+ * bits and the same run.
  *   dL_duK  device full state of the handle dtype: dL/du_K at every node,
  *           ring included (the sweeps copy the ring, so the ring of u_K is
  *           g and its gradient passes to g unchanged)

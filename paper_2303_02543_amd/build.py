@@ -19,15 +19,18 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 ARCH = "gfx950"
 
 SOURCES = ["jacobi_abi.hip", "k_layout.hip", "k_sweep.hip", "k_march2d.hip", "k_march3d.hip",
-           "k_residual.hip", "k_batch.hip", "k_deep.hip"]
+           "k_tile2d.hip", "k_residual.hip", "k_batch.hip", "k_deep.hip"]
 # k_march2d.hip and k_march3d.hip are compiled once per temporal depth (their
-# kernels) and once more for the depth dispatch; each entry: (source, object name, defines)
+# kernels) and once more for the depth dispatch, k_tile2d.hip likewise per type;
+# each entry: (source, object name, defines)
 MARCH2D_DEPTHS = list(range(1, 9)) + [10, 11, 12, 13, 14, 16]
 UNITS = ([(s, os.path.splitext(s)[0], []) for s in SOURCES] +
          [("k_march2d.hip", "k_march2d_d%d" % d, ["-DJAC_MARCH2D_DEPTH=%d" % d])
           for d in MARCH2D_DEPTHS] +
          [("k_march3d.hip", "k_march3d_d%d" % d, ["-DJAC_MARCH3D_DEPTH=%d" % d])
-          for d in range(1, 6)])
+          for d in range(1, 6)] +
+         [("k_tile2d.hip", "k_tile2d_%s" % t, ["-DJAC_TILE2D_TYPE=%s" % t])
+          for t in ("float", "double")])
 HEADERS = ["jacobi_internal.h", "kernels.h", "device_util.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -337,6 +337,11 @@ struct jacobi_s {
     int *d_active = nullptr;
     int *d_pc = nullptr;
     int tab_rows = 0;  // tile height / z segment the prefix tables hold (0: none)
+    // schedule facts of this handle's device and grid, filled on first use:
+    // compute units, and the marching pass's one-round tile height by mode
+    // (Laplace, Poisson, adjoint) and depth
+    mutable int cus = 0;
+    mutable int round_rows[3][17] = {};
     std::vector<int> h_prefix;
 };
 
@@ -347,13 +352,15 @@ int check_handle(jacobi_t h) {
     return JACOBI_OK;
 }
 
-// Compute units of the current device (0: unknown).
-int cu_count() {
+// Compute units of the handle's device (256 if they cannot be queried).
+int cu_count(const jacobi_s *h) {
+    if (h->cus > 0) return h->cus;
     int cus = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    return cus;
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        return 256;
+    return h->cus = cus;
 }
 
 // Tile height that makes one march launch fill the GPU in `rounds` whole
@@ -361,8 +368,7 @@ int cu_count() {
 // outer strips included) number at most rounds x (waves per CU x CUs).
 int balanced_rows(const jacobi_s *h, int depth, int mode, int rounds) {
     if (h->g.ndim != 2) return 64;
-    const int cus = cu_count();
-    if (cus <= 0) return 64;
+    const int cus = cu_count(h);
     const int wpc = h->dtype == JACOBI_F32 ? jac::march2d_waves_per_cu<float>(depth, mode)
                                            : jac::march2d_waves_per_cu<double>(depth, mode);
     if (wpc <= 0) return 64;
@@ -406,9 +412,16 @@ bool march_fits(const Geom &g, int dtype) {
 }
 
 
+// balanced_rows of one round, remembered by the handle.
+int round_rows(const jacobi_s *h, int depth, int mode) {
+    int &r = h->round_rows[mode][depth];
+    if (r == 0) r = balanced_rows(h, depth, mode, 1);
+    return r;
+}
+
 int default_rows(const jacobi_s *h) {
     const int d = h->depth > 0 ? h->depth : default_depth(h);
-    return balanced_rows(h, d, h->has_source ? 1 : 0, 1);
+    return round_rows(h, d, h->has_source ? 1 : 0);
 }
 
 int max_depth(int ndim, int dtype) {
@@ -426,6 +439,61 @@ int pick_depth(int dtype, int want) {
     for (int i = 0; i < n; ++i)
         if (list[i] <= want) best = list[i];
     return best;
+}
+
+// Estimated duration (us) of a marching 2D pass of compiled depth t: 2 t more
+// steps than the tile has rows (8, or what one round of resident waves
+// leaves), each as long as its levels take, or the time its bytes take.  The
+// step times are those of passes timed on MI355X: FP32 13 levels 0.9 - 1.1 us
+// at 130^2 .. 8192^2, FP64 4 levels 0.7, adjoint FP32 7 levels 1.2, FP64 3 levels
+// 0.85.  rows = 0: a lower bound, for tiles of the least height.
+template <typename R>
+double march_us(const jacobi_s *h, int t, int mode, int rows) {
+    const double level = sizeof(R) == 4 ? (mode == 2 ? 0.135 : 0.06) : (mode == 2 ? 0.20 : 0.11);
+    const double steps = (rows > 0 ? rows : kMinRows < h->g.n[1] ? kMinRows : h->g.n[1]) + 2 * t;
+    const double us = 2.0 + steps * (0.25 + level * t);
+    const double mem = (double)h->g.n[0] * h->g.n[1] * jac::pass_bytes<R>(mode) / jac::kPassBytesPerUs;
+    return us > mem ? us : mem;
+}
+
+// The next 2D pass of `left` sweeps that remain: its sweeps, and whether it
+// runs on tiles held in registers (tile, tp) or marches.  A caller's depth or
+// tile height is kept: a given depth fixes the split into passes, a given
+// height the marching kernel.  Otherwise tiles run where they are expected to
+// take less time per sweep than marching passes of depth `depth`.
+struct Pass2d {
+    int t;
+    bool tile;
+    jac::Tile2dPlan tp;
+};
+template <typename R>
+Pass2d plan2d(const jacobi_s *h, int64_t left, int depth, bool fixed_depth, bool fixed_rows,
+              int mode, bool res) {
+    Pass2d p;
+    const int64_t passes = (left + depth - 1) / depth;
+    const int want = (int)((left + passes - 1) / passes);
+    p.t = pick_depth(h->dtype, want);
+    p.tile = false;
+    if (fixed_rows || want == 1) return p;
+    const int cus = cu_count(h);
+    double best = 1e300;
+    const int64_t p0 = fixed_depth ? passes : (left + jac::kTileMaxSweeps - 1) / jac::kTileMaxSweeps;
+    for (int64_t k = p0; k < p0 + (fixed_depth ? 1 : 4); ++k) {
+        const int t = fixed_depth ? want : (int)((left + k - 1) / k);
+        jac::Tile2dPlan tp;
+        if (!jac::tile2d_plan<R>(h->g, t, mode, res, h->lay.part_cap, cus, &tp)) continue;
+        if (tp.us / t < best) {
+            best = tp.us / t;
+            p.tp = tp;
+        }
+    }
+    if (best == 1e300) return p;
+    if (best >= march_us<R>(h, p.t, mode, 0) / p.t &&
+        best >= march_us<R>(h, p.t, mode, round_rows(h, p.t, mode)) / p.t)
+        return p;
+    p.tile = true;
+    p.t = p.tp.t;
+    return p;
 }
 
 // Event pair around one sweep-kernel launch when profiling is on.
@@ -460,8 +528,7 @@ int do_halo(jacobi_t h) {
 // plan's own); its residual partials always fit the workspace's.
 template <typename R>
 int plan3d(const jacobi_s *h, int depth, jac::M3Plan *pl) {
-    const int cus = cu_count();
-    if (!jac::march3d_plan<R>(h->g, depth, h->rows, cus > 0 ? cus : 256, h->lay.part_cap, pl))
+    if (!jac::march3d_plan<R>(h->g, depth, h->rows, cu_count(h), h->lay.part_cap, pl))
         return fail(JACOBI_E_INVAL, "partials overflow");
     return JACOBI_OK;
 }
@@ -482,7 +549,7 @@ int do_residual(jacobi_t h, double *out) {
     }
     if (h->g.ndim == 2 && march_fits(h->g, h->dtype)) {
         // one residual-only pass of the march kernel (no stores)
-        const int rows = balanced_rows(h, 1, h->has_source ? 1 : 0, 1);
+        const int rows = round_rows(h, 1, h->has_source ? 1 : 0);
         const int64_t nw = jac::march2d_work_items<R>(h->g, 1, rows);
         if (nw < 0 || (size_t)nw > h->lay.part_cap) return fail(JACOBI_E_INVAL, "partials overflow");
         int64_t nwork = 0;
@@ -617,15 +684,32 @@ int do_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos = true) {
         return JACOBI_OK;
     }
     const int depth = h->depth > 0 ? h->depth : default_depth(h);
-    const int rows = h->rows > 0 ? h->rows : default_rows(h);
     int64_t left = n;
     bool first = true;
     while (left > 0) {
         // split what is left into the fewest passes of at most `depth`
         // sweeps, as evenly as possible (50 at depth 6: 6,6,6,6,6,5,5,5,5)
-        const int64_t passes = (left + depth - 1) / depth;
-        const int t = pick_depth(h->dtype, (int)((left + passes - 1) / passes));
+        const Pass2d ps = plan2d<R>(h, left, depth, h->depth > 0, h->rows > 0,
+                                    h->has_source ? 1 : 0, first && res_first);
+        const int t = ps.t;
         double *part = nullptr;
+        if (ps.tile) {
+            if (first && res_first) part = h->partials;
+            int rc = prof_begin(h);
+            if (rc) return rc;
+            HIP_TRY(jac::launch_tile2d<R>(h->g, h->u[h->cur], h->u[h->cur ^ 1], b, part, nullptr,
+                                          ps.tp, h->stream),
+                    "sweep launch");
+            rc = prof_end(h, t);
+            if (rc) return rc;
+            if (part)
+                HIP_TRY(jac::launch_residual_final(part, (int)ps.tp.items, res_first, h->stream),
+                        "residual launch");
+            first = false;
+            h->cur ^= 1;
+            left -= t;
+            continue;
+        }
         if (t == 1) {
             // one sweep per pass: the tile kernel, reading block-edge
             // neighbours from their owning blocks
@@ -652,6 +736,7 @@ int do_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos = true) {
             left -= 1;
             continue;
         }
+        const int rows = h->rows > 0 ? h->rows : default_rows(h);
         if (first && res_first) {
             const int64_t nw = jac::march2d_work_items<R>(h->g, t, rows);
             if (nw < 0 || (size_t)nw > h->lay.part_cap)
@@ -822,11 +907,23 @@ int do_adjoint(jacobi_t h, int64_t n) {
     // 820 GLUP/s vs 586 at depth 4; depth 8 runs out of registers for the
     // FP64 accumulator ring)
     int depth = h->adj_depth > 0 ? h->adj_depth : (h->dtype == JACOBI_F32 ? 7 : 3);
-    const int rows = h->adj_rows > 0 ? h->adj_rows : balanced_rows(h, depth, 2, 1);
     int64_t left = n;
     while (left > 0) {
-        const int64_t passes = (left + depth - 1) / depth;
-        const int t = pick_depth(h->dtype, (int)((left + passes - 1) / passes));
+        const Pass2d ps = plan2d<R>(h, left, depth, h->adj_depth > 0, h->adj_rows > 0, 2, false);
+        const int t = ps.t;
+        if (ps.tile) {
+            int rc = prof_begin(h);
+            if (rc) return rc;
+            HIP_TRY(jac::launch_tile2d<R>(h->g, h->u[h->cur], h->u[h->cur ^ 1], nullptr, nullptr,
+                                          h->gacc, ps.tp, h->stream),
+                    "adjoint launch");
+            rc = prof_end(h, t);
+            if (rc) return rc;
+            h->cur ^= 1;
+            left -= t;
+            continue;
+        }
+        const int rows = h->adj_rows > 0 ? h->adj_rows : round_rows(h, depth, 2);
         int rc = prof_begin(h);
         if (rc) return rc;
         HIP_TRY(jac::launch_sweep2d_march<R>(h->g, h->u[h->cur], h->u[h->cur ^ 1], nullptr, nullptr,
@@ -1230,6 +1327,7 @@ int jacobi_forward_ckpt(jacobi_t h, int64_t K, int64_t C, void *ckpt) {
     const size_t state_bytes =
         (size_t)(h->g.n[0] + 2) * (h->g.n[1] + 2) * (h->g.ndim == 3 ? h->g.n[2] + 2 : 1) * es;
     int64_t k = 0, j = 0;
+    if (!ckpt) C = K > 0 ? K : 1;  // nothing to store in between: one run
     while (k < K) {
         const int64_t step = K - k < C ? K - k : C;
         if (ckpt) {
@@ -1264,7 +1362,8 @@ int jacobi_adjoint(jacobi_t h, int64_t K, int64_t C, const void *dL_duK, double 
     if ((void *)dL_df == (void *)dL_dU0) return fail(JACOBI_E_INVAL, "dL_df and dL_dU0 must differ");
     rc = jacobi_adjoint_begin(h, dL_duK, dL_df);
     if (rc) return rc;
-    for (int64_t k = 0; k < K && !rc; k += C) rc = jacobi_adjoint_sweep(h, K - k < C ? K - k : C);
+    // the adjoint reads no checkpoint, so the segments of C are one run
+    rc = jacobi_adjoint_sweep(h, K);
     if (rc) {
         h->gacc = nullptr;
         return rc;
@@ -1434,6 +1533,9 @@ int jacobi_autotune(jacobi_t h, int64_t n_sweeps, int with_source, int *t_depth,
             const int nd = jac::march2d_depths(h->dtype, &list);
             static const int kRows[] = {16, 32, 64, 96, 128, 192, 256};
             for (int i = 0; i < nd; ++i) {
+                // rows 0: tiles held in registers where the library expects
+                // them to be faster
+                cands.push_back({list[i], 0, 0});
                 std::vector<int> rs(kRows, kRows + sizeof(kRows) / sizeof(int));
                 for (int k = 1; k <= 3; ++k) rs.push_back(balanced_rows(h, list[i], src, k));
                 std::vector<int> seen;

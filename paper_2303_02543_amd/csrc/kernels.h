@@ -74,6 +74,32 @@ int march2d_waves_per_cu(int depth, int mode);
 // Depths compiled for the 2D march kernel, ascending; returns the count.
 int march2d_depths(int dtype, const int **list);
 
+// Bytes per interior cell that a 2D pass cannot do without (mode 0 Laplace, 1
+// Poisson, 2 adjoint with its FP64 accumulator), and the rate, in bytes per
+// us, that the pass kernels reach on data that does not stay in the caches.
+template <typename R>
+double pass_bytes(int mode) {
+    return sizeof(R) * (mode == 1 ? 3.0 : 2.0) + (mode == 2 ? 16.0 : 0.0);
+}
+constexpr double kPassBytesPerUs = 4.5e6;
+
+// 2D pass of t sweeps with the grid's tiles held in registers (k_tile2d.hip).
+struct Tile2dPlan {
+    int t, shape, nstrips, ngrp;
+    int64_t items;  // work items = residual partials
+    double us;      // estimated duration
+};
+// Best tile shape for a pass of t sweeps in `mode` (0 Laplace, 1 Poisson, 2
+// adjoint) on `cus` compute units; res: residual partials wanted, at most cap.
+// false: no shape.
+constexpr int kTileMaxSweeps = 16;  // most sweeps worth holding a tile's halo for
+template <typename R>
+bool tile2d_plan(const Geom &g, int t, int mode, bool res, size_t cap, int cus, Tile2dPlan *out);
+// Arguments as launch_sweep2d_march.
+template <typename R>
+hipError_t launch_tile2d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
+                         double *gacc, const Tile2dPlan &pl, hipStream_t st);
+
 // Batched pass over the grids of a batch (Poisson kernels; see
 // k_march2d_batch).  nwork = prefix[ngrids]; res: one partial per work item
 // (NULL: no residual); store = false: residual only.

@@ -57,3 +57,58 @@ def test_3d_tile_edges(device, dtype, case):
             check(U0, src, h2, 11, 5, (bx, by, bz), dtype, device,
                   "3d tiles %s %s depth %d rows %d" % (case, np.dtype(dtype).name, depth, rows),
                   depth=depth, rows=rows)
+
+
+# 2D tiles held in registers: 64 x 32, 64 x 64, 128 x 64, 128 x 128 and (FP32)
+# 256 x 128 cells, picked by grid size; a pass of t sweeps loses t rows and t
+# columns (rounded up to a lane's columns) on the sides without a ring.
+TILES_2D = [
+    # (nx, ny, bx, by, sweeps per pass)
+    (64, 32, 2, 2, 8),      # one tile, exactly
+    (65, 33, 2, 3, 8),
+    (112, 48, 3, 2, 8),     # two strips and two groups, exactly
+    (113, 47, 2, 2, 8),
+    (63, 31, 1, 1, 13),
+    (1, 1, 1, 1, 5),
+    (3, 200, 1, 5, 12),
+    (300, 3, 4, 1, 16),
+    (517, 300, 5, 4, 16),
+    (1000, 777, 4, 3, 13),
+    (1502, 1499, 6, 5, 13),
+    (2049, 2030, 8, 8, 16),
+]
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", TILES_2D)
+def test_2d_register_tiles(device, dtype, case):
+    nx, ny, bx, by, t = case
+    U0 = RNG.uniform(0, 1, (ny + 2, nx + 2))
+    f = RNG.standard_normal((ny, nx)) * 100
+    h2 = synthetic.spacing2(max(nx, ny))
+    for src in (f, None):
+        for K, R in ((2 * t + 1, t), (3, 2)):
+            check(U0, src, h2, K, R, (bx, by), dtype, device,
+                  "2d tiles %s %s source %s" % (case, np.dtype(dtype).name, src is not None))
+
+
+@pytest.mark.parametrize("case", [(64, 32, 2, 2, 26), (113, 47, 2, 2, 9), (700, 301, 3, 2, 16),
+                                  (1030, 1101, 4, 5, 31), (2, 3, 1, 1, 33)])
+def test_adjoint_register_tiles(device, case):
+    """FP64 adjoint bit-exact with the oracle's (the accumulator adds the
+    levels in the same order), whatever the passes."""
+    import torch
+    import paper_2303_02543_amd as jb
+    nx, ny, bx, by, K = case
+    h2 = synthetic.spacing2(max(nx, ny))
+    full = RNG.standard_normal((ny + 2, nx + 2))
+    Gb, dU0 = oracle.adjoint2d_full(full, K)
+    s = jb.Solver((nx, ny), (bx, by), torch.float64, device=device)
+    try:
+        for chunk in (None, 7):
+            say("adjoint tiles", case, chunk)
+            gf, gU0 = s.adjoint(torch.from_numpy(full).to(device), K, h2, chunk=chunk)
+            assert bits_equal(gf.cpu().numpy(), h2 * Gb)
+            assert bits_equal(gU0.cpu().numpy(), dU0)
+    finally:
+        s.close()
