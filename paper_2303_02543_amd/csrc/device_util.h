@@ -58,7 +58,7 @@ __device__ __forceinline__ X buffer_get(const void *base, uint32_t off) {
 // and every wait for a load then also waits for the stores before it.
 constexpr uint32_t kBufferBytes = 0xfffff000u;  // offsets stay below this
 constexpr uint32_t kNoStore = 0xfffffff0u;
-template <typename X>
+template <bool NT = false, typename X>
 __device__ __forceinline__ void buffer_put16(void *base, uint32_t off, bool on, const X &v) {
     static_assert(sizeof(X) == 16, "16-byte stores only");
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -66,7 +66,7 @@ __device__ __forceinline__ void buffer_put16(void *base, uint32_t off, bool on, 
     __builtin_memcpy(&t, &v, 16);
     const __amdgpu_buffer_rsrc_t r =
         __builtin_amdgcn_make_buffer_rsrc(base, 0, on ? kBufferBytes : 0u, 0x00020000);
-    __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, NT ? 2 : 0);
 }
 
 // 16-byte store with the non-temporal hint (the line is not kept in the

@@ -52,7 +52,7 @@ constexpr int kM2Waves = 4;
 // into an FP64 accumulator.
 enum { MODE_LAPLACE = 0, MODE_POISSON = 1, MODE_ADJOINT = 2 };
 
-template <typename R, int T, int P>
+template <typename R, int T, int P, int MODE = MODE_LAPLACE>
 struct M2 {
     static constexpr int V = 16 / (int)sizeof(R);            // elements per lane
     static constexpr int W = 64 * V;                          // strip width
@@ -62,15 +62,23 @@ struct M2 {
     static constexpr int L1 = (A0 + OW) / V;                  // one past the last output lane
     // rows loaded ahead (prefetch distance): row r + P is loaded at step r
     static_assert(P >= 1 && P <= 3, "prefetch distance 1..3");
-    static constexpr int LR = P == 1 ? 4 : 6;                 // level-0 ring: rows r-2 .. r+P
-    static constexpr int BQ = P == 1 ? 2 : P;                 // source registers: rows r .. r+P
+    // With a source, depths 12 and 13 unroll 15 steps, and the source ring
+    // holds 15 rows (12 at depths 10 and 11, whose groups are 12 steps): every
+    // LDS slot is then a compile-time offset from the lane's base, not an
+    // address computed for every level (depth 13: 264 VALU instructions per
+    // step instead of 286, for 260 plain operations).
+    static constexpr bool BIG = MODE == MODE_POISSON && P == 2 && T >= 12;
+    static constexpr int LR = BIG ? 5 : P == 1 ? 4 : 6;       // level-0 ring: rows r-2 .. r+P
+    static constexpr int BQ = BIG ? 3 : P == 1 ? 2 : P;       // source registers: rows r .. r+P
     // BQ == P: the slot of row r is reused for row r + P, so row r goes to
     // LDS before that load is issued; otherwise after it
     static constexpr bool WRITE_FIRST = BQ == P;
-    static constexpr int U = 12;                              // steps per unrolled group
-    // ring slots are compile-time step indices mod 4, 3 and 2
+    static constexpr int U = BIG ? 15 : 12;                   // steps per unrolled group
+    // ring slots are compile-time step indices mod LR, 3 and BQ
     static_assert(U % LR == 0 && U % 3 == 0 && U % BQ == 0, "ring sizes must divide U");
-    static constexpr int RB = T + 1;                          // source rows r-T .. r (LDS)
+    static constexpr int RB = BIG ? 15 : T == 10 || T == 11 ? 12 : T + 1;  // source rows r-T .. r (LDS)
+    static constexpr bool FIXED = U % RB == 0;                // LDS slot = step mod RB
+    static_assert(RB > T, "source ring too small");
     static constexpr int NL = T > 1 ? T - 1 : 1;              // stored levels 1..T-1
     // adjoint accumulator rows r-T+1 .. r+1
     static constexpr int RA = T + 1 <= 2 ? 2 : T + 1 <= 3 ? 3 : T + 1 <= 4 ? 4 : T + 1 <= 6 ? 6 : 12;
@@ -175,9 +183,9 @@ struct Cur {
     }
 };
 
-template <typename R, int T, int P>
+template <typename R, int T, int P, int MODE>
 struct MRegs {
-    using S = M2<R, T, P>;
+    using S = M2<R, T, P, MODE>;
     R l0[S::LR][S::V];       // level-0 rows, slot = row mod LR (r-2 .. r+P)
     R e0[S::LR];             // level-0 cell just outside the strip (lanes 0, 63)
     R bq[S::BQ][S::V];       // source rows in flight, slot = row mod BQ
@@ -192,7 +200,7 @@ struct MLane {
     bool upd[8];                     // per element: interior column (column-edge tiles)
     bool st[8];                      // per element: interior output column (column-edge tiles)
     bool out_lane;                   // lane holds output columns
-    bool st_all;                     // every column of the lane is an interior output
+    uint32_t st_b;                   // whole-chunk store offset (kNoStore: not all columns are outputs)
     bool st_part;                    // some but not all are (the east ring's lane)
     bool nt;                         // non-temporal output stores
     int c;                           // global column of the lane's first element
@@ -206,8 +214,8 @@ template <typename R, int T, int P, int MODE, int EK, int SL, int SQ, int SA>
 __device__ __forceinline__ void m2_load(const Geom &g, const R *__restrict__ uin,
                                         const R *__restrict__ bsrc,
                                         const double *__restrict__ gacc, const MLane &L,
-                                        MRegs<R, T, P> &m, Cur &lc) {
-    constexpr int V = M2<R, T, P>::V;
+                                        MRegs<R, T, P, MODE> &m, Cur &lc) {
+    constexpr int V = M2<R, T, P, MODE>::V;
     constexpr bool SRC = MODE == MODE_POISSON;
     using C = Chunk<R, V>;
     const int y = lc.y, ny = g.n[1];
@@ -226,13 +234,13 @@ __device__ __forceinline__ void m2_load(const Geom &g, const R *__restrict__ uin
     // keeps at their values
     const bool row_ok = !(EK & 1) || (y >= -1 && y <= ny);
     const R *row = uin + (row_ok ? lc.su : (int64_t)g.pitch);
-    const C c = at<C>(row, L.lane_b);
+    const C c = buffer_get<C>(row, L.lane_b);
 #pragma unroll
     for (int v = 0; v < V; ++v) m.l0[SL][v] = c.v[v];
-    m.e0[SL] = at<R>(row, L.edge_b);
+    m.e0[SL] = buffer_get<R>(row, L.edge_b);
     if constexpr (SRC) {
         const bool brow = !(EK & 1) || (y >= 0 && y < ny);
-        const C cb = at<C>(bsrc + (brow ? lc.sb : (int64_t)0), L.src_b);
+        const C cb = buffer_get<C>(bsrc + (brow ? lc.sb : (int64_t)0), L.src_b);
 #pragma unroll
         for (int v = 0; v < V; ++v) m.bq[SQ][v] = cb.v[v];
     }
@@ -244,9 +252,9 @@ __device__ __forceinline__ void m2_load(const Geom &g, const R *__restrict__ uin
 // level (T - 1) has been added.
 template <typename R, int T, int P, int MODE, int EK, int SA, bool LAST>
 __device__ __forceinline__ void m2_accumulate(const Geom &g, double *__restrict__ gacc,
-                                              const MLane &L, MRegs<R, T, P> &m, const int y,
-                                              const R (&val)[M2<R, T, P>::V]) {
-    constexpr int V = M2<R, T, P>::V;
+                                              const MLane &L, MRegs<R, T, P, MODE> &m, const int y,
+                                              const R (&val)[M2<R, T, P, MODE>::V]) {
+    constexpr int V = M2<R, T, P, MODE>::V;
     if constexpr (MODE == MODE_ADJOINT) {
         if (!(EK & 1) || (y >= 0 && y < g.n[1])) {
             const R w = (R)0.25;
@@ -268,10 +276,10 @@ __device__ __forceinline__ void m2_accumulate(const Geom &g, double *__restrict_
 // the row K steps back (K = S: row r - S, for level S of this step; K = 0:
 // row r, for level 1 of the next step).  Issued one level before its use, so
 // the LDS latency overlaps the arithmetic of the level in between.
-template <typename R, int T, int P, int S, int K = S>
-__device__ __forceinline__ void m2_read_src(const MLane &L, MRegs<R, T, P> &m, const int sr) {
-    using M = M2<R, T, P>;
-    const int slot = sr - K < 0 ? sr - K + M::RB : sr - K;
+template <typename R, int T, int P, int J, int S, int K = S>
+__device__ __forceinline__ void m2_read_src(const MLane &L, MRegs<R, T, P, MODE_POISSON> &m, const int sr) {
+    using M = M2<R, T, P, MODE_POISSON>;
+    const int slot = M::FIXED ? (J % M::RB - K + M::RB) % M::RB : sr - K < 0 ? sr - K + M::RB : sr - K;
     const Chunk<R, M::V> c = static_cast<const Chunk<R, M::V> *>(L.bs)[slot * 64];
 #pragma unroll
     for (int v = 0; v < M::V; ++v) m.bn[S & 1][v] = c.v[v];
@@ -297,9 +305,9 @@ constexpr bool m2_next_l1() {
 
 template <typename R, int T, int P, int MODE, int EK, bool RES, int J, int S, int G = -1>
 __device__ __forceinline__ void m2_level(const Geom &g, R *__restrict__ uout,
-                                         double *__restrict__ gacc, const MLane &L, MRegs<R, T, P> &m, const int r,
+                                         double *__restrict__ gacc, const MLane &L, MRegs<R, T, P, MODE> &m, const int r,
                                          const Cur &sc, const int sr) {
-    using M = M2<R, T, P>;
+    using M = M2<R, T, P, MODE>;
     constexpr int V = M::V;
     constexpr bool SRC = MODE == MODE_POISSON;
     constexpr int LMAX = m2_lmax<T, M::U, G, J>();
@@ -326,9 +334,9 @@ __device__ __forceinline__ void m2_level(const Geom &g, R *__restrict__ uout,
 #pragma unroll
             for (int v = 0; v < V; ++v) bv[v] = m.bn[S & 1][v];
             if constexpr (S < LMAX)
-                m2_read_src<R, T, P, S + 1>(L, m, sr);
+                m2_read_src<R, T, P, J, S + 1>(L, m, sr);
             else if constexpr (m2_next_l1<T, M::U, G, J>())
-                m2_read_src<R, T, P, 1, 0>(L, m, sr);  // the next step's level 1: this row
+                m2_read_src<R, T, P, J, 1, 0>(L, m, sr);  // the next step's level 1: this row
             // keep the read ahead of this level's arithmetic: left to itself
             // the scheduler sinks it to just before its use, a few
             // instructions on, and every level then waits for LDS
@@ -381,24 +389,24 @@ __device__ __forceinline__ void m2_level(const Geom &g, R *__restrict__ uout,
             m2_accumulate<R, T, P, MODE, EK, (J - S + 2 * M::RA) % M::RA, S == T - 1>(g, gacc, L,
                                                                                      m, y, out);
         } else {
-            if (uout && y >= L.oy0 && y < L.oy1) {
-                R *row = uout + sc.su;
-                Chunk<R, V> o;
+            const bool on = uout && y >= L.oy0 && y < L.oy1;
+            R *row = uout + sc.su;
+            Chunk<R, V> o;
 #pragma unroll
-                for (int v = 0; v < V; ++v) o.v[v] = out[v];
-                if (L.st_all) {
-                    if (L.nt)
-                        store_nt16(&at_mut<Chunk<R, V>>(row, L.lane_b), o);
-                    else
-                        at_mut<Chunk<R, V>>(row, L.lane_b) = o;
-                } else if constexpr ((EK & 2) != 0) {
-                    // the lane holding the east ring column and interior
-                    // columns before it stores element by element
-                    if (L.st_part) {
+            for (int v = 0; v < V; ++v) o.v[v] = out[v];
+            // one store on every path, so that the waits for the rows in
+            // flight need not include it
+            if (L.nt)
+                buffer_put16<true>(row, L.st_b, on, o);
+            else
+                buffer_put16<false>(row, L.st_b, on, o);
+            if constexpr ((EK & 2) != 0) {
+                // the lane holding the east ring column and interior columns
+                // before it stores element by element
+                if (on && L.st_part) {
 #pragma unroll
-                        for (int v = 0; v < V; ++v)
-                            if (L.st[v]) at_mut<R>(row, L.lane_b + v * (uint32_t)sizeof(R)) = out[v];
-                    }
+                    for (int v = 0; v < V; ++v)
+                        if (L.st[v]) at_mut<R>(row, L.lane_b + v * (uint32_t)sizeof(R)) = out[v];
                 }
             }
         }
@@ -409,9 +417,9 @@ __device__ __forceinline__ void m2_level(const Geom &g, R *__restrict__ uout,
 template <typename R, int T, int P, int MODE, int EK, bool RES, int J, int G = -1>
 __device__ __forceinline__ void m2_steps(const Geom &g, const R *__restrict__ uin,
                                          R *__restrict__ uout, const R *__restrict__ bsrc,
-                                         double *__restrict__ gacc, const MLane &L, MRegs<R, T, P> &m, const int base, Cur &lc,
+                                         double *__restrict__ gacc, const MLane &L, MRegs<R, T, P, MODE> &m, const int base, Cur &lc,
                                          Cur &sc, int &sr) {
-    using M = M2<R, T, P>;
+    using M = M2<R, T, P, MODE>;
     constexpr int V = M::V;
     if constexpr (J < M::U) {
         const int r = base + J;
@@ -423,7 +431,7 @@ __device__ __forceinline__ void m2_steps(const Geom &g, const R *__restrict__ ui
                 Chunk<R, V> c;
 #pragma unroll
                 for (int v = 0; v < V; ++v) c.v[v] = m.bq[J % M::BQ][v];
-                static_cast<Chunk<R, V> *>(L.bs)[sr * 64] = c;
+                static_cast<Chunk<R, V> *>(L.bs)[(M::FIXED ? J % M::RB : sr) * 64] = c;
             }
         };
         if constexpr (M::WRITE_FIRST) to_lds();
@@ -445,10 +453,10 @@ __device__ __forceinline__ void m2_steps(const Geom &g, const R *__restrict__ ui
         // a step that computes no level reads the next step's row itself
         if constexpr (MODE == MODE_POISSON && m2_lmax<T, M::U, G, J>() == 0 &&
                       m2_next_l1<T, M::U, G, J>())
-            m2_read_src<R, T, P, 1, 0>(L, m, sr);
+            m2_read_src<R, T, P, J, 1, 0>(L, m, sr);
         m2_level<R, T, P, MODE, EK, RES, J, 1, G>(g, uout, gacc, L, m, r, sc, sr);
         sc.advance(g);
-        sr = sr + 1 == M::RB ? 0 : sr + 1;
+        if constexpr (!M::FIXED) sr = sr + 1 == M::RB ? 0 : sr + 1;
         m2_steps<R, T, P, MODE, EK, RES, J + 1, G>(g, uin, uout, bsrc, gacc, L, m, base, lc, sc,
                                                      sr);
     }
@@ -459,8 +467,8 @@ __device__ __forceinline__ void m2_body(const Geom &g, const R *__restrict__ uin
                                         R *__restrict__ uout, const R *__restrict__ bsrc,
                                         double *__restrict__ res_slot,
                                         double *__restrict__ gacc, const MLane &L, int r0) {
-    using S = M2<R, T, P>;
-    MRegs<R, T, P> m;
+    using S = M2<R, T, P, MODE>;
+    MRegs<R, T, P, MODE> m;
 #pragma unroll
     for (int k = 0; k < S::LR; ++k) {
         m.e0[k] = (R)0;
@@ -503,7 +511,7 @@ __device__ __forceinline__ void m2_body(const Geom &g, const R *__restrict__ uin
     }
     // without the warm-up groups the first step computes level 1 (its row
     // lies before the tile and is not an output)
-    if constexpr (MODE == MODE_POISSON && T == 1) m2_read_src<R, T, P, 1>(L, m, sr);
+    if constexpr (MODE == MODE_POISSON && T == 1) m2_read_src<R, T, P, 0, 1>(L, m, sr);
     for (; base <= L.r1; base += S::U)
         m2_steps<R, T, P, MODE, EK, RES, 0>(g, uin, uout, bsrc, gacc, L, m, base, lc, sc, sr);
     if constexpr (RES) {
@@ -519,9 +527,9 @@ template <typename R, int T, int P, int MODE, bool RES>
 __device__ __forceinline__ void m2_run(const Geom &g, const R *__restrict__ uin,
                                        R *__restrict__ uout, const R *__restrict__ bsrc,
                                        double *__restrict__ res_slot, double *__restrict__ gacc,
-                                       int wid, int rows, Chunk<R, M2<R, T, P>::V> *bs_wave,
+                                       int wid, int rows, Chunk<R, M2<R, T, P, MODE>::V> *bs_wave,
                                        bool nt) {
-    using S = M2<R, T, P>;
+    using S = M2<R, T, P, MODE>;
     constexpr bool SRC = MODE == MODE_POISSON;
     constexpr int V = S::V;
     const int lane = threadIdx.x & 63;
@@ -568,7 +576,7 @@ __device__ __forceinline__ void m2_run(const Geom &g, const R *__restrict__ uin,
             any = any || L.st[v];
         }
     }
-    L.st_all = all;
+    L.st_b = all ? L.lane_b : kNoStore;
     L.st_part = any && !all;
     // rows r0 .. r1 + P are read; an interior tile reads only grid rows and
     // columns, none of them on the ring
@@ -593,13 +601,13 @@ __device__ __forceinline__ void m2_run(const Geom &g, const R *__restrict__ uin,
 // one residual partial per work item; gacc is the FP64 accumulator of the
 // adjoint pass (MODE_ADJOINT only).
 template <typename R, int T, int P, int MODE, bool RES>
-__global__ __launch_bounds__(64 * kM2Waves) void k_march2d(Geom g, const R *__restrict__ uin,
+__global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_march2d(Geom g, const R *__restrict__ uin,
                                                  R *__restrict__ uout,
                                                  const R *__restrict__ bsrc,
                                                  double *__restrict__ res,
                                                  double *__restrict__ gacc, int rows, int nwork,
                                                  int nt) {
-    using S = M2<R, T, P>;
+    using S = M2<R, T, P, MODE>;
     constexpr bool SRC = MODE == MODE_POISSON;
     // per wave: a ring of RB source rows, one 16-byte chunk per lane each
     __shared__ Chunk<R, S::V> bsm[SRC ? kM2Waves * S::RB * 64 : 1];
@@ -617,13 +625,13 @@ __global__ __launch_bounds__(64 * kM2Waves) void k_march2d(Geom g, const R *__re
 // MODE: Poisson (the batched solver; the deep-halo form with a source) or
 // Laplace (the deep-halo form without one).
 template <typename R, int T, int P, bool RES, int MODE>
-__global__ __launch_bounds__(64 * kM2Waves) void k_march2d_batch(const BatchGrid *__restrict__ grids,
+__global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_march2d_batch(const BatchGrid *__restrict__ grids,
                                                        const int *__restrict__ prefix, int ngrids,
                                                        const int *__restrict__ active,
                                                        const int *__restrict__ pass_count,
                                                        double *__restrict__ res, int store,
                                                        int rows, int nwork) {
-    using S = M2<R, T, P>;
+    using S = M2<R, T, P, MODE>;
     constexpr bool SRC = MODE == MODE_POISSON;
     __shared__ Chunk<R, S::V> bsm[SRC ? kM2Waves * S::RB * 64 : 1];
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
