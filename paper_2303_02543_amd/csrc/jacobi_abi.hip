@@ -1121,12 +1121,8 @@ int jacobi_set_state(jacobi_t h, const void *u) {
     if (!u) return fail(JACOBI_E_INVAL, "u must not be NULL");
     if (h->dtype == JACOBI_F32) {
         HIP_TRY(jac::launch_scatter<float>(h->g, u, h->u[0], h->u[1], false, h->stream), "scatter launch");
-        HIP_TRY(jac::launch_halo_exchange<float>(h->g, h->u[0], h->stream), "halo exchange launch");
-        HIP_TRY(jac::launch_halo_exchange<float>(h->g, h->u[1], h->stream), "halo exchange launch");
     } else {
         HIP_TRY(jac::launch_scatter<double>(h->g, u, h->u[0], h->u[1], false, h->stream), "scatter launch");
-        HIP_TRY(jac::launch_halo_exchange<double>(h->g, h->u[0], h->stream), "halo exchange launch");
-        HIP_TRY(jac::launch_halo_exchange<double>(h->g, h->u[1], h->stream), "halo exchange launch");
     }
     if (h->halo > 0) {
         // every block's whole frame, ring nodes beyond its own ring included
@@ -1280,13 +1276,9 @@ int jacobi_adjoint_begin(jacobi_t h, const void *lam, double *grad_b) {
     if (h->dtype == JACOBI_F32) {
         HIP_TRY(jac::launch_scatter<float>(h->g, lam, h->u[0], h->u[1], true, h->stream),
                 "scatter launch");
-        HIP_TRY(jac::launch_halo_exchange<float>(h->g, h->u[0], h->stream), "halo exchange launch");
-        HIP_TRY(jac::launch_halo_exchange<float>(h->g, h->u[1], h->stream), "halo exchange launch");
     } else {
         HIP_TRY(jac::launch_scatter<double>(h->g, lam, h->u[0], h->u[1], true, h->stream),
                 "scatter launch");
-        HIP_TRY(jac::launch_halo_exchange<double>(h->g, h->u[0], h->stream), "halo exchange launch");
-        HIP_TRY(jac::launch_halo_exchange<double>(h->g, h->u[1], h->stream), "halo exchange launch");
     }
     HIP_TRY(jac::launch_fill_f64(grad_b, 0.0, (int64_t)h->g.n[0] * h->g.n[1], h->stream),
             "fill launch");
@@ -1988,13 +1980,9 @@ int jacobi_batch_set_grid(jacobi_batch_t b, int i, const void *u, const void *f,
     const jac::BatchGrid &g = b->h_grids[i];
     if (b->dtype == JACOBI_F32) {
         HIP_TRY(jac::launch_scatter<float>(g.g, u, g.u[0], g.u[1], false, b->stream), "scatter launch");
-        HIP_TRY(jac::launch_halo_exchange<float>(g.g, g.u[0], b->stream), "halo launch");
-        HIP_TRY(jac::launch_halo_exchange<float>(g.g, g.u[1], b->stream), "halo launch");
         HIP_TRY(jac::launch_scale_source<float>(g.g, f, (void *)g.b, h2, b->stream), "source launch");
     } else {
         HIP_TRY(jac::launch_scatter<double>(g.g, u, g.u[0], g.u[1], false, b->stream), "scatter launch");
-        HIP_TRY(jac::launch_halo_exchange<double>(g.g, g.u[0], b->stream), "halo launch");
-        HIP_TRY(jac::launch_halo_exchange<double>(g.g, g.u[1], b->stream), "halo launch");
         HIP_TRY(jac::launch_scale_source<double>(g.g, f, (void *)g.b, h2, b->stream), "source launch");
     }
     b->h_final_buf[i] = 0;

@@ -9,76 +9,152 @@
 // per halo cell: read the neighbour's edge cell, write the halo slot.
 #include <hip/hip_runtime.h>
 
+#include "device_util.h"
 #include "jacobi_internal.h"
 #include "kernels.h"
 
 namespace jac {
 
-// The element maps below run over rows of the full array (or of the source
-// for k_scale_source): one workgroup per row (rows strided over the grid),
-// its threads walking the row block by block, so no element needs a
-// division to find its owner and every access is coalesced.  (A flat
-// grid-stride form, which split a 64-bit element index per element, ran at
-// ~2 TB/s; one element per thread with one workgroup per 256 columns was
-// slower still, bound by workgroup dispatch.)
-
-// Element offset of row y / plane z (ring-extended) in block (0, by, bz) at
-// local x = 0, and whether the row is on the Dirichlet ring (uniform).
-struct RowYZ {
-    int64_t base;
-    bool ring;
+// The element maps below run over the rows of the blocks: a workgroup takes
+// rows of one block plane (2D: of the block), `lanes` lanes per row, each lane
+// V = 16 bytes of it, so that narrow blocks (64 columns of a 3D domain) fill
+// the lanes as well as wide ones, and the block's side is read and written in
+// aligned 16-byte pieces (the full array's rows have any alignment, which
+// global 16-byte accesses take at 4 bytes).  Blocks, planes and rows come from
+// the grid's coordinates, so no element needs a division.  Bound by memory;
+// 512^3 FP32 in 64^3 blocks, before (one workgroup per row of the full array,
+// a quarter of its lanes busy in each block) and now: scatter 664 us plus 464
+// for the two halo exchanges it now includes -> 604; gather 548 -> 286; source
+// 444 -> 203.  8192^2 FP32 in 512^2 blocks: 167 + 42 -> 154, 125 -> 88, 124 -> 100.
+struct RowMap {
+    int lanes, rows;  // lanes per row (a power of two), rows per workgroup and step
+    dim3 grid;        // x: row groups, y: planes, z: blocks (both strided beyond the limits)
 };
-__device__ __forceinline__ RowYZ row_yz(const Geom &g, int y, int z) {
-    int by, ly, bz = 0, lz = 0;
-    owner(y, g.e[1], g.nb[1], by, ly);
-    if (g.ndim == 3) owner(z, g.e[2], g.nb[2], bz, lz);
-    RowYZ r;
-    r.base = local_offset(g, ((int64_t)bz * g.nb[1] + by) * g.nb[0], 0, ly, lz);
-    r.ring = y < 0 || y >= g.n[1] || (g.ndim == 3 && (z < 0 || z >= g.n[2]));
-    return r;
+// nrows, nplanes: rows per block plane and planes per block to cover
+template <typename R>
+static RowMap row_map(const Geom &g, int nrows, int nplanes) {
+    constexpr int V = 16 / (int)sizeof(R);
+    RowMap m;
+    m.lanes = 1;
+    while (m.lanes < 256 && m.lanes * V < g.e[0]) m.lanes *= 2;
+    m.rows = 256 / m.lanes;
+    // four steps per workgroup where that still leaves workgroups enough
+    // (a 256^2 gather in one step each: 3.5 us, in four 5.7)
+    int groups = (nrows + m.rows - 1) / m.rows;
+    if ((double)groups * nplanes * (double)g.nblocks >= 8192.0) groups = (groups + 3) / 4;
+    m.grid = dim3((unsigned)(groups < 1 ? 1 : groups > (1 << 20) ? (1 << 20) : groups), (unsigned)(nplanes < 65535 ? nplanes : 65535),
+                  (unsigned)(g.nblocks < 65535 ? g.nblocks : 65535));
+    return m;
 }
 
-// Every node of the full (n+2)^d array goes to the block that owns it (ring
-// nodes to the domain-edge halo slots), in both state buffers.  Internal
-// halos are filled afterwards by the halo exchange.
+// 16 bytes at the full array's alignment
+template <typename R>
+struct __attribute__((packed, aligned(sizeof(R)))) Loose {
+    R v[16 / sizeof(R)];
+};
+
+// A block's coordinates and extents.
+struct BlockPos {
+    int b[3], ext[3];
+};
+__device__ __forceinline__ BlockPos block_pos(const Geom &g, int64_t blk) {
+    // fewer than 2^31 blocks (each stores at least 1 KiB): 32-bit divisions
+    BlockPos p;
+    const unsigned row = (unsigned)blk / (unsigned)g.nb[0];
+    p.b[0] = (int)((unsigned)blk - row * g.nb[0]);
+    p.b[2] = g.ndim == 3 ? (int)(row / (unsigned)g.nb[1]) : 0;
+    p.b[1] = (int)row - p.b[2] * g.nb[1];
+    for (int a = 0; a < 3; ++a) p.ext[a] = a < g.ndim ? extent(g.n[a], g.e[a], p.b[a]) : 1;
+    return p;
+}
+
+// Every block's interior and one-cell frame from the full (n+2)^d array, in
+// both state buffers: a frame cell holds the neighbour's value, or the
+// Dirichlet ring on the domain's sides, so no halo exchange has to follow.
+// zero_ring: the ring is written as 0.
 template <typename R>
 __global__ __launch_bounds__(256) void k_scatter(Geom g, const R *__restrict__ u,
-                                                 R *__restrict__ s0, R *__restrict__ s1,
-                                                 int64_t rows, int zero_ring) {
-    const int nx2 = g.n[0] + 2, ny2 = g.n[1] + 2;
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const RowYZ yz = row_yz(g, (int)(r % ny2) - 1, (int)(r / ny2) - 1);
-        const R *urow = u + r * nx2 + 1;  // urow[x], x in [-1, n]
-        for (int bx = 0; bx < g.nb[0]; ++bx) {
-            const int ext = extent(g.n[0], g.e[0], bx);
-            const int lo = bx == 0 ? -1 : 0, hi = bx == g.nb[0] - 1 ? ext + 1 : ext;
-            const int x0 = bx * g.e[0];
-            const int64_t boff = yz.base + (int64_t)bx * g.bstride;
-            for (int lx = lo + (int)threadIdx.x; lx < hi; lx += blockDim.x) {
-                const int x = x0 + lx;
-                const bool ring = yz.ring || x < 0 || x >= g.n[0];
-                const R v = (zero_ring && ring) ? (R)0 : urow[x];
-                s0[boff + lx] = v;
-                s1[boff + lx] = v;
+                                                 R *__restrict__ s0, R *__restrict__ s1, int lanes,
+                                                 int zero_ring) {
+    constexpr int V = 16 / (int)sizeof(R);
+    const int64_t nx2 = g.n[0] + 2, ny2 = g.n[1] + 2;
+    const int lane = threadIdx.x & (lanes - 1), r0 = threadIdx.x / lanes, rpw = 256 / lanes;
+    const int lz0 = g.ndim == 3 ? -1 : 0;
+    for (int64_t blk = blockIdx.z; blk < g.nblocks; blk += gridDim.z) {
+        const BlockPos p = block_pos(g, blk);
+        const int ex = p.ext[0], ey = p.ext[1], hz = g.ndim == 3 ? p.ext[2] : 0;
+        const int x0 = p.b[0] * g.e[0], y0 = p.b[1] * g.e[1], z0 = p.b[2] * g.e[2];
+        for (int lz = lz0 + (int)blockIdx.y; lz <= hz; lz += gridDim.y) {
+            const int z = z0 + lz;
+            const bool zr = g.ndim == 3 && (z < 0 || z >= g.n[2]);
+            for (int ly = -1 + (int)blockIdx.x * rpw + r0; ly <= ey; ly += (int)gridDim.x * rpw) {
+                const int y = y0 + ly;
+                const bool ring = zero_ring && (zr || y < 0 || y >= g.n[1]);
+                const R *src = u + ((g.ndim == 3 ? (int64_t)(z + 1) * ny2 : 0) + y + 1) * nx2 + 1 + x0;
+                const int64_t o = local_offset(g, blk, 0, ly, lz);
+                for (int c = lane * V; c < ex; c += lanes * V) {
+                    if (c + V <= ex) {
+                        Loose<R> t = *reinterpret_cast<const Loose<R> *>(src + c);
+                        Chunk<R, V> w;
+#pragma unroll
+                        for (int v = 0; v < V; ++v) w.v[v] = ring ? (R)0 : t.v[v];
+                        *reinterpret_cast<Chunk<R, V> *>(s0 + o + c) = w;
+                        *reinterpret_cast<Chunk<R, V> *>(s1 + o + c) = w;
+                    } else {
+                        for (int v = 0; c + v < ex; ++v)
+                            s0[o + c + v] = s1[o + c + v] = ring ? (R)0 : src[c + v];
+                    }
+                }
+                // the cells west and east of the row
+                if (lane < 2 || lanes < 2) {
+                    for (int side = lane; side < 2; side += lanes) {
+                        const int lx = side == 0 ? -1 : ex, x = x0 + lx;
+                        const bool zero = ring || (zero_ring && (x < 0 || x >= g.n[0]));
+                        s0[o + lx] = s1[o + lx] = zero ? (R)0 : src[lx];
+                    }
+                }
             }
         }
     }
 }
 
+// Every block's interior, and the ring nodes its frame holds on the domain's
+// sides, to the full array.
 template <typename R>
 __global__ __launch_bounds__(256) void k_gather(Geom g, const R *__restrict__ s,
-                                                R *__restrict__ u, int64_t rows) {
-    const int nx2 = g.n[0] + 2, ny2 = g.n[1] + 2;
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const RowYZ yz = row_yz(g, (int)(r % ny2) - 1, (int)(r / ny2) - 1);
-        R *urow = u + r * nx2 + 1;
-        for (int bx = 0; bx < g.nb[0]; ++bx) {
-            const int ext = extent(g.n[0], g.e[0], bx);
-            const int lo = bx == 0 ? -1 : 0, hi = bx == g.nb[0] - 1 ? ext + 1 : ext;
-            const int x0 = bx * g.e[0];
-            const int64_t boff = yz.base + (int64_t)bx * g.bstride;
-            for (int lx = lo + (int)threadIdx.x; lx < hi; lx += blockDim.x)
-                urow[x0 + lx] = s[boff + lx];
+                                                R *__restrict__ u, int lanes) {
+    constexpr int V = 16 / (int)sizeof(R);
+    const int64_t nx2 = g.n[0] + 2, ny2 = g.n[1] + 2;
+    const int lane = threadIdx.x & (lanes - 1), r0 = threadIdx.x / lanes, rpw = 256 / lanes;
+    for (int64_t blk = blockIdx.z; blk < g.nblocks; blk += gridDim.z) {
+        const BlockPos p = block_pos(g, blk);
+        const int ex = p.ext[0];
+        const int x0 = p.b[0] * g.e[0], y0 = p.b[1] * g.e[1], z0 = p.b[2] * g.e[2];
+        // rows and planes of the frame on the domain's sides
+        const int ylo = p.b[1] == 0 ? -1 : 0, yhi = p.ext[1] - (p.b[1] == g.nb[1] - 1 ? 0 : 1);
+        int zlo = 0, zhi = 0;
+        if (g.ndim == 3) {
+            zlo = p.b[2] == 0 ? -1 : 0;
+            zhi = p.ext[2] - (p.b[2] == g.nb[2] - 1 ? 0 : 1);
+        }
+        for (int lz = zlo + (int)blockIdx.y; lz <= zhi; lz += gridDim.y) {
+            for (int ly = ylo + (int)blockIdx.x * rpw + r0; ly <= yhi; ly += (int)gridDim.x * rpw) {
+                R *dst = u + ((g.ndim == 3 ? (int64_t)(z0 + lz + 1) * ny2 : 0) + y0 + ly + 1) * nx2 + 1 + x0;
+                const int64_t o = local_offset(g, blk, 0, ly, lz);
+                for (int c = lane * V; c < ex; c += lanes * V) {
+                    if (c + V <= ex) {
+                        const Chunk<R, V> w = *reinterpret_cast<const Chunk<R, V> *>(s + o + c);
+                        Loose<R> t;
+#pragma unroll
+                        for (int v = 0; v < V; ++v) t.v[v] = w.v[v];
+                        *reinterpret_cast<Loose<R> *>(dst + c) = t;
+                    } else {
+                        for (int v = 0; c + v < ex; ++v) dst[c + v] = s[o + c + v];
+                    }
+                }
+                if (lane == 0 && p.b[0] == 0) dst[-1] = s[o - 1];
+                if (lane == 0 && p.b[0] == g.nb[0] - 1) dst[ex] = s[o + ex];
+            }
         }
     }
 }
@@ -86,116 +162,107 @@ __global__ __launch_bounds__(256) void k_gather(Geom g, const R *__restrict__ s,
 // b = fl_R(h2 * f): the product in FP64, one rounding to R.
 template <typename R>
 __global__ __launch_bounds__(256) void k_scale_source(Geom g, const R *__restrict__ f,
-                                                      R *__restrict__ b, double h2,
-                                                      int64_t rows) {
-    const int nx = g.n[0], ny = g.n[1];
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const int y = (int)(r % ny), z = (int)(r / ny);
-        int by, ly, bz = 0, lz = 0;
-        owner(y, g.e[1], g.nb[1], by, ly);
-        if (g.ndim == 3) owner(z, g.e[2], g.nb[2], bz, lz);
-        const int64_t base = ((int64_t)bz * g.nb[1] + by) * g.nb[0] * g.sstride +
-                             ((int64_t)lz * g.e[1] + ly) * g.e[0];
-        const R *frow = f + r * nx;
-        for (int bx = 0; bx < g.nb[0]; ++bx) {
-            const int ext = extent(g.n[0], g.e[0], bx);
-            const int x0 = bx * g.e[0];
-            const int64_t boff = base + (int64_t)bx * g.sstride;
-            for (int lx = (int)threadIdx.x; lx < ext; lx += blockDim.x)
-                b[boff + lx] = (R)(h2 * (double)frow[x0 + lx]);
+                                                      R *__restrict__ b, double h2, int lanes) {
+    constexpr int V = 16 / (int)sizeof(R);
+    const int64_t nx = g.n[0], ny = g.n[1];
+    const int lane = threadIdx.x & (lanes - 1), r0 = threadIdx.x / lanes, rpw = 256 / lanes;
+    for (int64_t blk = blockIdx.z; blk < g.nblocks; blk += gridDim.z) {
+        const BlockPos p = block_pos(g, blk);
+        const int ex = p.ext[0], ey = p.ext[1], ez = p.ext[2];
+        const int x0 = p.b[0] * g.e[0], y0 = p.b[1] * g.e[1], z0 = p.b[2] * g.e[2];
+        for (int lz = (int)blockIdx.y; lz < ez; lz += gridDim.y) {
+            for (int ly = (int)blockIdx.x * rpw + r0; ly < ey; ly += (int)gridDim.x * rpw) {
+                const R *src = f + ((int64_t)(z0 + lz) * ny + y0 + ly) * nx + x0;
+                R *dst = b + blk * g.sstride + ((int64_t)lz * g.e[1] + ly) * g.e[0];
+                for (int c = lane * V; c < ex; c += lanes * V) {
+                    if (c + V <= ex) {
+                        const Loose<R> t = *reinterpret_cast<const Loose<R> *>(src + c);
+                        Chunk<R, V> w;
+#pragma unroll
+                        for (int v = 0; v < V; ++v) w.v[v] = (R)(h2 * (double)t.v[v]);
+                        *reinterpret_cast<Chunk<R, V> *>(dst + c) = w;
+                    } else {
+                        for (int v = 0; c + v < ex; ++v) dst[c + v] = (R)(h2 * (double)src[c + v]);
+                    }
+                }
+            }
         }
     }
 }
 
-// Halo exchange.  Work item (block, face, t): face = 2*axis + side (side 0 =
-// low, 1 = high), t enumerates the face's cells over the block's extents in
-// the other axes (first of them fastest, so y- and z-faces are contiguous
-// rows).  Faces on the domain boundary keep the Dirichlet values.
-template <typename R>
-__global__ __launch_bounds__(256) void k_halo_exchange(Geom g, R *__restrict__ s,
-                                                       int64_t maxface, int64_t total) {
-    const int nf = 2 * g.ndim;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t t = i % maxface;
-        const int64_t rest = i / maxface;
-        const int face = (int)(rest % nf);
-        const int64_t blk = rest / nf;
-        const int axis = face >> 1, side = face & 1;
-        int bc[3];
-        bc[0] = (int)(blk % g.nb[0]);
-        bc[1] = (int)((blk / g.nb[0]) % g.nb[1]);
-        bc[2] = (int)(blk / ((int64_t)g.nb[0] * g.nb[1]));
-        if (side == 0 && bc[axis] == 0) continue;
-        if (side == 1 && bc[axis] == g.nb[axis] - 1) continue;
-        int ext[3];
-        for (int a = 0; a < 3; ++a) ext[a] = a < g.ndim ? extent(g.n[a], g.e[a], bc[a]) : 1;
-        // the two tangential axes, lower one first
-        const int ta = axis == 0 ? 1 : 0;
-        const int tb = axis == 2 ? 1 : 2;
-        const int64_t fa = ext[ta];
-        const int64_t fb = (g.ndim == 3) ? ext[tb] : 1;
-        if (t >= fa * fb) continue;
-        int loc[3] = {0, 0, 0};
-        loc[ta] = (int)(t % fa);
-        if (g.ndim == 3) loc[tb] = (int)(t / fa);
-        loc[axis] = side == 0 ? -1 : ext[axis];
-        const int64_t dst = local_offset(g, blk, loc[0], loc[1], loc[2]);
-        // the halo cell's global coordinates; its owner is the face neighbour
-        const int gx = bc[0] * g.e[0] + loc[0];
-        const int gy = bc[1] * g.e[1] + loc[1];
-        const int gz = g.ndim == 3 ? bc[2] * g.e[2] + loc[2] : 0;
-        s[dst] = s[state_offset(g, gx, gy, gz)];
+// Cell t of a face of a block along AXIS (the lower of the two tangential axes
+// fastest, so y- and z-faces are contiguous rows): its place in the block at
+// normal coordinate `at`, and in the block across the face at `nat`; false
+// beyond the face.
+template <int AXIS>
+__device__ __forceinline__ bool face_cell(const Geom &g, const BlockPos &p, int64_t blk,
+                                          int64_t nbr, int t, int at, int nat, int64_t *here,
+                                          int64_t *there) {
+    constexpr int TA = AXIS == 0 ? 1 : 0, TB = AXIS == 2 ? 1 : 2;
+    const int fa = p.ext[TA];
+    int hi = 0, lo = t;
+    if (g.ndim == 3) {
+        hi = t / fa;
+        lo = t - hi * fa;
+        if (hi >= p.ext[TB]) return false;
+    } else if (t >= fa) {
+        return false;
     }
+    int l[3] = {0, 0, 0}, m[3] = {0, 0, 0};
+    l[TA] = m[TA] = lo;
+    l[TB] = m[TB] = hi;
+    l[AXIS] = at;
+    m[AXIS] = nat;
+    *here = local_offset(g, blk, l[0], l[1], l[2]);
+    *there = local_offset(g, nbr, m[0], m[1], m[2]);
+    return true;
 }
 
-// Face sends of the source blocks b0 .. b1-1: work item (block, face, t) as
-// in k_halo_exchange, but the block is the sender: its edge cells go into
-// the halo of its face neighbour.  Sending the faces of every block fills
-// the same halo cells, with the same values, as k_halo_exchange.
-template <typename R>
-__global__ __launch_bounds__(256) void k_halo_send(Geom g, R *__restrict__ s, int64_t b0,
-                                                   int64_t maxface, int64_t total) {
-    const int nf = 2 * g.ndim;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t t = i % maxface;
-        const int64_t rest = i / maxface;
-        const int face = (int)(rest % nf);
-        const int64_t blk = b0 + rest / nf;
-        const int axis = face >> 1, side = face & 1;
-        int bc[3];
-        bc[0] = (int)(blk % g.nb[0]);
-        bc[1] = (int)((blk / g.nb[0]) % g.nb[1]);
-        bc[2] = (int)(blk / ((int64_t)g.nb[0] * g.nb[1]));
-        if (side == 0 && bc[axis] == 0) continue;
-        if (side == 1 && bc[axis] == g.nb[axis] - 1) continue;
-        int ext[3];
-        for (int a = 0; a < 3; ++a) ext[a] = a < g.ndim ? extent(g.n[a], g.e[a], bc[a]) : 1;
-        const int ta = axis == 0 ? 1 : 0;
-        const int tb = axis == 2 ? 1 : 2;
-        const int64_t fa = ext[ta];
-        const int64_t fb = (g.ndim == 3) ? ext[tb] : 1;
-        if (t >= fa * fb) continue;
-        int loc[3] = {0, 0, 0};
-        loc[ta] = (int)(t % fa);
-        if (g.ndim == 3) loc[tb] = (int)(t / fa);
-        loc[axis] = side == 0 ? 0 : ext[axis] - 1;  // the block's edge cell
-        const int64_t src = local_offset(g, blk, loc[0], loc[1], loc[2]);
-        // the neighbour across the face and the halo slot facing this block
-        int64_t step = 1;
-        for (int a = 0; a < axis; ++a) step *= g.nb[a];
-        const int64_t nbr = side == 0 ? blk - step : blk + step;
-        int nloc[3] = {loc[0], loc[1], loc[2]};
-        nloc[axis] = side == 0 ? g.e[axis] : -1;  // a low neighbour is a full block
-        s[local_offset(g, nbr, nloc[0], nloc[1], nloc[2])] = s[src];
+// One face of block blk.  SEND: the block's edge cells go into the halo of its
+// face neighbour; otherwise the block's halo takes the neighbour's edge
+// cells.  kFaceCells cells per thread: one per thread was bound by workgroup
+// dispatch at 512^3 in 64^3 blocks (12.6 M halo cells).
+constexpr int kFaceCells = 4;
+template <typename R, int AXIS, bool SEND>
+__device__ __forceinline__ void face_copy(const Geom &g, R *__restrict__ s, int64_t blk,
+                                          const BlockPos &p, int side) {
+    if (side == 0 ? p.b[AXIS] == 0 : p.b[AXIS] == g.nb[AXIS] - 1) return;  // the domain's ring
+    const int64_t step = AXIS == 0 ? 1 : AXIS == 1 ? g.nb[0] : (int64_t)g.nb[0] * g.nb[1];
+    const int64_t nbr = side == 0 ? blk - step : blk + step;
+    // a low neighbour is a full block
+    const int at = SEND ? (side == 0 ? 0 : p.ext[AXIS] - 1) : (side == 0 ? -1 : p.ext[AXIS]);
+    const int nat = SEND ? (side == 0 ? g.e[AXIS] : -1) : (side == 0 ? g.e[AXIS] - 1 : 0);
+    int64_t here[kFaceCells], there[kFaceCells];
+    bool in[kFaceCells];
+    R v[kFaceCells];
+#pragma unroll
+    for (int k = 0; k < kFaceCells; ++k) {
+        const int t = (blockIdx.x * kFaceCells + k) * 256 + threadIdx.x;
+        in[k] = face_cell<AXIS>(g, p, blk, nbr, t, at, nat, &here[k], &there[k]);
+        if (in[k]) v[k] = s[SEND ? here[k] : there[k]];
     }
+#pragma unroll
+    for (int k = 0; k < kFaceCells; ++k)
+        if (in[k]) s[SEND ? there[k] : here[k]] = v[k];
 }
 
-// Grid of the row maps: one workgroup per row, rows strided beyond 2^20.
-static inline dim3 row_grid(int64_t rows) {
-    const int64_t gx = rows < 1 ? 1 : rows > (1 << 20) ? (1 << 20) : rows;
-    return dim3((unsigned)gx);
+// Halo exchange (SEND = false) of every block, or the face sends of the
+// blocks b0 .. b1-1: sending the faces of every block fills the same halo
+// cells, with the same values, as the exchange.  Grid: x over a face's cells,
+// y = 2 * axis + side (side 0 = low, 1 = high), z over blocks.  Faces on the
+// domain boundary keep the Dirichlet values.
+template <typename R, bool SEND>
+__global__ __launch_bounds__(256) void k_halo(Geom g, R *__restrict__ s, int64_t b0, int64_t b1) {
+    const int face = blockIdx.y, axis = face >> 1, side = face & 1;
+    for (int64_t blk = b0 + blockIdx.z; blk < b1; blk += gridDim.z) {
+        const BlockPos p = block_pos(g, blk);
+        if (axis == 0)
+            face_copy<R, 0, SEND>(g, s, blk, p, side);
+        else if (axis == 1)
+            face_copy<R, 1, SEND>(g, s, blk, p, side);
+        else
+            face_copy<R, 2, SEND>(g, s, blk, p, side);
+    }
 }
 
 static inline int grid_for(int64_t total) {
@@ -208,9 +275,9 @@ static inline int grid_for(int64_t total) {
 template <typename R>
 hipError_t launch_scatter(const Geom &g, const void *u, void *s0, void *s1, bool zero_ring,
                           hipStream_t st) {
-    const int64_t rows = (int64_t)(g.n[1] + 2) * (g.ndim == 3 ? g.n[2] + 2 : 1);
-    hipLaunchKernelGGL(k_scatter<R>, row_grid(rows), dim3(256), 0, st, g,
-                       (const R *)u, (R *)s0, (R *)s1, rows, zero_ring ? 1 : 0);
+    const RowMap m = row_map<R>(g, g.e[1] + 2, g.ndim == 3 ? g.e[2] + 2 : 1);
+    hipLaunchKernelGGL(k_scatter<R>, m.grid, dim3(256), 0, st, g, (const R *)u, (R *)s0, (R *)s1,
+                       m.lanes, zero_ring ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -313,44 +380,44 @@ hipError_t launch_adjoint_finish(const Geom &g, const double *gb, double h2, dou
 
 template <typename R>
 hipError_t launch_gather(const Geom &g, const void *s, void *u, hipStream_t st) {
-    const int64_t rows = (int64_t)(g.n[1] + 2) * (g.ndim == 3 ? g.n[2] + 2 : 1);
-    hipLaunchKernelGGL(k_gather<R>, row_grid(rows), dim3(256), 0, st, g,
-                       (const R *)s, (R *)u, rows);
+    const RowMap m = row_map<R>(g, g.e[1] + 2, g.ndim == 3 ? g.e[2] + 2 : 1);
+    hipLaunchKernelGGL(k_gather<R>, m.grid, dim3(256), 0, st, g, (const R *)s, (R *)u, m.lanes);
     return hipGetLastError();
 }
 
 template <typename R>
 hipError_t launch_scale_source(const Geom &g, const void *f, void *b, double h2, hipStream_t st) {
-    const int64_t rows = (int64_t)g.n[1] * (g.ndim == 3 ? g.n[2] : 1);
-    hipLaunchKernelGGL(k_scale_source<R>, row_grid(rows), dim3(256), 0, st, g,
-                       (const R *)f, (R *)b, h2, rows);
+    const RowMap m = row_map<R>(g, g.e[1], g.ndim == 3 ? g.e[2] : 1);
+    hipLaunchKernelGGL(k_scale_source<R>, m.grid, dim3(256), 0, st, g, (const R *)f, (R *)b, h2,
+                       m.lanes);
     return hipGetLastError();
 }
 
-int64_t halo_maxface(const Geom &g) {
-    if (g.ndim == 2) return g.e[0] > g.e[1] ? g.e[0] : g.e[1];
-    int64_t a = (int64_t)g.e[1] * g.e[2], b = (int64_t)g.e[0] * g.e[2], c = (int64_t)g.e[0] * g.e[1];
+static bool face_grid(const Geom &g, int64_t blocks, dim3 *grid) {
+    const int64_t a = (int64_t)g.e[1] * g.e[2], b = (int64_t)g.e[0] * g.e[2], c = (int64_t)g.e[0] * g.e[1];
     int64_t m = a > b ? a : b;
-    return m > c ? m : c;
+    if (g.ndim == 3 && c > m) m = c;
+    if (m > 0x7fffffff - 4096) return false;
+    *grid = dim3((unsigned)((m + 256 * kFaceCells - 1) / (256 * kFaceCells)), 2 * g.ndim,
+                 (unsigned)(blocks < 65535 ? blocks : 65535));
+    return true;
 }
 
 template <typename R>
 hipError_t launch_halo_exchange(const Geom &g, void *s, hipStream_t st) {
-    const int64_t maxface = halo_maxface(g);
-    const int64_t total = g.nblocks * 2 * g.ndim * maxface;
-    if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_halo_exchange<R>, dim3(grid_for(total)), dim3(256), 0, st, g, (R *)s,
-                       maxface, total);
+    if (g.nblocks <= 1) return hipSuccess;  // no internal face
+    dim3 grid;
+    if (!face_grid(g, g.nblocks, &grid)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_halo<R, false>), grid, dim3(256), 0, st, g, (R *)s, (int64_t)0, g.nblocks);
     return hipGetLastError();
 }
 
 template <typename R>
 hipError_t launch_halo_send(const Geom &g, void *s, int64_t b0, int64_t b1, hipStream_t st) {
-    const int64_t maxface = halo_maxface(g);
-    const int64_t total = (b1 - b0) * 2 * g.ndim * maxface;
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_halo_send<R>, dim3(grid_for(total)), dim3(256), 0, st, g, (R *)s, b0,
-                       maxface, total);
+    if (b1 <= b0) return hipSuccess;
+    dim3 grid;
+    if (!face_grid(g, b1 - b0, &grid)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_halo<R, true>), grid, dim3(256), 0, st, g, (R *)s, b0, b1);
     return hipGetLastError();
 }
 

@@ -7,6 +7,7 @@
 
 namespace jac {
 
+// Fills both state buffers, block frames included (no halo exchange needed).
 // zero_ring: write 0 instead of the ring values (the adjoint state's ring).
 template <typename R>
 hipError_t launch_scatter(const Geom &g, const void *u, void *s0, void *s1, bool zero_ring,
