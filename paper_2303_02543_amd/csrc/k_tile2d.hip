@@ -57,13 +57,13 @@ struct T2Lane {
 template <typename R, int V>
 using T2Sh = Cells<R, V> (*)[kT2Waves + 2][2][64];
 
-// One sweep from cur to nxt; buffer `par` of the LDS rows.
-template <typename R, int V, int RY, int MODE, bool EDGE, bool RES>
-__device__ __forceinline__ void t2_sweep(const R (&cur)[RY][V], R (&nxt)[RY][V],
-                                         const R (&b)[RY][V], double (&ga)[RY][V],
-                                         T2Lane<R, V, RY> &L, T2Sh<R, V> sh, int par) {
-    using C = Cells<R, V>;
-    C lo, hi;
+// The rows just above and below the wave's own, through buffer `par` of the
+// LDS rows.
+template <typename R, int V, int RY>
+__device__ __forceinline__ void t2_rows_of(const R (&cur)[RY][V], const T2Lane<R, V, RY> &L,
+                                           T2Sh<R, V> sh, int par, Cells<R, V> &so,
+                                           Cells<R, V> &no) {
+    Cells<R, V> lo, hi;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
         lo.v[v] = cur[0][v];
@@ -72,7 +72,43 @@ __device__ __forceinline__ void t2_sweep(const R (&cur)[RY][V], R (&nxt)[RY][V],
     sh[par][L.wv + 1][0][L.lane] = lo;
     sh[par][L.wv + 1][1][L.lane] = hi;
     __syncthreads();
-    const C so = sh[par][L.wv][1][L.lane], no = sh[par][L.wv + 2][0][L.lane];
+    so = sh[par][L.wv][1][L.lane];
+    no = sh[par][L.wv + 2][0][L.lane];
+}
+
+// Residual partial of the pass's input, FP64 from widened values.
+template <typename R, int V, int RY, int MODE, bool EDGE>
+__device__ __forceinline__ void t2_residual(const R (&cur)[RY][V], const R (&b)[RY][V],
+                                            T2Lane<R, V, RY> &L, T2Sh<R, V> sh) {
+    Cells<R, V> so, no;
+    t2_rows_of<R, V, RY>(cur, L, sh, 1, so, no);
+#pragma unroll
+    for (int j = 0; j < RY; ++j) {
+        const R eo = EDGE ? L.e[j] : (R)0;
+        const R left = shift_up(eo, cur[j][V - 1]);
+        const R right = shift_down(eo, cur[j][0]);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const double Wd = v > 0 ? cur[j][v - 1] : left;
+            const double Ed = v < V - 1 ? cur[j][v + 1] : right;
+            const double Sd = j > 0 ? cur[j - 1][v] : so.v[v];
+            const double Nd = j < RY - 1 ? cur[j + 1][v] : no.v[v];
+            const double sd = (Wd + Ed) + (Sd + Nd);
+            const double bd = MODE == T2_POISSON ? (double)b[j][v] : 0.0;
+            const double r = bd - (4.0 * (double)cur[j][v] - sd);
+            const bool mine = L.out && j >= L.o0 && j < L.o1 && (!EDGE || v < L.nxr);
+            L.acc += mine ? r * r : 0.0;
+        }
+    }
+}
+
+// One sweep from cur to nxt; buffer `par` of the LDS rows.
+template <typename R, int V, int RY, int MODE, bool EDGE>
+__device__ __forceinline__ void t2_sweep(const R (&cur)[RY][V], R (&nxt)[RY][V],
+                                         const R (&b)[RY][V], double (&ga)[RY][V],
+                                         T2Lane<R, V, RY> &L, T2Sh<R, V> sh, int par) {
+    Cells<R, V> so, no;
+    t2_rows_of<R, V, RY>(cur, L, sh, par, so, no);
     const R w = (R)0.25;
 #pragma unroll
     for (int jj = 0; jj < RY; ++jj) {
@@ -89,14 +125,6 @@ __device__ __forceinline__ void t2_sweep(const R (&cur)[RY][V], R (&nxt)[RY][V],
             const R Nv = j < RY - 1 ? cur[j + 1][v] : no.v[v];
             const R s = (Wv + Ev) + (Sv + Nv);
             R o = MODE == T2_POISSON ? (s + b[j][v]) * w : s * w;
-            if constexpr (RES) {
-                // residual of the input state, FP64 from widened values
-                const double sd = ((double)Wv + (double)Ev) + ((double)Sv + (double)Nv);
-                const double bd = MODE == T2_POISSON ? (double)b[j][v] : 0.0;
-                const double r = bd - (4.0 * (double)cur[j][v] - sd);
-                const bool mine = L.out && j >= L.o0 && j < L.o1 && (!EDGE || v < L.nxr);
-                L.acc += mine ? r * r : 0.0;
-            }
             // adjoint: the level swept from is the next term of the sum
             if constexpr (MODE == T2_ADJOINT) ga[j][v] += (double)(w * cur[j][v]);
             // ring cells and cells beyond the ring keep their values
@@ -222,23 +250,21 @@ __device__ __forceinline__ void t2_body(const Geom &g, const R *__restrict__ uin
         sh[0][slot][L.wv == 0 ? 1 : 0][L.lane] = r;
         sh[1][slot][L.wv == 0 ? 1 : 0][L.lane] = r;
     }
-    auto run = [&](R (&x)[RY][V], R (&z)[RY][V], int n, int par) {
-        for (int i = 0; i + 1 < n; i += 2) {
-            t2_sweep<R, V, RY, MODE, EDGE, false>(x, z, b, ga, L, sh, par);
-            t2_sweep<R, V, RY, MODE, EDGE, false>(z, x, b, ga, L, sh, par ^ 1);
-        }
-        if (n & 1) {
-            t2_sweep<R, V, RY, MODE, EDGE, false>(x, z, b, ga, L, sh, par);
-            t2_store<R, V, RY>(uout, z, L, rows, col);
-        } else {
-            t2_store<R, V, RY>(uout, x, L, rows, col);
-        }
-    };
     if constexpr (RES) {
-        t2_sweep<R, V, RY, MODE, EDGE, true>(p, q, b, ga, L, sh, 0);
-        run(q, p, t - 1, 1);
+        t2_residual<R, V, RY, MODE, EDGE>(p, b, L, sh);
+        // the sum is taken here: left to itself the compiler moves it to its
+        // use at the kernel's end, with every row's neighbours held till then
+        asm volatile("" : "+v"(L.acc));
+    }
+    for (int i = 0; i + 1 < t; i += 2) {
+        t2_sweep<R, V, RY, MODE, EDGE>(p, q, b, ga, L, sh, 0);
+        t2_sweep<R, V, RY, MODE, EDGE>(q, p, b, ga, L, sh, 1);
+    }
+    if (t & 1) {
+        t2_sweep<R, V, RY, MODE, EDGE>(p, q, b, ga, L, sh, 0);
+        t2_store<R, V, RY>(uout, q, L, rows, col);
     } else {
-        run(p, q, t, 0);
+        t2_store<R, V, RY>(uout, p, L, rows, col);
     }
     if constexpr (MODE == T2_ADJOINT) {
 #pragma unroll
