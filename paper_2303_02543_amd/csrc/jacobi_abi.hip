@@ -883,7 +883,7 @@ int do_deep_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos) {
         const int *pre = h->d_prefix + (size_t)t * (nb + 1);
         if (nd == 2)
             HIP_TRY(jac::launch_march2d_batch<R>(h->d_tab[h->cur], pre, (int)nb, h->d_active, h->d_pc,
-                                                 nullptr, true, t, rows, nwork, h->stream,
+                                                 0, nullptr, true, t, rows, nwork, h->stream,
                                                  h->has_source ? 1 : 0),
                     "deep pass launch");
         else
@@ -1688,6 +1688,7 @@ struct jacobi_batch_s {
     std::vector<char> grid_set;
     int depth, rows, use_graph;
     int table_rows;  // tile height the uploaded tables were built for (0: none)
+    int default_rows[kMaxDepth + 1] = {};  // batch_rows of each depth (0: not computed)
     int *h_active;   // pinned host copy of the activity flags
     // captured interval
     hipGraphExec_t graph;
@@ -1709,9 +1710,43 @@ void batch_drop_graph(jacobi_batch_t b) {
     b->graph_R = 0;
 }
 
-int batch_rows(const jacobi_batch_t b) { return b->rows > 0 ? b->rows : 64; }
+// Default schedule: the single grid's depth, and the smallest tile height whose
+// tiles over all grids fit the fewest rounds of resident waves that leave it
+// at 256 rows or less.  12 grids of 257 .. 2049 a side, FP32, 50 sweeps: depth 13
+// in one round 4 passes of 60 us, the fixed depth 7 and 64 rows before it 8
+// passes of 53 us; 64 grids of up to 4097: within a few percent of the
+// autotuned 192 rows.
 int batch_depth(const jacobi_batch_t b) {
-    return b->depth > 0 ? b->depth : (b->dtype == JACOBI_F32 ? 7 : 4);
+    return b->depth > 0 ? b->depth : (b->dtype == JACOBI_F32 ? 13 : 4);
+}
+int batch_rows(const jacobi_batch_t b) {
+    if (b->rows > 0) return b->rows;
+    const int depth = pick_depth(b->dtype, batch_depth(b));
+    int &cached = b->default_rows[depth];
+    if (cached > 0) return cached;
+    int cus = 0, dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        return 64;
+    const int wpc = b->dtype == JACOBI_F32 ? jac::march2d_waves_per_cu<float>(depth, 1)
+                                           : jac::march2d_waves_per_cu<double>(depth, 1);
+    if (wpc <= 0) return 64;
+    auto tiles = [&](int rows) {
+        int64_t n = 0;
+        for (const Geom &g : b->bl.geoms)
+            n += b->dtype == JACOBI_F32 ? jac::march2d_batch_work<float>(g, depth, rows)
+                                        : jac::march2d_batch_work<double>(g, depth, rows);
+        return n;
+    };
+    const int64_t slots = (int64_t)wpc * cus;
+    const int64_t rounds = (tiles(256) + slots - 1) / slots;
+    int lo = kMinRows, hi = 256;
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (tiles(mid) <= rounds * slots) hi = mid; else lo = mid + 1;
+    }
+    return cached = lo;
 }
 
 // Work tables for the current tile height: per grid its tiles per strip, and
@@ -1771,19 +1806,21 @@ int batch_interval(jacobi_batch_t b, int64_t n, double tol, bool check = true) {
     const std::vector<int> ds = batch_passes(b->dtype, batch_depth(b), n);
     const int rows = batch_rows(b);
     const int cnt = b->count;
+    if (n == 0) return JACOBI_OK;
     for (size_t p = 0; p < ds.size(); ++p) {
         const int t = ds[p];
         const int *pre = b->d_prefix + (size_t)t * (cnt + 1);
         const int nwork = b->h_prefix[(size_t)t * (cnt + 1) + cnt];
         HIP_TRY(jac::launch_march2d_batch<R>(b->d_grids, pre, cnt, b->st.active, b->st.pass_count,
-                                             (p == 0 && check) ? b->partials : nullptr, true, t,
+                                             (int)p, (p == 0 && check) ? b->partials : nullptr, true, t,
                                              rows, nwork, b->stream),
                 "batch pass launch");
         if (p == 0 && check)
             HIP_TRY(jac::launch_batch_check(pre, b->partials, cnt, b->st, tol, false, b->stream),
                     "batch check launch");
-        HIP_TRY(jac::launch_batch_advance(b->st, t, b->stream), "batch advance launch");
     }
+    HIP_TRY(jac::launch_batch_advance(b->st, (int)ds.size(), (int)n, b->stream),
+            "batch advance launch");
     return JACOBI_OK;
 }
 
@@ -1793,7 +1830,7 @@ int batch_final(jacobi_batch_t b, double tol) {
     const int cnt = b->count;
     const int *pre = b->d_prefix + (size_t)1 * (cnt + 1);
     const int nwork = b->h_prefix[(size_t)1 * (cnt + 1) + cnt];
-    HIP_TRY(jac::launch_march2d_batch<R>(b->d_grids, pre, cnt, b->st.active, b->st.pass_count,
+    HIP_TRY(jac::launch_march2d_batch<R>(b->d_grids, pre, cnt, b->st.active, b->st.pass_count, 0,
                                          b->partials, false, 1, batch_rows(b), nwork, b->stream),
             "batch residual launch");
     HIP_TRY(jac::launch_batch_check(pre, b->partials, cnt, b->st, tol, true, b->stream),

@@ -34,9 +34,11 @@ __global__ void k_batch_init(int count, BatchState st) {
     }
 }
 
-__global__ void k_batch_advance(BatchState st, int sweeps) {
+// The passes and sweeps of an interval, counted once at its end (once per pass
+// it cost a launch of 4.6 us each, 7% of a 12-grid batch).
+__global__ void k_batch_advance(BatchState st, int passes, int sweeps) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        *st.pass_count += 1;
+        *st.pass_count += passes;
         *st.k_now += sweeps;
     }
 }
@@ -96,8 +98,8 @@ hipError_t launch_batch_init(int count, const BatchState &st, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_batch_advance(const BatchState &st, int sweeps, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_advance, dim3(1), dim3(64), 0, s, st, sweeps);
+hipError_t launch_batch_advance(const BatchState &st, int passes, int sweeps, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_advance, dim3(1), dim3(64), 0, s, st, passes, sweeps);
     return hipGetLastError();
 }
 

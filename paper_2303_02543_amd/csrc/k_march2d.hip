@@ -621,14 +621,16 @@ __global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2
 // Batched pass: the work items of all grids of a batch in one launch.  Work
 // item w belongs to grid gi with prefix[gi] <= w < prefix[gi+1]; inactive
 // grids (stopped by the convergence test) skip their items.  All active
-// grids advance together, so the input buffer is u[pass_count & 1].
+// grids advance together: pass_count counts the passes before the interval
+// and `pass` those of the interval before this one, so the input buffer is
+// u[(pass_count + pass) & 1].
 // MODE: Poisson (the batched solver; the deep-halo form with a source) or
 // Laplace (the deep-halo form without one).
 template <typename R, int T, int P, bool RES, int MODE>
 __global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_march2d_batch(const BatchGrid *__restrict__ grids,
                                                        const int *__restrict__ prefix, int ngrids,
                                                        const int *__restrict__ active,
-                                                       const int *__restrict__ pass_count,
+                                                       const int *__restrict__ pass_count, int pass,
                                                        double *__restrict__ res, int store,
                                                        int rows, int nwork) {
     using S = M2<R, T, P, MODE>;
@@ -645,7 +647,7 @@ __global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2
     const int gi = __builtin_amdgcn_readfirstlane(lo);
     if (!active[gi]) return;
     const Geom g = grids[gi].g;
-    const int par = *pass_count & 1;
+    const int par = (*pass_count + pass) & 1;
     const R *uin = (const R *)grids[gi].u[par];
     R *uout = store ? (R *)grids[gi].u[par ^ 1] : nullptr;
     m2_run<R, T, P, MODE, RES>(g, uin, uout, SRC ? (const R *)grids[gi].b : nullptr,
@@ -680,8 +682,8 @@ hipError_t m2_launch_t(const Geom &g, const void *uin, void *uout, const void *b
                        double *gacc, int rows, hipStream_t st, int64_t *nwork_out, int nt);
 template <typename R, int T>
 hipError_t m2b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, const int *active,
-                        const int *pass_count, double *res, bool store, int rows, int nwork,
-                        hipStream_t st, int mode);
+                        const int *pass_count, int pass, double *res, bool store, int rows,
+                        int nwork, hipStream_t st, int mode);
 template <typename R, int T>
 int m2_waves_per_cu_t(int mode);
 
@@ -734,32 +736,32 @@ hipError_t m2_launch_t(const Geom &g, const void *uin, void *uout, const void *b
 
 template <typename R, int T, int P>
 static hipError_t m2b_launch_p(const BatchGrid *grids, const int *prefix, int ngrids,
-                               const int *active, const int *pass_count, double *res, bool store,
-                               int rows, int nwork, hipStream_t st, int mode) {
+                               const int *active, const int *pass_count, int pass, double *res,
+                               bool store, int rows, int nwork, hipStream_t st, int mode) {
     const int grid = (nwork + kM2Waves - 1) / kM2Waves;
     if (mode == MODE_LAPLACE) {
         // the deep-halo form without a source: no residual
         if (res) return hipErrorInvalidValue;
         hipLaunchKernelGGL((k_march2d_batch<R, T, P, false, MODE_LAPLACE>), dim3(grid), dim3(64 * kM2Waves),
-                           0, st, grids, prefix, ngrids, active, pass_count, res, store ? 1 : 0,
+                           0, st, grids, prefix, ngrids, active, pass_count, pass, res, store ? 1 : 0,
                            rows, nwork);
     } else if (res)
         hipLaunchKernelGGL((k_march2d_batch<R, T, P, true, MODE_POISSON>), dim3(grid), dim3(64 * kM2Waves),
-                           0, st, grids, prefix, ngrids, active, pass_count, res, store ? 1 : 0,
+                           0, st, grids, prefix, ngrids, active, pass_count, pass, res, store ? 1 : 0,
                            rows, nwork);
     else
         hipLaunchKernelGGL((k_march2d_batch<R, T, P, false, MODE_POISSON>), dim3(grid), dim3(64 * kM2Waves),
-                           0, st, grids, prefix, ngrids, active, pass_count, res, store ? 1 : 0,
+                           0, st, grids, prefix, ngrids, active, pass_count, pass, res, store ? 1 : 0,
                            rows, nwork);
     return hipGetLastError();
 }
 
 template <typename R, int T>
 hipError_t m2b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, const int *active,
-                        const int *pass_count, double *res, bool store, int rows, int nwork,
-                        hipStream_t st, int mode) {
-    return m2b_launch_p<R, T, m2_pf<T>()>(grids, prefix, ngrids, active, pass_count, res, store,
-                                          rows, nwork, st, mode);
+                        const int *pass_count, int pass, double *res, bool store, int rows,
+                        int nwork, hipStream_t st, int mode) {
+    return m2b_launch_p<R, T, m2_pf<T>()>(grids, prefix, ngrids, active, pass_count, pass, res,
+                                          store, rows, nwork, st, mode);
 }
 
 template <typename R, int T>
@@ -784,7 +786,7 @@ int m2_waves_per_cu_t(int mode) {
                                           double *, double *, int, hipStream_t, int64_t *,     \
                                           int);                                                \
     template hipError_t m2b_launch_t<R, T>(const BatchGrid *, const int *, int, const int *,   \
-                                           const int *, double *, bool, int, int,              \
+                                           const int *, int, double *, bool, int, int,         \
                                            hipStream_t, int);                                  \
     template int m2_waves_per_cu_t<R, T>(int);
 
@@ -861,11 +863,12 @@ int64_t march2d_batch_work(const Geom &g, int depth, int rows) {
 
 template <typename R>
 hipError_t launch_march2d_batch(const BatchGrid *grids, const int *prefix, int ngrids,
-                                const int *active, const int *pass_count, double *res, bool store,
-                                int depth, int rows, int nwork, hipStream_t st, int mode) {
+                                const int *active, const int *pass_count, int pass, double *res,
+                                bool store, int depth, int rows, int nwork, hipStream_t st,
+                                int mode) {
     if (nwork <= 0) return hipSuccess;
     JAC_M2_SWITCH(depth, m2b_launch_t, R, hipErrorInvalidValue, grids, prefix, ngrids, active,
-                  pass_count, res, store, rows, nwork, st, mode)
+                  pass_count, pass, res, store, rows, nwork, st, mode)
 }
 
 template hipError_t launch_sweep2d_march<float>(const Geom &, const void *, void *, const void *,
@@ -877,10 +880,10 @@ template hipError_t launch_sweep2d_march<double>(const Geom &, const void *, voi
 template int64_t march2d_batch_work<float>(const Geom &, int, int);
 template int64_t march2d_batch_work<double>(const Geom &, int, int);
 template hipError_t launch_march2d_batch<float>(const BatchGrid *, const int *, int, const int *,
-                                                const int *, double *, bool, int, int, int,
+                                                const int *, int, double *, bool, int, int, int,
                                                 hipStream_t, int);
 template hipError_t launch_march2d_batch<double>(const BatchGrid *, const int *, int, const int *,
-                                                 const int *, double *, bool, int, int, int,
+                                                 const int *, int, double *, bool, int, int, int,
                                                  hipStream_t, int);
 template int64_t march2d_work_items<float>(const Geom &, int, int);
 template int64_t march2d_work_items<double>(const Geom &, int, int);

@@ -102,13 +102,15 @@ hipError_t launch_tile2d(const Geom &g, const void *uin, void *uout, const void 
                          double *gacc, const Tile2dPlan &pl, hipStream_t st);
 
 // Batched pass over the grids of a batch (Poisson kernels; see
-// k_march2d_batch).  nwork = prefix[ngrids]; res: one partial per work item
-// (NULL: no residual); store = false: residual only.
+// k_march2d_batch).  nwork = prefix[ngrids]; pass: passes done since
+// pass_count was last advanced; res: one partial per work item (NULL: no
+// residual); store = false: residual only.
 // mode: 1 Poisson (the grids' sources), 0 Laplace (no residual).
 template <typename R>
 hipError_t launch_march2d_batch(const BatchGrid *grids, const int *prefix, int ngrids,
-                                const int *active, const int *pass_count, double *res, bool store,
-                                int depth, int rows, int nwork, hipStream_t st, int mode = 1);
+                                const int *active, const int *pass_count, int pass, double *res,
+                                bool store, int depth, int rows, int nwork, hipStream_t st,
+                                int mode = 1);
 // Work items of one grid at this depth / tile height.
 template <typename R>
 int64_t march2d_batch_work(const Geom &g, int depth, int rows);
@@ -155,7 +157,7 @@ hipError_t launch_deep_source(const Geom &g, const void *b, void *bd, int H, hip
 
 // Batched-solver bookkeeping (k_batch.hip).
 hipError_t launch_batch_init(int count, const BatchState &st, hipStream_t s);
-hipError_t launch_batch_advance(const BatchState &st, int sweeps, hipStream_t s);
+hipError_t launch_batch_advance(const BatchState &st, int passes, int sweeps, hipStream_t s);
 hipError_t launch_batch_check(const int *prefix, const double *partials, int count,
                               const BatchState &st, double tol, bool final_check, hipStream_t s);
 
