@@ -664,6 +664,33 @@ int do_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos = true) {
         return JACOBI_OK;
     }
     if ((h->flags & JACOBI_FLAG_OVERLAP) && explicit_halo) return do_sweep_overlap<R>(h, n, res_first);
+    if (explicit_halo && n > 0 && jac::sweep2d_sends(h->g, h->rows)) {
+        // each sweep also writes its edge cells into the neighbours' halos of
+        // the new state, and the first sums the residual of its input
+        for (int64_t k = 0; k < n; ++k) {
+            double *part = nullptr;
+            if (k == 0 && res_first) {
+                const int64_t nw = jac::sweep_tile_partials<R>(h->g, h->rows);
+                if (nw < 0 || (size_t)nw > h->lay.part_cap)
+                    return fail(JACOBI_E_INVAL, "partials overflow");
+                part = h->partials;
+            }
+            int rc = prof_begin(h);
+            if (rc) return rc;
+            int64_t nwork = 0;
+            HIP_TRY(jac::launch_sweep2d_tile_send<R>(h->g, h->u[h->cur], h->u[h->cur ^ 1], b, part,
+                                                     h->rows, h->stream, &nwork,
+                                                     h->flags & JACOBI_FLAG_NT_STORES),
+                    "sweep launch");
+            rc = prof_end(h, 1);
+            if (rc) return rc;
+            h->cur ^= 1;
+            if (part)
+                HIP_TRY(jac::launch_residual_final(part, (int)nwork, res_first, h->stream),
+                        "residual launch");
+        }
+        return JACOBI_OK;
+    }
     if (explicit_halo || n == 0) {
         if (res_first) {
             int rc = do_residual<R>(h, res_first);

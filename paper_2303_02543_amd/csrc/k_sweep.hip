@@ -203,7 +203,11 @@ __global__ __launch_bounds__(256) void k_sweep_rows(Geom g, const R *__restrict_
 // to run before the sweep (the exchange fused into the loads); on the
 // domain's boundary the stored halo is the Dirichlet ring and is read as it
 // is.  RES: each wave also sums the FP64 residual of its input rows into
-// res[4 * item + wave].
+// res[4 * item + wave].  SEND: the block's new edge cells are also written into
+// the halos of its face neighbours in the new state (which nothing reads
+// before the next sweep), so the exchange that the next sweep needs is done
+// when this one ends; as a launch of its own it took 8 us per sweep beside the
+// sweep's 32 (4096^2 FP32 in 256^2 blocks).
 //
 // Work items are numbered in memory order (column chunk fastest, then tile,
 // then block).  Workgroups are dealt round-robin over the 8 XCDs; runs of
@@ -223,7 +227,7 @@ __device__ __forceinline__ int tile_item(int p, int np, int group) {
     return (k / group) * round + x * group + (k % group);
 }
 
-template <typename R, bool SRC, bool FUSED, bool RES>
+template <typename R, bool SRC, bool FUSED, bool SEND, bool RES>
 __global__ __launch_bounds__(256) void k_sweep_tile(Geom g, const R *__restrict__ uin,
                                                     R *__restrict__ uout,
                                                     const R *__restrict__ b,
@@ -366,6 +370,31 @@ __global__ __launch_bounds__(256) void k_sweep_tile(Geom g, const R *__restrict_
                 for (int v = 0; v < V; ++v)
                     if (upd[v]) orow[g.ax + c + v] = out.v[v];
             }
+            if constexpr (SEND) {
+                // row 0 to the halo above the lower block's last row, the
+                // last row to the upper block's halo row -1
+                auto send_row = [&](int64_t to, int64_t row) {
+                    R *d = uout + to * g.bstride + row * g.pitch;
+                    if (full) {
+                        at_mut<C>(d, lane_b) = out;
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < V; ++v)
+                            if (upd[v]) d[g.ax + c + v] = out.v[v];
+                    }
+                };
+                if (y == 0 && by > 0) send_row(blk - g.nb[0], (int64_t)g.e[1] + 1);
+                if (y == ey - 1 && by < g.nb[1] - 1) send_row(blk + g.nb[0], 0);
+                // column 0 to the west block's east halo, the last column (a
+                // block with an east neighbour is full) to the east block's
+                // west halo
+                if (c == 0 && bx > 0)
+                    uout[(int64_t)(blk - 1) * g.bstride + (int64_t)(y + 1) * g.pitch + g.ax + g.e[0]] =
+                        out.v[0];
+                if (c + V == ex && bx < g.nb[0] - 1)
+                    uout[(int64_t)(blk + 1) * g.bstride + (int64_t)(y + 1) * g.pitch + g.ax - 1] =
+                        out.v[V - 1];
+            }
         }
     };
     if (wv == 0) sh[2][4][lane] = load(y0 - 1);  // "previous step's last row"
@@ -397,7 +426,7 @@ template <typename R> constexpr int sweep_rows_default() { return 8; }
 // round-robin order, the same at 32 tiles, less at 4).
 constexpr int kTileRun = 8;
 
-template <typename R, bool FUSED>
+template <typename R, bool FUSED, bool SEND>
 static hipError_t launch_tile(const Geom &g, const void *uin, void *uout, const void *b,
                               double *res, int rg, int64_t b0, int64_t b1, hipStream_t st,
                               int64_t *nwork, int nt) {
@@ -411,7 +440,7 @@ static hipError_t launch_tile(const Geom &g, const void *uin, void *uout, const 
     const int grp = kTileRun * nchunks;
     const R *bb = (const R *)b;
 #define JAC_TILE(SRCV, RESV)                                                                    \
-    hipLaunchKernelGGL((k_sweep_tile<R, SRCV, FUSED, RESV>), dim3((unsigned)items), dim3(256),  \
+    hipLaunchKernelGGL((k_sweep_tile<R, SRCV, FUSED, SEND, RESV>), dim3((unsigned)items), dim3(256),  \
                        0, st, g, (const R *)uin, (R *)uout, bb, res, steps, ntiles, nchunks,    \
                        (int)b0, (int)items, grp, nt)
     if (b && res)
@@ -433,7 +462,7 @@ static hipError_t launch_sweep_rows(const Geom &g, const void *uin, void *uout, 
     if (rg <= 0) rg = sweep_rows_default<R>();
     const int nchunks = (g.e[0] + W - 1) / W;
     if (rg >= 4)
-        return launch_tile<R, false>(g, uin, uout, b, nullptr, rg, b0, b1, st, nullptr, nt);
+        return launch_tile<R, false, false>(g, uin, uout, b, nullptr, rg, b0, b1, st, nullptr, nt);
     const int ngroups = (g.e[1] + rg - 1) / rg;
     const int64_t nwork = (b1 - b0) * ngroups * nchunks;
     if (nwork > 0x7fffffff - 3) return hipErrorInvalidValue;
@@ -466,7 +495,15 @@ hipError_t launch_sweep2d_tile_fused(const Geom &g, const void *uin, void *uout,
     if (g.ndim != 2) return hipErrorInvalidValue;
     if (rg <= 0) rg = sweep_rows_default<R>();
     if (rg < 4) rg = 4;
-    return launch_tile<R, true>(g, uin, uout, b, res, rg, 0, g.nblocks, st, nwork, nt);
+    return launch_tile<R, true, false>(g, uin, uout, b, res, rg, 0, g.nblocks, st, nwork, nt);
+}
+
+template <typename R>
+hipError_t launch_sweep2d_tile_send(const Geom &g, const void *uin, void *uout, const void *b,
+                                    double *res, int rg, hipStream_t st, int64_t *nwork, int nt) {
+    if (!sweep2d_sends(g, rg)) return hipErrorInvalidValue;
+    if (rg <= 0) rg = sweep_rows_default<R>();
+    return launch_tile<R, false, true>(g, uin, uout, b, res, rg, 0, g.nblocks, st, nwork, nt);
 }
 
 template <typename R>
@@ -499,6 +536,11 @@ template hipError_t launch_sweep2d_tile_fused<float>(const Geom &, const void *,
 template hipError_t launch_sweep2d_tile_fused<double>(const Geom &, const void *, void *,
                                                       const void *, double *, int, hipStream_t,
                                                       int64_t *, int);
+template hipError_t launch_sweep2d_tile_send<float>(const Geom &, const void *, void *, const void *,
+                                                    double *, int, hipStream_t, int64_t *, int);
+template hipError_t launch_sweep2d_tile_send<double>(const Geom &, const void *, void *,
+                                                     const void *, double *, int, hipStream_t,
+                                                     int64_t *, int);
 template hipError_t launch_sweep_local<double>(const Geom &, const void *, void *, const void *,
                                                hipStream_t, int, int64_t, int64_t, int);
 

@@ -44,7 +44,15 @@ template <typename R>
 hipError_t launch_sweep2d_tile_fused(const Geom &g, const void *uin, void *uout, const void *b,
                                      double *res, int rg, hipStream_t st, int64_t *nwork,
                                      int nt = 0);
-// Residual partials of one launch_sweep2d_tile_fused launch.
+// One 2D sweep of every block from its own storage (halos must be current)
+// that also writes the new state's halos: no exchange has to follow.  For rg
+// = 0 (the default) or >= 4 rows per tile (sweep2d_sends); res, nwork: as
+// launch_sweep2d_tile_fused.
+template <typename R>
+hipError_t launch_sweep2d_tile_send(const Geom &g, const void *uin, void *uout, const void *b,
+                                    double *res, int rg, hipStream_t st, int64_t *nwork, int nt);
+inline bool sweep2d_sends(const Geom &g, int rg) { return g.ndim == 2 && (rg <= 0 || rg >= 4); }
+// Residual partials of one launch_sweep2d_tile_fused / _send launch.
 template <typename R>
 int64_t sweep_tile_partials(const Geom &g, int rg);
 // Face sends of blocks b0 .. b1-1: each block's edge cells into the halos of
