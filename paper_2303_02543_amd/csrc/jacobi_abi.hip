@@ -1739,10 +1739,9 @@ void batch_drop_graph(jacobi_batch_t b) {
 
 // Default schedule: the single grid's depth, and the smallest tile height whose
 // tiles over all grids fit the fewest rounds of resident waves that leave it
-// at 256 rows or less.  12 grids of 257 .. 2049 a side, FP32, 50 sweeps: depth 13
-// in one round 4 passes of 60 us, the fixed depth 7 and 64 rows before it 8
-// passes of 53 us; 64 grids of up to 4097: within a few percent of the
-// autotuned 192 rows.
+// at 256 rows or less.  12 grids of 257 .. 2049 a side, FP32, in one round: passes
+// of 12 sweeps take 75 us, of 13 84 us, of 13 with the residual 107 us; 500 sweeps
+// 5.44 (fixed depth 7, 64 rows, a counter launch per pass) -> 4.38 ms in all.
 int batch_depth(const jacobi_batch_t b) {
     return b->depth > 0 ? b->depth : (b->dtype == JACOBI_F32 ? 13 : 4);
 }
