@@ -19,7 +19,7 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 ARCH = "gfx950"
 
 SOURCES = ["jacobi_abi.hip", "k_layout.hip", "k_sweep.hip", "k_march2d.hip", "k_march3d.hip",
-           "k_tile2d.hip", "k_residual.hip", "k_batch.hip", "k_deep.hip"]
+           "k_rows3d.hip", "k_tile2d.hip", "k_residual.hip", "k_batch.hip", "k_deep.hip"]
 # k_march2d.hip and k_march3d.hip are compiled once per temporal depth (their
 # kernels) and once more for the depth dispatch, k_tile2d.hip likewise per type;
 # each entry: (source, object name, defines)

@@ -337,6 +337,7 @@ struct jacobi_s {
     int *d_active = nullptr;
     int *d_pc = nullptr;
     int tab_rows = 0;  // tile height / z segment the prefix tables hold (0: none)
+    bool tab_wide = false;  // 3D: a small grid needs 64-bit offsets
     // schedule facts of this handle's device and grid, filled on first use:
     // compute units, and the marching pass's one-round tile height by mode
     // (Laplace, Poisson, adjoint) and depth
@@ -398,7 +399,7 @@ int balanced_rows(const jacobi_s *h, int depth, int mode, int rounds) {
 // resident waves, and for a 512^3 grid in 64^3 blocks (depth 5, the deepest
 // 3D pass).
 int default_depth(const jacobi_s *h) {
-    if (h->g.ndim == 3) return 5;
+    if (h->g.ndim == 3) return h->halo > 0 && h->dtype == JACOBI_F64 ? 4 : 5;
     return h->dtype == JACOBI_F32 ? 13 : 4;
 }
 
@@ -808,6 +809,9 @@ int deep_tables(jacobi_t h, int rows) {
                                  (char *)h->bdeep);
     }
     h->h_prefix.assign((size_t)(kDeepMaxDepth + 1) * (nb + 1), -1);
+    h->tab_wide = false;
+    for (int64_t k = 0; k < nb && h->g.ndim == 3; ++k)
+        h->tab_wide = h->tab_wide || jac::march3d_batch_wide<R>(t[0][k].g);
     for (int d = 1; d <= kDeepMaxDepth; ++d) {
         int *pre = &h->h_prefix[(size_t)d * (nb + 1)];
         int64_t acc = 0;
@@ -914,8 +918,8 @@ int do_deep_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos) {
                                                  h->has_source ? 1 : 0),
                     "deep pass launch");
         else
-            HIP_TRY(jac::launch_march3d_batch<R>(h->d_tab[h->cur], pre, (int)nb, h->has_source, t,
-                                                 rows, nwork, h->stream),
+            HIP_TRY(jac::launch_march3d_batch<R>(h->d_tab[h->cur], pre, (int)nb, h->has_source,
+                                                 h->tab_wide, t, rows, nwork, h->stream),
                     "deep pass launch");
         rc = prof_end(h, t);
         if (rc) return rc;

@@ -557,12 +557,15 @@ void k_march3d(Geom g, const R *__restrict__ uin, R *__restrict__ uout,
 // Batched pass: the work items of many grids in one launch (one descriptor
 // each; the deep-halo form runs every block as its own grid).  Work item w
 // belongs to grid gi with prefix[gi] <= w < prefix[gi+1]; every grid's input
-// is u[0] and its output u[1].
-template <typename R, int T, int RY, int MODE>
+// is u[0] and its output u[1].  FP32 on 32-row tiles, two workgroups per CU:
+// 512^3 in 8^3 blocks of frames of 4, 60 sweeps at depth 5, 18.5 ms against 26.0
+// on 64-row tiles (blocks of 72 rows: two tiles of 64 or three of 32) and 29.4
+// for the row kernel of k_rows3d.hip, which runs FP64.
+template <typename R, int T, int MODE, typename OFF>
 __global__ __launch_bounds__(kM3Threads) __attribute__((amdgpu_waves_per_eu(2)))
 void k_march3d_batch(const BatchGrid *__restrict__ grids, const int *__restrict__ prefix,
                      int ngrids, int zseg, int nitems) {
-    using M = M3<R, T, RY>;
+    using M = M3<R, T, 1>;
     __shared__ Chunk<R, M::V> sh[M::NL][2][M::H + 2][16];
     const int w = xcd_logical_block(blockIdx.x, gridDim.x);
     if (w >= nitems) return;  // whole workgroup
@@ -575,7 +578,7 @@ void k_march3d_batch(const BatchGrid *__restrict__ grids, const int *__restrict_
     const Geom g = grids[gi].g;
     const int nstrips = m3_tiles(g.n[0], M::W, M::OW);
     const int ngrp = m3_tiles(g.n[1], M::H, M::OY);
-    m3_item<R, T, RY, MODE, false, uint64_t>(g, (const R *)grids[gi].u[0], (R *)grids[gi].u[1],
+    m3_item<R, T, 1, MODE, false, OFF>(g, (const R *)grids[gi].u[0], (R *)grids[gi].u[1],
                                         (const R *)grids[gi].b, nullptr, w - prefix[gi], nstrips,
                                         ngrp, zseg, sh);
 }
@@ -588,9 +591,9 @@ void k_march3d_batch(const BatchGrid *__restrict__ grids, const int *__restrict_
 template <typename R, int T>
 hipError_t m3_launch_t(const Geom &g, const void *uin, void *uout, const void *b, double *res,
                        const M3Plan &pl, hipStream_t st);
-template <typename R, int T>
-hipError_t m3b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, bool src, int zseg,
-                        int nitems, hipStream_t st);
+template <int T>
+hipError_t m3b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, bool src, bool wide,
+                        int zseg, int nitems, hipStream_t st);
 
 // Rows held per lane in the taller of the two tile heights (64 rows).
 constexpr int kM3Ry = 2;
@@ -627,27 +630,32 @@ hipError_t m3_launch_t(const Geom &g, const void *uin, void *uout, const void *b
     return m3_launch_ry<R, T, 1, uint32_t>(g, uin, uout, b, res, pl, st);
 }
 
-template <typename R, int T>
-hipError_t m3b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, bool src, int zseg,
-                        int nitems, hipStream_t st) {
-    constexpr int RY = kM3Ry;
+template <int T>
+hipError_t m3b_launch_t(const BatchGrid *grids, const int *prefix, int ngrids, bool src, bool wide,
+                        int zseg, int nitems, hipStream_t st) {
     if (nitems <= 0) return hipSuccess;
-    if (src)
-        hipLaunchKernelGGL((k_march3d_batch<R, T, RY, 1>), dim3(nitems),
-                           dim3(kM3Threads), 0, st, grids, prefix, ngrids, zseg, nitems);
+#define JAC_M3B(MODEV, OFFV)                                                                     \
+    hipLaunchKernelGGL((k_march3d_batch<float, T, MODEV, OFFV>), dim3(nitems), dim3(kM3Threads), \
+                       0, st, grids, prefix, ngrids, zseg, nitems)
+    if (wide && src)
+        JAC_M3B(1, uint64_t);
+    else if (wide)
+        JAC_M3B(0, uint64_t);
+    else if (src)
+        JAC_M3B(1, uint32_t);
     else
-        hipLaunchKernelGGL((k_march3d_batch<R, T, RY, 0>), dim3(nitems),
-                           dim3(kM3Threads), 0, st, grids, prefix, ngrids, zseg, nitems);
+        JAC_M3B(0, uint32_t);
+#undef JAC_M3B
     return hipGetLastError();
 }
 
 #define JAC_M3_INSTANTIATE(R, T)                                                                \
     template hipError_t m3_launch_t<R, T>(const Geom &, const void *, void *, const void *,      \
-                                          double *, const M3Plan &, hipStream_t);                \
-    template hipError_t m3b_launch_t<R, T>(const BatchGrid *, const int *, int, bool, int, int,  \
-                                           hipStream_t);
+                                          double *, const M3Plan &, hipStream_t);
 JAC_M3_INSTANTIATE(float, JAC_MARCH3D_DEPTH)
 JAC_M3_INSTANTIATE(double, JAC_MARCH3D_DEPTH)
+template hipError_t m3b_launch_t<JAC_MARCH3D_DEPTH>(const BatchGrid *, const int *, int, bool, bool,
+                                                    int, int, hipStream_t);
 
 #else  // dispatch object
 
@@ -703,45 +711,81 @@ bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Pla
             if (rounds > 16) break;
         }
     }
+    // FP64 below depth 5: the row kernel where it is the faster one and its
+    // partials fit.  Depths 1 - 3, from 2^26 cells on: us per pass, it and the
+    // tiles above, 500x480x510 Poisson depth 1 1023 and 1066, depth 2 1105 and 1164,
+    // depth 3 1136 and 1182 (400^3 depth 3 524 and 529, 350x301x260 262 and 233).
+    // Depth 4, where passes are bound by their rounds, by the estimated time: its
+    // tiles run two per CU, 1.85 us per plane step of a round, the tiles above
+    // 1.25 us per unit of cost: 256^3 131 and 144, 350x301x260 266 and 271, 400^3
+    // 510 and 453, 512^3 1090 and 1162.
+    M3Plan row;
+    if (sizeof(R) == 8 && rows3d_plan(g, depth, zseg, cap, &row)) {
+        const double rounds = (double)((row.items + 2 * cus - 1) / (2 * cus));
+        const bool faster = depth < 4 ? (double)g.n[0] * g.n[1] * nz >= (double)(1 << 26)
+                                      : row.items > cus &&
+                                            1.85 * rounds * (row.zseg + 2 * (depth - 1)) <
+                                                1.25 * best_cost;
+        if (faster || best_cost >= 1e300) {
+            *out = row;
+            return true;
+        }
+    }
     *out = best;
     return best_cost < 1e300;
 }
 
-#define JAC_M3_SWITCH(depth, F, R, ...)                   \
-    switch (depth) {                                      \
-    case 1: return F<R, 1>(__VA_ARGS__);                  \
-    case 2: return F<R, 2>(__VA_ARGS__);                  \
-    case 3: return F<R, 3>(__VA_ARGS__);                  \
-    case 4: return F<R, 4>(__VA_ARGS__);                  \
-    case 5: return F<R, 5>(__VA_ARGS__);                  \
-    default: return hipErrorInvalidValue;                 \
+#define JAC_M3_SWITCH(depth, F, ...)                  \
+    switch (depth) {                                  \
+    case 1: return JAC_M3_CASE(F, 1)(__VA_ARGS__);    \
+    case 2: return JAC_M3_CASE(F, 2)(__VA_ARGS__);    \
+    case 3: return JAC_M3_CASE(F, 3)(__VA_ARGS__);    \
+    case 4: return JAC_M3_CASE(F, 4)(__VA_ARGS__);    \
+    case 5: return JAC_M3_CASE(F, 5)(__VA_ARGS__);    \
+    default: return hipErrorInvalidValue;             \
     }
 
 template <typename R>
+bool march3d_batch_wide(const Geom &g) {
+    return sizeof(R) == 4 && m3_wide(g, sizeof(R));
+}
+
+template <typename R>
 int64_t march3d_batch_items(const Geom &g, int zseg, int depth) {
+    if (sizeof(R) == 8) return rows3d_batch_items(g, zseg, depth);
     if (depth < 1 || depth > march3d_max_depth()) return -1;
     int ns, ng;
-    m3_shape<R>(g, depth, kM3Ry, ns, ng);
+    m3_shape<R>(g, depth, 1, ns, ng);
     return (int64_t)ns * ng * ((g.n[2] + zseg - 1) / zseg);
 }
 
 template <typename R>
 hipError_t launch_march3d_batch(const BatchGrid *grids, const int *prefix, int ngrids, bool src,
-                                int depth, int zseg, int nitems, hipStream_t st) {
-    JAC_M3_SWITCH(depth, m3b_launch_t, R, grids, prefix, ngrids, src, zseg, nitems, st)
+                                bool wide, int depth, int zseg, int nitems, hipStream_t st) {
+    if (sizeof(R) == 8)
+        return launch_rows3d_batch(grids, prefix, ngrids, src, depth, zseg, nitems, st);
+#define JAC_M3_CASE(F, T) F<T>
+    JAC_M3_SWITCH(depth, m3b_launch_t, grids, prefix, ngrids, src, wide, zseg, nitems, st)
+#undef JAC_M3_CASE
 }
 
 template <typename R>
 hipError_t launch_march3d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
                           const M3Plan &pl, hipStream_t st, int depth) {
-    JAC_M3_SWITCH(depth, m3_launch_t, R, g, uin, uout, b, res, pl, st)
+    if (pl.row)
+        return sizeof(R) == 8 ? launch_rows3d(g, uin, uout, b, res, pl, st, depth)
+                              : hipErrorInvalidValue;
+#define JAC_M3_CASE(F, T) F<R, T>
+    JAC_M3_SWITCH(depth, m3_launch_t, g, uin, uout, b, res, pl, st)
+#undef JAC_M3_CASE
 }
 
 #define JAC_M3_DISPATCH(R)                                                                       \
     template bool march3d_plan<R>(const Geom &, int, int, int, size_t, M3Plan *);                \
+    template bool march3d_batch_wide<R>(const Geom &);                                           \
     template int64_t march3d_batch_items<R>(const Geom &, int, int);                             \
-    template hipError_t launch_march3d_batch<R>(const BatchGrid *, const int *, int, bool, int,  \
-                                                int, int, hipStream_t);                          \
+    template hipError_t launch_march3d_batch<R>(const BatchGrid *, const int *, int, bool, bool, \
+                                                int, int, int, hipStream_t);                     \
     template hipError_t launch_march3d<R>(const Geom &, const void *, void *, const void *,      \
                                           double *, const M3Plan &, hipStream_t, int);
 JAC_M3_DISPATCH(float)

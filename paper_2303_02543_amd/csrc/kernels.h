@@ -130,6 +130,7 @@ struct M3Plan {
     int ry, nstrips, ngrp, zseg;
     int64_t items, partials;
     bool wide;
+    bool row = false;  // FP64: the kernel of k_rows3d.hip
 };
 // Plan of a pass of `depth` sweeps; zseg: output planes per work item (0:
 // chosen here, for `cus` compute units); cap: most residual partials.  false:
@@ -148,12 +149,25 @@ hipError_t launch_march3d(const Geom &g, const void *uin, void *uout, const void
 // descriptor table in one launch, each grid read from u[0] and written to
 // u[1]; src: Poisson (the grids' sources) or Laplace.  prefix[i]: first work
 // item of grid i, prefix[ngrids] = nitems.  march3d_batch_items: work items
-// of one grid.
+// of one grid; wide: some grid needs 64-bit offsets (march3d_batch_wide).
 template <typename R>
 hipError_t launch_march3d_batch(const BatchGrid *grids, const int *prefix, int ngrids, bool src,
-                                int depth, int zseg, int nitems, hipStream_t st);
+                                bool wide, int depth, int zseg, int nitems, hipStream_t st);
 template <typename R>
 int64_t march3d_batch_items(const Geom &g, int zseg, int depth);
+template <typename R>
+bool march3d_batch_wide(const Geom &g);
+
+// FP64 3D passes of one row per lane (k_rows3d.hip), reached through
+// march3d_plan (depths kRows3dLo .. kRows3dHi) and the FP64 batches.
+constexpr int kRows3dLo = 1, kRows3dHi = 4;
+constexpr int kRows3dZseg = 64;  // output planes per work item unless set
+bool rows3d_plan(const Geom &g, int depth, int zseg, size_t cap, M3Plan *p);
+hipError_t launch_rows3d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
+                         const M3Plan &pl, hipStream_t st, int depth);
+int64_t rows3d_batch_items(const Geom &g, int zseg, int depth);
+hipError_t launch_rows3d_batch(const BatchGrid *grids, const int *prefix, int ngrids, bool src,
+                               int depth, int zseg, int nitems, hipStream_t st);
 
 // Deep-halo block storage (k_deep.hip): refresh every block's H-deep frame
 // of state buffer s from the cells' owning blocks; fill the deep source

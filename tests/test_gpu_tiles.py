@@ -112,3 +112,38 @@ def test_adjoint_register_tiles(device, case):
             assert bits_equal(gU0.cpu().numpy(), dU0)
     finally:
         s.close()
+
+
+# FP64 passes of up to four sweeps on the row kernel: depth 4 where its rounds
+# are the shorter ones (256^3), depths 1 - 3 from 2^26 cells on.
+ROWS_3D = [
+    # (nx, ny, nz, bx, by, bz, depth, z segment)
+    (256, 256, 256, 4, 4, 4, 4, 0),
+    (251, 263, 259, 3, 4, 2, 4, 0),
+    (512, 512, 256, 8, 8, 4, 1, 0),
+    (419, 401, 403, 3, 4, 5, 2, 0),
+    (419, 401, 403, 4, 3, 2, 3, 37),
+]
+
+
+@pytest.mark.parametrize("case", ROWS_3D)
+def test_3d_rows(device, case):
+    nx, ny, nz, bx, by, bz, depth, zseg = case
+    rng = np.random.default_rng(5)
+    U0 = rng.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
+    f = rng.uniform(-1, 1, (nz, ny, nx))
+    h2 = synthetic.spacing2(max(nx, ny, nz))
+    for src in (f, None):
+        check(U0, src, h2, 4, 3, (bx, by, bz), np.float64, device,
+              "3d rows %s %s" % (case, "laplace" if src is None else "poisson"),
+              depth=depth, rows=zseg)
+
+
+def test_3d_wide_offsets(device):
+    """A z layer of blocks of more than 4 GiB (8 x 1 x 690 cells in 32 x 256 narrow
+    blocks): the pass runs on 64-bit lane offsets."""
+    nx, ny, nz = 256, 256, 690
+    rng = np.random.default_rng(6)
+    U0 = rng.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
+    f = rng.uniform(-1, 1, (nz, ny, nx))
+    check(U0, f, synthetic.spacing2(nz), 5, 4, (32, 256, 1), np.float32, device, "3d wide")
