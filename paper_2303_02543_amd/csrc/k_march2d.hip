@@ -838,8 +838,19 @@ int march2d_depths(int dtype, const int **list) {
     }
 
 template <typename R>
-int march2d_waves_per_cu(int depth, int mode) {
+static int m2_resident(int depth, int mode) {
     JAC_M2_SWITCH(depth, m2_waves_per_cu_t, R, 0, mode)
+}
+
+// From depth 6 on an FP32 source pass is cut for two waves per SIMD also where
+// three fit (depths 6 - 8): the shorter tiles for a third cost more warm-up
+// rows than it hides.  4096^2 Poisson, 27 - 28 rows (three) against 40 (two):
+// depth 6 48.6 and 44.0 us, depth 7 49.8 and 45.5, depth 8 52 and 48; 3000x3500, 18
+// against 27 rows: 36.1 and 31.1, 37.4 and 32.8, 39 and 35.
+template <typename R>
+int march2d_waves_per_cu(int depth, int mode) {
+    const int w = m2_resident<R>(depth, mode);
+    return sizeof(R) == 4 && depth >= 6 && mode == MODE_POISSON && w > 8 ? 8 : w;
 }
 
 template <typename R>
