@@ -319,6 +319,8 @@ struct jacobi_s {
     struct Rec {
         int depth;
         double updates, bytes;
+        float ms = -1.0f;  // elapsed time, once it was read (a second reading of
+                           // the same event pair can differ by a nanosecond)
     };
     std::vector<Rec> recs;  // one per recorded launch; events 2i, 2i+1
     // overlapped explicit-halo sweeps: the stream that sends faces, and
@@ -1474,9 +1476,13 @@ int jacobi_profile_read(jacobi_t h, int depth, double *ms, int64_t *launches, do
     int64_t cnt = 0;
     for (size_t i = 0; i < h->recs.size(); ++i) {
         if (depth && h->recs[i].depth != depth) continue;
-        float t = 0.0f;
-        HIP_TRY(hipEventElapsedTime(&t, h->ev_pool[2 * i], h->ev_pool[2 * i + 1]),
-                "event elapsed time");
+        float &t = h->recs[i].ms;
+        if (t < 0.0f) {
+            float e = 0.0f;
+            HIP_TRY(hipEventElapsedTime(&e, h->ev_pool[2 * i], h->ev_pool[2 * i + 1]),
+                    "event elapsed time");
+            t = e;
+        }
         total += t;
         up += h->recs[i].updates;
         by += h->recs[i].bytes;
