@@ -667,7 +667,7 @@ int do_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos = true) {
         return JACOBI_OK;
     }
     if ((h->flags & JACOBI_FLAG_OVERLAP) && explicit_halo) return do_sweep_overlap<R>(h, n, res_first);
-    if (explicit_halo && n > 0 && jac::sweep2d_sends(h->g, h->rows)) {
+    if (explicit_halo && n > 0 && jac::sweep2d_sends<R>(h->g, h->rows)) {
         // each sweep also writes its edge cells into the neighbours' halos of
         // the new state, and the first sums the residual of its input
         for (int64_t k = 0; k < n; ++k) {

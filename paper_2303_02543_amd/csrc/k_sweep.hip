@@ -501,7 +501,7 @@ hipError_t launch_sweep2d_tile_fused(const Geom &g, const void *uin, void *uout,
 template <typename R>
 hipError_t launch_sweep2d_tile_send(const Geom &g, const void *uin, void *uout, const void *b,
                                     double *res, int rg, hipStream_t st, int64_t *nwork, int nt) {
-    if (!sweep2d_sends(g, rg)) return hipErrorInvalidValue;
+    if (!sweep2d_sends<R>(g, rg)) return hipErrorInvalidValue;
     if (rg <= 0) rg = sweep_rows_default<R>();
     return launch_tile<R, false, true>(g, uin, uout, b, res, rg, 0, g.nblocks, st, nwork, nt);
 }

@@ -46,12 +46,24 @@ hipError_t launch_sweep2d_tile_fused(const Geom &g, const void *uin, void *uout,
                                      int nt = 0);
 // One 2D sweep of every block from its own storage (halos must be current)
 // that also writes the new state's halos: no exchange has to follow.  For rg
-// = 0 (the default) or >= 4 rows per tile (sweep2d_sends); res, nwork: as
+// = 0 (the default) or >= 4 rows per tile where sweep2d_sends; res, nwork: as
 // launch_sweep2d_tile_fused.
 template <typename R>
 hipError_t launch_sweep2d_tile_send(const Geom &g, const void *uin, void *uout, const void *b,
                                     double *res, int rg, hipStream_t st, int64_t *nwork, int nt);
-inline bool sweep2d_sends(const Geom &g, int rg) { return g.ndim == 2 && (rg <= 0 || rg >= 4); }
+// Not for blocks narrower than a wave's 64 lanes of 16 bytes, whose column cells
+// are then a large part of the stores, unless the launch is what a sweep costs
+// (up to 4096 work items).  us per sweep, send and exchange launch, FP32 Poisson:
+// 4096^2 in 64^2 / 128^2 blocks 115 / 55 and 92 / 51, 8192^2 in 256^2 blocks 168
+// and 183, 2048^2 in 128^2 blocks (4096 items) 17.4 and 18.4, 1000x777 in 9x7
+// blocks 6.9 and 11.0.
+template <typename R>
+bool sweep2d_sends(const Geom &g, int rg) {
+    if (g.ndim != 2 || (rg > 0 && rg < 4)) return false;
+    const int64_t w = 64 * (16 / (int64_t)sizeof(R)), tile = rg > 0 ? rg : 8;
+    const int64_t items = g.nblocks * ((g.e[1] + tile - 1) / tile) * ((g.e[0] + w - 1) / w);
+    return g.e[0] >= w || items <= 4096;
+}
 // Residual partials of one launch_sweep2d_tile_fused / _send launch.
 template <typename R>
 int64_t sweep_tile_partials(const Geom &g, int rg);

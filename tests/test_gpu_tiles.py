@@ -147,3 +147,17 @@ def test_3d_wide_offsets(device):
     U0 = rng.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
     f = rng.uniform(-1, 1, (nz, ny, nx))
     check(U0, f, synthetic.spacing2(nz), 5, 4, (32, 256, 1), np.float32, device, "3d wide")
+
+
+# The explicit-halo sweep sends its edge cells itself where blocks span a wave's
+# columns or the work items are few, else an exchange launch follows it.
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", [(1024, 1024, 64, 64), (1000, 1030, 63, 61), (513, 300, 2, 3)])
+def test_explicit_send_rule(device, dtype, case):
+    from paper_2303_02543_amd import JACOBI_FLAG_EXPLICIT_HALO
+    nx, ny, bx, by = case
+    U0 = RNG.uniform(0, 1, (ny + 2, nx + 2))
+    f = RNG.uniform(-1, 1, (ny, nx))
+    for src in (f, None):
+        check(U0, src, synthetic.spacing2(max(nx, ny)), 7, 3, (bx, by), dtype, device,
+              "explicit %s" % (case,), depth=1, flags=JACOBI_FLAG_EXPLICIT_HALO)
