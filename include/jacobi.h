@@ -68,8 +68,9 @@ enum jacobi_flags {
      * (the exchange fused into the sweep's loads) and may do several sweeps
      * per pass. */
     JACOBI_FLAG_EXPLICIT_HALO = 1,
-    /* Store pass outputs with the non-temporal hint (not kept in the caches).
-     * A pure performance choice; results are identical either way. */
+    /* Store 2D pass outputs with the non-temporal hint (not kept in the caches);
+     * 3D passes accept and ignore it.  A pure performance choice; results are
+     * identical either way. */
     JACOBI_FLAG_NT_STORES = 2,
     /* Accepted and ignored: the 2D passes now choose how far ahead they load
      * by their depth (two rows at depths up to 13, one row beyond and in the

@@ -66,8 +66,13 @@ def build(verbose: bool = False, jobs: int = 8, incremental: bool = False) -> st
     os.makedirs(BUILD_DIR, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=jobs) as ex:
         # the largest units first, so they do not end up last in the queue
-        units = sorted(UNITS, key=lambda u: -int(u[1].rsplit("_d", 1)[-1])
-                       if u[1].startswith("k_march2d_d") else 0)
+        # (a 3D depth compiles about as long as a 2D one eight levels deeper)
+        def weight(u):
+            for stem, extra in (("k_march2d_d", 0), ("k_march3d_d", 8)):
+                if u[1].startswith(stem):
+                    return -int(u[1][len(stem):]) - extra
+            return 0
+        units = sorted(UNITS, key=weight)
         objs = list(ex.map(lambda u: _compile(u, verbose, incremental), units))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp] + objs

@@ -13,13 +13,13 @@
 // s - 1 cells on every side.  Ring cells, and cells beyond the ring, copy
 // their input at every level.
 //
-// What bounds it: memory, with two loads of a lane's 16 bytes less per plane and
-// row than k_march3d.hip, which loads the rows above and below from the L1.
-// In FP64 a lane holds two columns only, so that weighs twice what it does in
-// FP32.  Against k_march3d.hip (the better of its tiles): 512^3 Poisson, per
-// pass, depth 2 1143 and 1214 us, depth 3 1147 and 1200, depth 4 1090 and 1162,
-// but depth 5 1448 and 1108; 350x301x260 depths 2 - 3 254 - 262 and 231 - 234.
-// Deep-halo form, 512^3 in 8^3 blocks, 60 sweeps at depth 4: 28.2 and 39.6 ms.
+// What bounds it: memory (512^3 moves 3.2 GB per pass at depths 2 - 4 in the time
+// of 2.8 TB/s, whatever the depth).  It is kept for what it measured against
+// k_march3d.hip, whose loads per row are as many; the cause was not isolated.
+// us per pass, it and the better of that kernel's tiles: 512^3 Poisson, depth 2
+// 1143 and 1214, depth 3 1147 and 1200, depth 4 1090 and 1162, but depth 5 1448 and
+// 1108; 350x301x260 depths 2 - 3 254 - 262 and 231 - 234.  Deep-halo form, 512^3 in
+// 8^3 blocks, 60 sweeps at depth 4: 28.2 and 39.6 ms.
 #include <hip/hip_runtime.h>
 
 #include "device_util.h"
