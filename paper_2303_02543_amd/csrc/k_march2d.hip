@@ -50,7 +50,12 @@ constexpr int kM2Waves = 4;
 // Pass modes: Laplace (no source), Poisson (source b), and the adjoint pass,
 // which sweeps a zero-ring Laplace state and adds w * (every level it holds)
 // into an FP64 accumulator.
-enum { MODE_LAPLACE = 0, MODE_POISSON = 1, MODE_ADJOINT = 2 };
+// Odd modes have a source.  MODE_POISSON_RES: a Poisson pass with the folded
+// residual, inside the kernels only.
+enum { MODE_LAPLACE = 0, MODE_POISSON = 1, MODE_ADJOINT = 2, MODE_POISSON_RES = 5 };
+constexpr int m2_mode(int mode, bool res) {
+    return res && mode == MODE_POISSON ? MODE_POISSON_RES : mode;
+}
 
 template <typename R, int T, int P, int MODE = MODE_LAPLACE>
 struct M2 {
@@ -62,7 +67,9 @@ struct M2 {
     static constexpr int L1 = (A0 + OW) / V;                  // one past the last output lane
     // rows loaded ahead (prefetch distance): row r + P is loaded at step r
     static_assert(P >= 1 && P <= 3, "prefetch distance 1..3");
-    // With a source, depths 12 and 13 unroll 15 steps, and the source ring
+    // With a source (without the folded residual, whose pass took 10 us longer that
+    // way, at 3000x2500 as at 6000x5000: 65 and 54 us, 130 and 117), depths 12 and 13
+    // unroll 15 steps, and the source ring
     // holds 15 rows (12 at depths 10 and 11, whose groups are 12 steps): every
     // LDS slot is then a compile-time offset from the lane's base, not an
     // address computed for every level (depth 13: 264 VALU instructions per
@@ -216,7 +223,7 @@ __device__ __forceinline__ void m2_load(const Geom &g, const R *__restrict__ uin
                                         const double *__restrict__ gacc, const MLane &L,
                                         MRegs<R, T, P, MODE> &m, Cur &lc) {
     constexpr int V = M2<R, T, P, MODE>::V;
-    constexpr bool SRC = MODE == MODE_POISSON;
+    constexpr bool SRC = (MODE & 1) != 0;
     using C = Chunk<R, V>;
     const int y = lc.y, ny = g.n[1];
     if constexpr (MODE == MODE_ADJOINT) {
@@ -276,9 +283,9 @@ __device__ __forceinline__ void m2_accumulate(const Geom &g, double *__restrict_
 // the row K steps back (K = S: row r - S, for level S of this step; K = 0:
 // row r, for level 1 of the next step).  Issued one level before its use, so
 // the LDS latency overlaps the arithmetic of the level in between.
-template <typename R, int T, int P, int J, int S, int K = S>
-__device__ __forceinline__ void m2_read_src(const MLane &L, MRegs<R, T, P, MODE_POISSON> &m, const int sr) {
-    using M = M2<R, T, P, MODE_POISSON>;
+template <typename R, int T, int P, int J, int S, int K = S, int MODE>
+__device__ __forceinline__ void m2_read_src(const MLane &L, MRegs<R, T, P, MODE> &m, const int sr) {
+    using M = M2<R, T, P, MODE>;
     const int slot = M::FIXED ? (J % M::RB - K + M::RB) % M::RB : sr - K < 0 ? sr - K + M::RB : sr - K;
     const Chunk<R, M::V> c = static_cast<const Chunk<R, M::V> *>(L.bs)[slot * 64];
 #pragma unroll
@@ -309,7 +316,7 @@ __device__ __forceinline__ void m2_level(const Geom &g, R *__restrict__ uout,
                                          const Cur &sc, const int sr) {
     using M = M2<R, T, P, MODE>;
     constexpr int V = M::V;
-    constexpr bool SRC = MODE == MODE_POISSON;
+    constexpr bool SRC = (MODE & 1) != 0;
     constexpr int LMAX = m2_lmax<T, M::U, G, J>();
     if constexpr (S <= LMAX) {
         const int y = r - S;
@@ -427,7 +434,7 @@ __device__ __forceinline__ void m2_steps(const Geom &g, const R *__restrict__ ui
         // the source row r, loaded P steps ago, moves to the LDS slot that
         // row r - RB held; levels read it from the next step on
         auto to_lds = [&]() {
-            if constexpr (MODE == MODE_POISSON) {
+            if constexpr ((MODE & 1) != 0) {
                 Chunk<R, V> c;
 #pragma unroll
                 for (int v = 0; v < V; ++v) c.v[v] = m.bq[J % M::BQ][v];
@@ -451,7 +458,7 @@ __device__ __forceinline__ void m2_steps(const Geom &g, const R *__restrict__ ui
         }
         // level 1's source row was read by the last level of the step before;
         // a step that computes no level reads the next step's row itself
-        if constexpr (MODE == MODE_POISSON && m2_lmax<T, M::U, G, J>() == 0 &&
+        if constexpr ((MODE & 1) != 0 && m2_lmax<T, M::U, G, J>() == 0 &&
                       m2_next_l1<T, M::U, G, J>())
             m2_read_src<R, T, P, J, 1, 0>(L, m, sr);
         m2_level<R, T, P, MODE, EK, RES, J, 1, G>(g, uout, gacc, L, m, r, sc, sr);
@@ -511,7 +518,7 @@ __device__ __forceinline__ void m2_body(const Geom &g, const R *__restrict__ uin
     }
     // without the warm-up groups the first step computes level 1 (its row
     // lies before the tile and is not an output)
-    if constexpr (MODE == MODE_POISSON && T == 1) m2_read_src<R, T, P, 0, 1>(L, m, sr);
+    if constexpr ((MODE & 1) != 0 && T == 1) m2_read_src<R, T, P, 0, 1>(L, m, sr);
     for (; base <= L.r1; base += S::U)
         m2_steps<R, T, P, MODE, EK, RES, 0>(g, uin, uout, bsrc, gacc, L, m, base, lc, sc, sr);
     if constexpr (RES) {
@@ -530,7 +537,7 @@ __device__ __forceinline__ void m2_run(const Geom &g, const R *__restrict__ uin,
                                        int wid, int rows, Chunk<R, M2<R, T, P, MODE>::V> *bs_wave,
                                        bool nt) {
     using S = M2<R, T, P, MODE>;
-    constexpr bool SRC = MODE == MODE_POISSON;
+    constexpr bool SRC = (MODE & 1) != 0;
     constexpr int V = S::V;
     const int lane = threadIdx.x & 63;
     const int nx = g.n[0], ny = g.n[1];
@@ -607,14 +614,15 @@ __global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2
                                                  double *__restrict__ res,
                                                  double *__restrict__ gacc, int rows, int nwork,
                                                  int nt) {
-    using S = M2<R, T, P, MODE>;
-    constexpr bool SRC = MODE == MODE_POISSON;
+    constexpr int KM = m2_mode(MODE, RES);
+    using S = M2<R, T, P, KM>;
+    constexpr bool SRC = (MODE & 1) != 0;
     // per wave: a ring of RB source rows, one 16-byte chunk per lane each
     __shared__ Chunk<R, S::V> bsm[SRC ? kM2Waves * S::RB * 64 : 1];
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
     const int wid = __builtin_amdgcn_readfirstlane(lb * (blockDim.x >> 6) + (threadIdx.x >> 6));
     if (wid >= nwork) return;
-    m2_run<R, T, P, MODE, RES>(g, uin, uout, bsrc, RES ? res + wid : nullptr, gacc, wid, rows,
+    m2_run<R, T, P, KM, RES>(g, uin, uout, bsrc, RES ? res + wid : nullptr, gacc, wid, rows,
                                &bsm[SRC ? (threadIdx.x >> 6) * S::RB * 64 : 0], nt != 0);
 }
 
@@ -633,8 +641,9 @@ __global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2
                                                        const int *__restrict__ pass_count, int pass,
                                                        double *__restrict__ res, int store,
                                                        int rows, int nwork) {
-    using S = M2<R, T, P, MODE>;
-    constexpr bool SRC = MODE == MODE_POISSON;
+    constexpr int KM = m2_mode(MODE, RES);
+    using S = M2<R, T, P, KM>;
+    constexpr bool SRC = (MODE & 1) != 0;
     __shared__ Chunk<R, S::V> bsm[SRC ? kM2Waves * S::RB * 64 : 1];
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
     const int wid = __builtin_amdgcn_readfirstlane(lb * (blockDim.x >> 6) + (threadIdx.x >> 6));
@@ -650,7 +659,7 @@ __global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2
     const int par = (*pass_count + pass) & 1;
     const R *uin = (const R *)grids[gi].u[par];
     R *uout = store ? (R *)grids[gi].u[par ^ 1] : nullptr;
-    m2_run<R, T, P, MODE, RES>(g, uin, uout, SRC ? (const R *)grids[gi].b : nullptr,
+    m2_run<R, T, P, KM, RES>(g, uin, uout, SRC ? (const R *)grids[gi].b : nullptr,
                                RES ? res + wid : nullptr, nullptr, wid - prefix[gi], rows,
                                &bsm[SRC ? (threadIdx.x >> 6) * S::RB * 64 : 0], false);
 }
