@@ -259,6 +259,12 @@ int jacobi_solve_noalloc(int ndim, const int64_t *grid, const int64_t *blocks, i
  * flags: jacobi_flags.  JACOBI_E_INVAL for values out of range.
  * Bit-neutral: every choice gives the same results. */
 int jacobi_set_tuning(jacobi_t h, int t_depth, int rows, int flags);
+
+/* Not in the paper (performance only).  The handle's schedule, as values that
+ * jacobi_set_tuning takes to give it again (on a handle of the same shape and
+ * source).  0 stands for what the library chooses pass by pass: rows of the 3D
+ * pass and of the block-local sweep, and rows and t_depth where the 2D passes
+ * run on tiles held in registers; elsewhere the default depth and height. */
 int jacobi_get_tuning(jacobi_t h, int *t_depth, int *rows, int *flags);
 
 /* Not in the paper.  Largest temporal depth this build supports for the

@@ -499,6 +499,19 @@ Pass2d plan2d(const jacobi_s *h, int64_t left, int depth, bool fixed_depth, bool
     return p;
 }
 
+// Whether the handle's schedule has passes on register tiles, for any number of
+// sweeps (plan2d looks at the sweeps that are left; runs of up to four of its
+// longest passes stand for all).
+template <typename R>
+bool tiles_run(const jacobi_s *h) {
+    if (h->g.ndim != 2 || h->halo > 0 || h->rows > 0) return false;
+    const int depth = h->depth > 0 ? h->depth : default_depth(h);
+    for (int64_t left = 2; left <= 4 * jac::kTileMaxSweeps; ++left)
+        if (plan2d<R>(h, left, depth, h->depth > 0, false, h->has_source ? 1 : 0, false).tile)
+            return true;
+    return false;
+}
+
 // Event pair around one sweep-kernel launch when profiling is on.
 int prof_begin(jacobi_t h) {
     if (!h->profiling) return JACOBI_OK;
@@ -1432,17 +1445,20 @@ int jacobi_get_tuning(jacobi_t h, int *t_depth, int *rows, int *flags) {
     if (rc) return rc;
     if (!t_depth || !rows || !flags) return fail(JACOBI_E_INVAL, "output pointers must not be NULL");
     *t_depth = h->depth > 0 ? h->depth : default_depth(h);
-    if (h->rows > 0)
-        *rows = h->rows;
-    else if (h->halo > 0 && h->g.ndim == 3)
-        *rows = h->g.e[2] + 2 * (h->halo - 1);  // deep-halo passes: one z segment per block
-    else if (h->g.ndim == 3) {
-        jac::M3Plan pl;
-        rc = h->dtype == JACOBI_F32 ? plan3d<float>(h, *t_depth, &pl) : plan3d<double>(h, *t_depth, &pl);
-        if (rc) return rc;
-        *rows = pl.zseg;
-    } else
-        *rows = default_rows(h);
+    *rows = h->rows;
+    // what the library chooses per pass is reported as 0, which set_tuning
+    // takes back: a height or segment of one pass would pin all of them
+    if (h->rows == 0 && h->g.ndim == 3 && h->halo > 0) {
+        // deep-halo passes: one z segment per block
+        const int z = h->g.e[2] + 2 * (h->halo - 1);
+        *rows = z >= kMinRows ? z : 0;
+    } else if (h->rows == 0 && h->g.ndim == 2 && !(h->flags & JACOBI_FLAG_EXPLICIT_HALO) &&
+               march_fits(h->g, h->dtype)) {
+        if (!(h->dtype == JACOBI_F32 ? tiles_run<float>(h) : tiles_run<double>(h)))
+            *rows = default_rows(h);
+        else if (h->depth == 0)
+            *t_depth = 0;
+    }
     *flags = h->flags;
     return JACOBI_OK;
 }

@@ -98,3 +98,33 @@ def test_profile_records_count_passes(device):
     finally:
         s.close()
     assert bits_equal(got, oracle.sweep(U0, oracle.scale_source(f, h2, np.float32), K + 5))
+
+
+@pytest.mark.parametrize("case", [((513, 260), (3, 5), "float32"), ((300, 201), (2, 2), "float64"),
+                                  ((2500, 1701), (5, 4), "float64"), ((40, 36, 30), (2, 2, 2), "float32"),
+                                  ((96, 96, 96), (2, 2, 2), "float64")])
+def test_tuning_read_back_gives_the_schedule_again(device, case):
+    """What get_tuning reports is accepted by set_tuning and leaves the passes
+    as they were: the launches of a run, counted per depth, stay the same."""
+    import torch
+    import paper_2303_02543_amd as jb
+    grid, blocks, name = case
+    s = jb.Solver(grid, blocks, getattr(torch, name), device=device)
+    try:
+        s.set_state(torch.zeros(s.state_shape, dtype=s.torch_dtype, device=device))
+        seen = []
+        for _ in range(2):
+            counts = []
+            for K in (48, 7):
+                s.profile(True)
+                s.sweep(K)
+                counts.append([s.profile_read(d)["launches"] for d in range(1, 17)])
+                s.profile(False)
+            seen.append(counts)
+            t = s.get_tuning()
+            say("read back", case, t)
+            s.set_tuning(*t)
+            assert s.get_tuning() == t
+        assert seen[0] == seen[1]
+    finally:
+        s.close()
