@@ -439,7 +439,8 @@ int jacobi_profile_read(jacobi_t h, int depth, double *ms, int64_t *launches,
  * (JACOBI_E_STATE until jacobi_set_state).  Synchronises the stream.
  * If the environment variable JACOBI_TUNE_CACHE names a file, results are
  * looked up in and appended to it (one line per problem shape).
- * Outputs (may be NULL): the chosen depth, rows and flags. */
+ * Outputs (may be NULL): the chosen depth, rows and flags, as jacobi_set_tuning
+ * takes them (0: left to the library). */
 int jacobi_autotune(jacobi_t h, int64_t n_sweeps, int with_source, int *t_depth, int *rows,
                     int *flags);
 

@@ -1515,7 +1515,9 @@ namespace {
 
 std::string tune_key(const jacobi_s *h, int64_t n, int src) {
     char buf[256];
-    snprintf(buf, sizeof buf, "jacobi-v1 nd=%d n=%d,%d,%d b=%d,%d,%d dt=%d src=%d sweeps=%lld",
+    // v2: schedules timed on the present kernels (a line of another version was
+    // the fastest of other ones, and is left alone)
+    snprintf(buf, sizeof buf, "jacobi-v2 nd=%d n=%d,%d,%d b=%d,%d,%d dt=%d src=%d sweeps=%lld",
              h->g.ndim, h->g.n[0], h->g.n[1], h->g.n[2], h->g.nb[0], h->g.nb[1], h->g.nb[2],
              h->dtype, src, (long long)n);
     return buf;
@@ -1568,15 +1570,18 @@ int jacobi_autotune(jacobi_t h, int64_t n_sweeps, int with_source, int *t_depth,
             for (int rg : {2, 4, 8, 16}) cands.push_back({1, rg, JACOBI_FLAG_EXPLICIT_HALO});
         cands.push_back({1, 0, JACOBI_FLAG_EXPLICIT_HALO | JACOBI_FLAG_OVERLAP});
         if (h->g.ndim == 3) {
-            static const int kZseg[] = {16, 32, 64, 128};
+            // segment 0: the plan's own, by pass
+            static const int kZseg[] = {0, 16, 32, 64, 128};
             for (int d = 1; d <= jac::march3d_max_depth(); ++d)
-                for (int z : kZseg)
-                    for (int f : {0, (int)JACOBI_FLAG_NT_STORES}) cands.push_back({d, z, f});
+                for (int z : kZseg) cands.push_back({d, z, 0});
         }
         if (h->g.ndim == 2) {
             const int *list;
             const int nd = jac::march2d_depths(h->dtype, &list);
             static const int kRows[] = {16, 32, 64, 96, 128, 192, 256};
+            // the default's passes on tiles held in registers are longer than
+            // any depth that can be set in FP64 (FP32 depths reach as far)
+            if (list[nd - 1] < jac::kTileMaxSweeps) cands.push_back({0, 0, 0});
             for (int i = 0; i < nd; ++i) {
                 // rows 0: tiles held in registers where the library expects
                 // them to be faster

@@ -128,3 +128,50 @@ def test_tuning_read_back_gives_the_schedule_again(device, case):
         assert seen[0] == seen[1]
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("case", [((700, 601), (3, 2), "float64"), ((1200, 1000), (4, 4), "float32"),
+                                  ((96, 96, 96), (2, 2, 2), "float32")])
+def test_autotune_is_not_slower_than_the_default(device, monkeypatch, case):
+    """The default schedule is among those the autotuner times, so its pick
+    takes at most the default's kernel time (a sixth is left for noise)."""
+    import torch
+    import paper_2303_02543_amd as jb
+    monkeypatch.delenv("JACOBI_TUNE_CACHE", raising=False)
+    grid, blocks, name = case
+    s = jb.Solver(grid, blocks, getattr(torch, name), device=device)
+
+    def kernel_ms():
+        s.set_state(torch.zeros(s.state_shape, dtype=s.torch_dtype, device=device))
+        out = []
+        for _ in range(7):
+            s.profile(True)
+            s.sweep(48)
+            out.append(s.profile_read(0)["ms"])
+            s.profile(False)
+        return min(out)
+
+    try:
+        default = kernel_ms()
+        tuned = s.autotune(48, with_source=False)
+        ms = kernel_ms()
+        say("autotuned", case, tuned, "%.4f ms, default %.4f" % (ms, default))
+        assert ms <= default * 7 / 6
+    finally:
+        s.close()
+
+
+def test_tune_cache_lines_of_other_versions_are_not_taken(device, tmp_path, monkeypatch):
+    import torch
+    import paper_2303_02543_amd as jb
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("JACOBI_TUNE_CACHE", str(cache))
+    old = "jacobi-v1 nd=2 n=300,200,1 b=3,2,1 dt=0 src=0 sweeps=20 -> 1 0 1"
+    cache.write_text(old + "\n")
+    s = jb.Solver((300, 200), (3, 2), torch.float32, device=device)
+    try:
+        assert s.autotune(20, with_source=False) != (1, 0, 1)
+        lines = cache.read_text().splitlines()
+        assert lines[0] == old and len(lines) == 2
+    finally:
+        s.close()
