@@ -328,7 +328,8 @@ int jacobi_batch_set_grid(jacobi_batch_t b, int i, const void *u, const void *f,
 int jacobi_batch_get_grid(jacobi_batch_t b, int i, void *u);
 
 /* Not in the paper (performance only).  Schedule: temporal depth (0 = default), tile rows (0 = default, else >= 8),
- * use_graph (replay captured check intervals). */
+ * use_graph (replay captured check intervals).  get_tuning reports rows 0 where
+ * the default heights differ from pass to pass. */
 int jacobi_batch_set_tuning(jacobi_batch_t b, int t_depth, int rows, int use_graph);
 int jacobi_batch_get_tuning(jacobi_batch_t b, int *t_depth, int *rows, int *use_graph);
 

@@ -1745,8 +1745,11 @@ struct jacobi_batch_s {
     std::vector<int> h_final_buf;
     std::vector<char> grid_set;
     int depth, rows, use_graph;
-    int table_rows;  // tile height the uploaded tables were built for (0: none)
-    int default_rows[kMaxDepth + 1] = {};  // batch_rows of each depth (0: not computed)
+    int table_key;   // batch_key the uploaded tables were built for (0: none)
+    // batch_balanced of each depth (0: not computed), and whether its tiles
+    // take one round of resident waves
+    int balanced[kMaxDepth + 1] = {};
+    bool one_round[kMaxDepth + 1] = {};
     int *h_active;   // pinned host copy of the activity flags
     // captured interval
     hipGraphExec_t graph;
@@ -1773,22 +1776,26 @@ void batch_drop_graph(jacobi_batch_t b) {
 // at 256 rows or less.  12 grids of 257 .. 2049 a side, FP32, in one round: passes
 // of 12 sweeps take 75 us, of 13 84 us, of 13 with the residual 107 us; 500 sweeps
 // 5.44 (fixed depth 7, 64 rows, a counter launch per pass) -> 4.38 ms in all.
+// FP64 is cut for two waves per SIMD also where more fit: the shorter tiles for
+// the others cost more warm-up rows than they hide.  200 sweeps, a residual every
+// 50: 6 grids of 600 .. 1500 a side 17 rows 2.17 ms, 33 rows 1.86 (64 rows 2.15 with
+// the kernel of that time); 40 of 300 12 rows 1.46, 27 rows 1.27; 2049^2 10 rows 1.64,
+// 20 rows 1.36.
 int batch_depth(const jacobi_batch_t b) {
     return b->depth > 0 ? b->depth : (b->dtype == JACOBI_F32 ? 13 : 4);
 }
-int batch_rows(const jacobi_batch_t b) {
-    if (b->rows > 0) return b->rows;
-    const int depth = pick_depth(b->dtype, batch_depth(b));
-    int &cached = b->default_rows[depth];
+int batch_balanced(const jacobi_batch_t b, int depth) {
+    int &cached = b->balanced[depth];
     if (cached > 0) return cached;
     int cus = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
         return 64;
-    const int wpc = b->dtype == JACOBI_F32 ? jac::march2d_waves_per_cu<float>(depth, 1)
-                                           : jac::march2d_waves_per_cu<double>(depth, 1);
+    int wpc = b->dtype == JACOBI_F32 ? jac::march2d_waves_per_cu<float>(depth, 1)
+                                     : jac::march2d_waves_per_cu<double>(depth, 1);
     if (wpc <= 0) return 64;
+    if (b->dtype == JACOBI_F64 && wpc > 8) wpc = 8;
     auto tiles = [&](int rows) {
         int64_t n = 0;
         for (const Geom &g : b->bl.geoms)
@@ -1803,19 +1810,32 @@ int batch_rows(const jacobi_batch_t b) {
         const int mid = lo + (hi - lo) / 2;
         if (tiles(mid) <= rounds * slots) hi = mid; else lo = mid + 1;
     }
+    b->one_round[depth] = rounds <= 1;
     return cached = lo;
 }
+// Tile height of a pass of t sweeps.  Where the tiles take several rounds,
+// passes of up to 7 sweeps keep 64 rows: 64 grids of 257 .. 4100 a side, FP32,
+// passes of 1 sweep 1112 us and 1140 at the balanced 244 rows, of 3 1179 and 1199,
+// but of 13 1365 and 1304.
+int batch_rows(const jacobi_batch_t b, int t) {
+    if (b->rows > 0) return b->rows;
+    const int depth = pick_depth(b->dtype, batch_depth(b));
+    const int rows = batch_balanced(b, depth);
+    return t <= 7 && rows > 64 && !b->one_round[depth] ? 64 : rows;
+}
+// What the tile heights depend on.
+int batch_key(const jacobi_batch_t b) { return b->rows > 0 ? b->rows : -batch_depth(b); }
 
-// Work tables for the current tile height: per grid its tiles per strip, and
-// per depth the prefix sums of work items.  Uploaded when the height changes.
+// Work tables for the current tile heights: per grid its tiles per strip, and
+// per depth the prefix sums of work items.  Uploaded when the heights change.
 template <typename R>
 int batch_tables(jacobi_batch_t b) {
-    const int rows = batch_rows(b);
-    if (b->table_rows == rows) return JACOBI_OK;
+    if (b->table_key == batch_key(b)) return JACOBI_OK;
     const int n = b->count;
     b->h_prefix.assign((size_t)(kMaxDepth + 1) * (n + 1), 0);
     for (int d = 1; d <= kMaxDepth; ++d) {
         int *pre = &b->h_prefix[(size_t)d * (n + 1)];
+        const int rows = batch_rows(b, d);
         int64_t acc = 0;
         for (int i = 0; i < n; ++i) {
             pre[i] = (int)acc;
@@ -1836,7 +1856,7 @@ int batch_tables(jacobi_batch_t b) {
                            hipMemcpyHostToDevice, b->stream),
             "batch table upload");
     HIP_TRY(hipStreamSynchronize(b->stream), "stream synchronize");
-    b->table_rows = rows;
+    b->table_key = batch_key(b);
     batch_drop_graph(b);
     return JACOBI_OK;
 }
@@ -1861,7 +1881,6 @@ std::vector<int> batch_passes(int dtype, int depth, int64_t n) {
 template <typename R>
 int batch_interval(jacobi_batch_t b, int64_t n, double tol, bool check = true) {
     const std::vector<int> ds = batch_passes(b->dtype, batch_depth(b), n);
-    const int rows = batch_rows(b);
     const int cnt = b->count;
     if (n == 0) return JACOBI_OK;
     for (size_t p = 0; p < ds.size(); ++p) {
@@ -1870,7 +1889,7 @@ int batch_interval(jacobi_batch_t b, int64_t n, double tol, bool check = true) {
         const int nwork = b->h_prefix[(size_t)t * (cnt + 1) + cnt];
         HIP_TRY(jac::launch_march2d_batch<R>(b->d_grids, pre, cnt, b->st.active, b->st.pass_count,
                                              (int)p, (p == 0 && check) ? b->partials : nullptr, true, t,
-                                             rows, nwork, b->stream),
+                                             batch_rows(b, t), nwork, b->stream),
                 "batch pass launch");
         if (p == 0 && check)
             HIP_TRY(jac::launch_batch_check(pre, b->partials, cnt, b->st, tol, false, b->stream),
@@ -1888,7 +1907,7 @@ int batch_final(jacobi_batch_t b, double tol) {
     const int *pre = b->d_prefix + (size_t)1 * (cnt + 1);
     const int nwork = b->h_prefix[(size_t)1 * (cnt + 1) + cnt];
     HIP_TRY(jac::launch_march2d_batch<R>(b->d_grids, pre, cnt, b->st.active, b->st.pass_count, 0,
-                                         b->partials, false, 1, batch_rows(b), nwork, b->stream),
+                                         b->partials, false, 1, batch_rows(b, 1), nwork, b->stream),
             "batch residual launch");
     HIP_TRY(jac::launch_batch_check(pre, b->partials, cnt, b->st, tol, true, b->stream),
             "batch check launch");
@@ -1898,7 +1917,7 @@ int batch_final(jacobi_batch_t b, double tol) {
 template <typename R>
 int batch_capture(jacobi_batch_t b, int64_t n, double tol) {
     if (b->graph && b->graph_R == n && b->graph_depth == batch_depth(b) &&
-        b->graph_rows == batch_rows(b) && b->graph_tol == tol)
+        b->graph_rows == batch_key(b) && b->graph_tol == tol)
         return JACOBI_OK;
     batch_drop_graph(b);
     HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal), "begin capture");
@@ -1917,7 +1936,7 @@ int batch_capture(jacobi_batch_t b, int64_t n, double tol) {
     b->graph = exec;
     b->graph_R = n;
     b->graph_depth = batch_depth(b);
-    b->graph_rows = batch_rows(b);
+    b->graph_rows = batch_key(b);
     b->graph_tol = tol;
     return JACOBI_OK;
 }
@@ -2043,7 +2062,7 @@ int jacobi_batch_create(int count, const int64_t *grids, int64_t block, int dtyp
     b->depth = 0;
     b->rows = 0;
     b->use_graph = 1;
-    b->table_rows = 0;
+    b->table_key = 0;
     b->graph = nullptr;
     b->graph_R = 0;
     if (hipHostMalloc((void **)&b->h_active, sizeof(int) * count, hipHostMallocDefault) != hipSuccess) {
@@ -2118,7 +2137,8 @@ int jacobi_batch_get_tuning(jacobi_batch_t b, int *t_depth, int *rows, int *use_
     int rc = batch_check(b);
     if (rc) return rc;
     if (t_depth) *t_depth = batch_depth(b);
-    if (rows) *rows = batch_rows(b);
+    // 0: tile heights that differ from pass to pass, chosen by the library
+    if (rows) *rows = batch_rows(b, 1) == batch_rows(b, kMaxDepth) ? batch_rows(b, 1) : 0;
     if (use_graph) *use_graph = b->use_graph;
     return JACOBI_OK;
 }

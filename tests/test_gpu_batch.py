@@ -159,3 +159,43 @@ def test_autotune_is_bit_neutral_and_batch_equals_single(device):
         finally:
             s.close()
         assert bits_equal(finals[i], single), "grid %d batched != single" % i
+
+
+def test_default_tile_heights(device):
+    """FP64 tiles are cut for two waves per SIMD (40 grids of 300 a side: 27
+    rows, 12 for all that fit); tiles that take several rounds
+    of waves have heights of their own in passes of up to 7 sweeps (reported
+    as 0), and what is read back is taken back."""
+    import torch
+    import paper_2303_02543_amd as jb
+    B, _ = make_batch([(300, 300)] * 40, np.float64, device)
+    try:
+        assert B.get_tuning()[1] >= 20
+    finally:
+        B.close()
+    n, nx, ny = 2500, 20, 601
+    picks = (0, 7, 1249, 2499)
+    rng = np.random.default_rng(9)
+    U0 = [rng.uniform(0, 1, (ny + 2, nx + 2)).astype(np.float32) for _ in picks]
+    f = [rng.uniform(-1, 1, (ny, nx)).astype(np.float32) for _ in picks]
+    B = jb.Batch([(nx, ny)] * n, torch.float32, device=device)
+    Ud = [torch.from_numpy(x).to(device) for x in U0]
+    fd = [torch.from_numpy(x).to(device) for x in f]
+    h2 = synthetic.spacing2(ny)
+    try:
+        t = B.get_tuning()
+        say("several rounds", t)
+        assert t[1] == 0
+        B.set_tuning(*t)
+        assert B.get_tuning() == t
+        for R, K in ((3, 7), (13, 33)):
+            say("several rounds", R, K)
+            for i in range(n):
+                k = picks.index(i) if i in picks else i % len(picks)
+                B.set_grid(i, Ud[k], fd[k], h2)
+            B.solve(0.0, K, R)
+            for k, i in enumerate(picks):
+                want = oracle.sweep(U0[k], oracle.scale_source(f[k], h2, np.float32), K)
+                assert bits_equal(B.get_grid(i).cpu().numpy(), want), (R, K, i)
+    finally:
+        B.close()
