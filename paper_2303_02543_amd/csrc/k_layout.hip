@@ -218,58 +218,92 @@ __device__ __forceinline__ bool face_cell(const Geom &g, const BlockPos &p, int6
     return true;
 }
 
-// One face of block blk.  SEND: the block's edge cells go into the halo of its
-// face neighbour; otherwise the block's halo takes the neighbour's edge
-// cells.  kFaceCells cells per thread: one per thread was bound by workgroup
-// dispatch at 512^3 in 64^3 blocks (12.6 M halo cells).
-constexpr int kFaceCells = 4;
-template <typename R, int AXIS, bool SEND, bool PACK>
+// Cell t of the faces of block blk along AXIS.  SEND: the block's edge cell goes
+// into the halo of its face neighbour; otherwise the block's halo takes the
+// neighbour's edge cell.  SIDES = 2: of both faces (low, high), else of face
+// `side0`.
+template <typename R, int AXIS, bool SEND, int SIDES>
 __device__ __forceinline__ void face_copy(const Geom &g, R *__restrict__ s, int64_t blk,
-                                          const BlockPos &p, int side, int t0) {
-    constexpr int kCells = PACK ? 1 : kFaceCells;
-    if (side == 0 ? p.b[AXIS] == 0 : p.b[AXIS] == g.nb[AXIS] - 1) return;  // the domain's ring
+                                          const BlockPos &p, int side0, int t) {
     const int64_t step = AXIS == 0 ? 1 : AXIS == 1 ? g.nb[0] : (int64_t)g.nb[0] * g.nb[1];
-    const int64_t nbr = side == 0 ? blk - step : blk + step;
-    // a low neighbour is a full block
-    const int at = SEND ? (side == 0 ? 0 : p.ext[AXIS] - 1) : (side == 0 ? -1 : p.ext[AXIS]);
-    const int nat = SEND ? (side == 0 ? g.e[AXIS] : -1) : (side == 0 ? g.e[AXIS] - 1 : 0);
-    int64_t here[kCells], there[kCells];
-    bool in[kCells];
-    R v[kCells];
+    int64_t to[SIDES];
+    bool in[SIDES];
+    R v[SIDES];
 #pragma unroll
-    for (int k = 0; k < kCells; ++k) {
-        const int t = (blockIdx.x * kCells + k) * 256 + t0;
-        in[k] = face_cell<AXIS>(g, p, blk, nbr, t, at, nat, &here[k], &there[k]);
-        if (in[k]) v[k] = s[SEND ? here[k] : there[k]];
+    for (int q = 0; q < SIDES; ++q) {
+        const int side = SIDES == 2 ? q : side0;
+        const bool ring = side == 0 ? p.b[AXIS] == 0 : p.b[AXIS] == g.nb[AXIS] - 1;
+        const int64_t nbr = side == 0 ? blk - step : blk + step;
+        // a low neighbour is a full block
+        const int at = SEND ? (side == 0 ? 0 : p.ext[AXIS] - 1) : (side == 0 ? -1 : p.ext[AXIS]);
+        const int nat = SEND ? (side == 0 ? g.e[AXIS] : -1) : (side == 0 ? g.e[AXIS] - 1 : 0);
+        int64_t here = 0, there = 0;
+        // a face on the domain's side keeps the Dirichlet ring
+        in[q] = !ring && face_cell<AXIS>(g, p, blk, nbr, t, at, nat, &here, &there);
+        to[q] = SEND ? there : here;
+        if (in[q]) v[q] = s[SEND ? here : there];
     }
 #pragma unroll
-    for (int k = 0; k < kCells; ++k)
-        if (in[k]) s[SEND ? there[k] : here[k]] = v[k];
+    for (int q = 0; q < SIDES; ++q)
+        if (in[q]) s[to[q]] = v[q];
 }
 
 // Halo exchange (SEND = false) of every block, or the face sends of the
 // blocks b0 .. b1-1: sending the faces of every block fills the same halo
-// cells, with the same values, as the exchange.  Grid: x over a face's cells,
-// y = 2 * axis + side (side 0 = low, 1 = high), z over blocks.  Faces on the
-// domain boundary keep the Dirichlet values.
-// PACK: faces of at most 128 cells, 256 / lanes blocks per workgroup and one cell
-// per thread (4096^2 FP32 Poisson in 32^2 blocks, a sweep and its exchange: 237 us
-// with a workgroup per face, 192 packed).
-template <typename R, bool SEND, bool PACK>
+// cells, with the same values, as the exchange.  Faces on the domain boundary
+// keep the Dirichlet values.
+//
+// The west and east halo cells of a row lie in one 128-byte line (the end of
+// one stored row and the start of the next), so a workgroup fills both x-faces of
+// a block: from two, mostly on different XCDs, every line was written twice.
+//
+// PACK: faces of at most 128 cells, `lanes` threads each, consecutive groups of
+// threads on consecutive faces of a block (exchange alone, a workgroup per face
+// and now: 4096^2 FP32 in 32^2 blocks 46.4 -> 31.2 us, 16^2 94 -> 53, 64^2 24.6 -> 16.7;
+// one thread after the other over all faces, with a division each: 32.3, 54, 18.2).
+// Otherwise a thread does one cell of a face, or of both faces of an axis
+// (SIDES), and the grid runs over a face's cells, the axes and the blocks.  In 2D
+// the axes come last: faces of one axis may fill few of the workgroups that the
+// longest face needs, and workgroups of one axis, dealt out in between, then
+// sit on the same XCDs (2048^2 FP32 in 32 x 1024 blocks 11.0 us, axes last 6.6).
+// In 3D the axes of a block come one after the other (512^3 in 64^3 blocks 236 us,
+// axes last 256).  The faces of a 3D block are sent one by one: they go to
+// different blocks, and an overlapped sweep of 256^3 FP32 in 32^3 blocks takes 131 us,
+// 134 with both from one thread; 2D sends of 8 columns by 4096 rows 765 and 812
+// the other way round.
+template <typename R, bool SEND, bool PACK, int SIDES>
 __global__ __launch_bounds__(256) void k_halo(Geom g, R *__restrict__ s, int64_t b0, int64_t b1,
-                                              int lanes) {
-    const int face = blockIdx.y, axis = face >> 1, side = face & 1;
-    const int sub = PACK ? (int)threadIdx.x / lanes : 0, per = PACK ? 256 / lanes : 1;
-    const int t0 = PACK ? (int)threadIdx.x % lanes : (int)threadIdx.x;
-    for (int64_t blk = b0 + (int64_t)blockIdx.z * per + sub; blk < b1;
-         blk += (int64_t)gridDim.z * per) {
-        const BlockPos p = block_pos(g, blk);
-        if (axis == 0)
-            face_copy<R, 0, SEND, PACK>(g, s, blk, p, side, t0);
-        else if (axis == 1)
-            face_copy<R, 1, SEND, PACK>(g, s, blk, p, side, t0);
-        else
-            face_copy<R, 2, SEND, PACK>(g, s, blk, p, side, t0);
+                                              int lanes, int64_t stride) {
+    if constexpr (PACK) {
+        const int sub = (int)threadIdx.x / lanes, per = 256 / lanes, t0 = (int)threadIdx.x % lanes;
+        // launched with at most 2^30 groups of threads
+        const unsigned nf = g.ndim == 3 ? 6 : 4;
+        const unsigned i0 = blockIdx.x * per + sub;
+        const unsigned rel0 = g.ndim == 3 ? i0 / 6u : i0 / 4u, face = i0 - rel0 * nf;
+        const unsigned axis = face >> 1, side = face & 1;
+        for (int64_t blk = b0 + rel0; blk < b1; blk += stride) {
+            const BlockPos p = block_pos(g, blk);
+            if (axis == 0)
+                face_copy<R, 0, SEND, SIDES>(g, s, blk, p, side, t0);
+            else if (axis == 1)
+                face_copy<R, 1, SEND, SIDES>(g, s, blk, p, side, t0);
+            else
+                face_copy<R, 2, SEND, SIDES>(g, s, blk, p, side, t0);
+        }
+    } else {
+        const int t0 = (int)(blockIdx.x * 256 + threadIdx.x);
+        const int face = (int)(g.ndim == 3 ? blockIdx.y : blockIdx.z) * SIDES;
+        const int axis = face >> 1, side = face & 1;
+        for (int64_t blk = b0 + (int64_t)(g.ndim == 3 ? blockIdx.z : blockIdx.y); blk < b1;
+             blk += stride) {
+            const BlockPos p = block_pos(g, blk);
+            if (axis == 0)
+                face_copy<R, 0, SEND, SIDES>(g, s, blk, p, side, t0);
+            else if (axis == 1)
+                face_copy<R, 1, SEND, SIDES>(g, s, blk, p, side, t0);
+            else
+                face_copy<R, 2, SEND, SIDES>(g, s, blk, p, side, t0);
+        }
     }
 }
 
@@ -410,16 +444,27 @@ static hipError_t launch_faces(const Geom &g, void *s, int64_t b0, int64_t b1, h
     if (m > 0x7fffffff - 4096) return hipErrorInvalidValue;
     const int64_t blocks = b1 - b0;
     if (m <= 128) {
-        int lanes = 16;
+        int lanes = 4;
         while (lanes < m) lanes *= 2;
-        const int64_t z = (blocks + 256 / lanes - 1) / (256 / lanes);
-        hipLaunchKernelGGL((k_halo<R, SEND, true>), dim3(1, 2 * g.ndim, (unsigned)(z < 65535 ? z : 65535)),
-                           dim3(256), 0, st, g, (R *)s, b0, b1, lanes);
+        // whole blocks per step of the grid, so that a thread's face is fixed
+        const int nf = 2 * g.ndim, per = 256 / lanes;
+        const int64_t most = (1 << 28) / nf;
+        const int64_t stride = blocks < most ? blocks : most;
+        hipLaunchKernelGGL((k_halo<R, SEND, true, 1>), dim3((unsigned)((stride * nf + per - 1) / per)),
+                           dim3(256), 0, st, g, (R *)s, b0, b1, lanes, stride);
         return hipGetLastError();
     }
-    const dim3 grid((unsigned)((m + 256 * kFaceCells - 1) / (256 * kFaceCells)), 2 * g.ndim,
-                    (unsigned)(blocks < 65535 ? blocks : 65535));
-    hipLaunchKernelGGL((k_halo<R, SEND, false>), grid, dim3(256), 0, st, g, (R *)s, b0, b1, 256);
+    const unsigned cells = (unsigned)((m + 255) / 256);
+    const unsigned strided = (unsigned)(blocks < 65535 ? blocks : 65535);
+    if (g.ndim == 2)
+        hipLaunchKernelGGL((k_halo<R, SEND, false, 2>), dim3(cells, strided, 2), dim3(256), 0, st, g,
+                           (R *)s, b0, b1, 256, (int64_t)strided);
+    else if constexpr (SEND)
+        hipLaunchKernelGGL((k_halo<R, true, false, 1>), dim3(cells, 6, strided), dim3(256), 0, st, g,
+                           (R *)s, b0, b1, 256, (int64_t)strided);
+    else
+        hipLaunchKernelGGL((k_halo<R, false, false, 2>), dim3(cells, 3, strided), dim3(256), 0, st, g,
+                           (R *)s, b0, b1, 256, (int64_t)strided);
     return hipGetLastError();
 }
 

@@ -161,3 +161,38 @@ def test_explicit_send_rule(device, dtype, case):
     for src in (f, None):
         check(U0, src, synthetic.spacing2(max(nx, ny)), 7, 3, (bx, by), dtype, device,
               "explicit %s" % (case,), depth=1, flags=JACOBI_FLAG_EXPLICIT_HALO)
+
+
+# Faces of up to 4, 8, ... 128 cells share workgroups, longer ones do not;
+# narrow and tall blocks, flat ones, and 3D faces of unequal size.  x blocks of
+# 32 columns or fewer: no sweep sends its cells itself.
+FACES = [
+    # (grid, blocks)
+    ((131, 60), (17, 5)),
+    ((600, 203), (15, 7)),
+    ((2000, 1300), (50, 26)),
+    ((1900, 900), (15, 7)),
+    ((512, 2611), (64, 2)),
+    ((16, 70000), (2, 240)),
+    ((40, 33, 29), (5, 4, 6)),
+    ((24, 10, 11), (3, 4, 3)),
+    ((96, 20, 70), (3, 2, 7)),
+    ((70, 41, 130), (2, 2, 3)),
+    ((33, 300, 9), (2, 3, 3)),
+]
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", FACES)
+def test_face_exchange_and_sends(device, dtype, case):
+    from paper_2303_02543_amd import JACOBI_FLAG_EXPLICIT_HALO, JACOBI_FLAG_OVERLAP
+    grid, blocks = case
+    shape = tuple(reversed(grid))
+    U0 = RNG.uniform(0, 1, tuple(n + 2 for n in shape))
+    f = RNG.uniform(-1, 1, shape)
+    # rows 1: 2D sweeps that leave the exchange to its own launch
+    for flags, rows in ((JACOBI_FLAG_EXPLICIT_HALO, 1 if len(grid) == 2 else 0),
+                        (JACOBI_FLAG_EXPLICIT_HALO | JACOBI_FLAG_OVERLAP, 0)):
+        check(U0, f, synthetic.spacing2(max(grid)), 6, 4, blocks, dtype, device,
+              "faces %s %s flags %d" % (case, np.dtype(dtype).name, flags), depth=1, rows=rows,
+              flags=flags)
