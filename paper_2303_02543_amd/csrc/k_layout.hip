@@ -438,9 +438,13 @@ hipError_t launch_scale_source(const Geom &g, const void *f, void *b, double h2,
 // The faces of blocks b0 .. b1-1.
 template <typename R, bool SEND>
 static hipError_t launch_faces(const Geom &g, void *s, int64_t b0, int64_t b1, hipStream_t st) {
-    const int64_t a = (int64_t)g.e[1] * g.e[2], b = (int64_t)g.e[0] * g.e[2], c = (int64_t)g.e[0] * g.e[1];
-    int64_t m = a > b ? a : b;
-    if (g.ndim == 3 && c > m) m = c;
+    // the longest face between blocks (an axis of one block has none)
+    int64_t m = 0;
+    for (int a = 0; a < g.ndim; ++a) {
+        const int64_t face = (int64_t)g.e[a == 0 ? 1 : 0] * g.e[a == 2 ? 1 : 2];
+        if (g.nb[a] > 1 && face > m) m = face;
+    }
+    if (m == 0) return hipSuccess;
     if (m > 0x7fffffff - 4096) return hipErrorInvalidValue;
     const int64_t blocks = b1 - b0;
     if (m <= 128) {
