@@ -31,7 +31,7 @@ UNITS = ([(s, os.path.splitext(s)[0], []) for s in SOURCES] +
           for d in range(1, 6)] +
          [("k_tile2d.hip", "k_tile2d_%s" % t, ["-DJAC_TILE2D_TYPE=%s" % t])
           for t in ("float", "double")])
-HEADERS = ["jacobi_internal.h", "kernels.h", "device_util.h"]
+HEADERS = ["jacobi_internal.h", "kernels.h", "device_util.h", "grid3d.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

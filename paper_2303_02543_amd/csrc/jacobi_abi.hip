@@ -543,8 +543,8 @@ int do_halo(jacobi_t h) {
 // Plan of a 3D pass of `depth` sweeps with the handle's z segment (or the
 // plan's own); its residual partials always fit the workspace's.
 template <typename R>
-int plan3d(const jacobi_s *h, int depth, jac::M3Plan *pl) {
-    if (!jac::march3d_plan<R>(h->g, depth, h->rows, cu_count(h), h->lay.part_cap, pl))
+int plan3d(const jacobi_s *h, int depth, jac::M3Plan *pl, bool store = true) {
+    if (!jac::march3d_plan<R>(h->g, depth, h->rows, cu_count(h), h->lay.part_cap, store, pl))
         return fail(JACOBI_E_INVAL, "partials overflow");
     return JACOBI_OK;
 }
@@ -554,7 +554,7 @@ int do_residual(jacobi_t h, double *out) {
     const void *b = h->has_source ? h->b : nullptr;
     if (h->g.ndim == 3) {
         jac::M3Plan pl;
-        int rc = plan3d<R>(h, 1, &pl);
+        int rc = plan3d<R>(h, 1, &pl, false);
         if (rc) return rc;
         HIP_TRY(jac::launch_march3d<R>(h->g, h->u[h->cur], nullptr, b, h->partials, pl, h->stream,
                                        1),

@@ -46,6 +46,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device_util.h"
+#include "grid3d.h"
 #include "jacobi_internal.h"
 #include "kernels.h"
 
@@ -71,28 +72,6 @@ struct M3 {
 // LDS copies of levels 1 .. T-1: [level][step parity][row + 1][lane of the row]
 template <typename R, int T, int RY>
 using M3Sh = Chunk<R, M3<R, T, RY>::V> (*)[2][M3<R, T, RY>::H + 2][16];
-
-// Element offset of the z part (block layer and plane) of a global plane z.
-__device__ __forceinline__ int64_t plane_part(const Geom &g, int zblk, int zloc) {
-    return (int64_t)zblk * g.nb[1] * g.nb[0] * g.bstride + (int64_t)(zloc + 1) * g.plane;
-}
-__device__ __forceinline__ int64_t src_plane_part(const Geom &g, int zblk, int zloc) {
-    return (int64_t)zblk * g.nb[1] * g.nb[0] * g.sstride + (int64_t)zloc * g.e[1] * g.e[0];
-}
-// Element offset of the x/y part of node (x, y) inside its z layer: its
-// block column / row and its place in the block's plane (state buffers).
-__device__ __forceinline__ int64_t xy_part(const Geom &g, int x, int y) {
-    int bx, lx, by, ly;
-    owner(x, g.e[0], g.nb[0], bx, lx);
-    owner(y, g.e[1], g.nb[1], by, ly);
-    return ((int64_t)by * g.nb[0] + bx) * g.bstride + (int64_t)(ly + 1) * g.pitch + g.ax + lx;
-}
-__device__ __forceinline__ int64_t src_xy_part(const Geom &g, int x, int y) {
-    int bx, lx, by, ly;
-    owner(x, g.e[0], g.nb[0], bx, lx);
-    owner(y, g.e[1], g.nb[1], by, ly);
-    return ((int64_t)by * g.nb[0] + bx) * g.sstride + (int64_t)ly * g.e[0] + lx;
-}
 
 // Plane cursor: global plane q (any integer), advanced one plane at a time;
 // off / soff are the element offsets of plane q clamped to [-1, n_z] in the
@@ -679,9 +658,48 @@ static bool m3_wide(const Geom &g, size_t es) {
     return (span + g.ax + 64.0) * (double)es >= (double)kBufferBytes;
 }
 
+// Which tiles, and the row kernel or the tiles: by estimated time, per depth.
+// The tiles' unit is a plane step of a 32-row tile per round of workgroups over
+// the CUs; a step of a 64-row tile takes `tall` units, and plans of several
+// rounds, which share less of their neighbours' planes in the L2s, `several`
+// times as many.  A plane step of the row kernel per round, two workgroups per CU,
+// takes `row` units (0: not compiled), its rounds counted whole below
+// `whole_below` cells.  It is a choice from `least` cells on, on plates of up to 32
+// planes from `plate` cells on, and is taken from `always` on.
+//
+// The constants are those that pick best among passes timed at 35 grids of 64^3 ..
+// 640^3, plates, and bars, with and without source, and checked at 30 others: passes
+// that are further than 5% behind the row kernel by itself are FP64 at depth 1, 256^3
+// (93 us against 86), 1024^2 x 3 (14.4 and 12.8), FP64 depth 5 of 1024^2 x 128 (1487 and
+// 1386), and FP64 residuals alone (300x280x320 72 and 59).  us per pass, tiles and row
+// kernel: FP64 512^3 Poisson depth 2 1200 and 1116, depth 4 1153 and 1071, but 640^3
+// depth 2 1928 and 2307 (one round); 400^3 depth 2 532 and 501, 350x301x260 229 and 256;
+// 1024^2 x 3 depth 4 61 and 45.  FP32 640^3 Laplace depth 1 555 and 506, depth 2 884 and
+// 764, 600x520x500 depth 1 477 and 438, but 512^3 depth 2 454 and 554, 353x343x186 45 and 70.
+struct M3Rule {
+    double tall, several, row, whole_below, least, plate, always;
+    double residual;  // `least` of passes without stores
+};
+constexpr double kNever = 1e300;
+static const M3Rule kM3Rule[2][5] = {
+    // FP32, depths 1 - 5
+    {{1.9, 1.0, 1.85, kNever, 1.05e8, 1 << 21, 1.05e8, 1.05e8},
+     {1.8, 1.2, 1.75, kNever, 1 << 26, kNever, kNever, kNever},
+     {1.8, 1.1, 1.70, 0, 1 << 26, kNever, kNever, kNever},
+     {1.8, 1.0, 1.60, kNever, 1 << 26, kNever, kNever, kNever},
+     {1.8, 1.0, 0, 0, kNever, kNever, kNever, kNever}},
+    // FP64
+    {{1.8, 1.0, 1.75, 0, 5.5e7, kNever, kNever, 3.5e7},
+     {1.8, 1.0, 1.40, kNever, 4e7, 0, kNever, kNever},
+     {1.8, 1.2, 1.60, kNever, 4e7, 0, kNever, kNever},
+     {1.8, 1.0, 1.48, 5e7, 0, 0, kNever, kNever},
+     {1.8, 1.0, 0, 0, kNever, kNever, kNever, kNever}},
+};
+
 template <typename R>
-bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Plan *out) {
+bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, bool store, M3Plan *out) {
     if (depth < 1 || depth > march3d_max_depth()) return false;
+    const M3Rule &rule = kM3Rule[sizeof(R) == 8][depth - 1];
     const int nz = g.n[2];
     M3Plan best;
     double best_cost = 1e300;
@@ -692,8 +710,7 @@ bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Pla
         p.wide = wide;
         m3_shape<R>(g, depth, ry, p.nstrips, p.ngrp);
         const int64_t tiles = (int64_t)p.nstrips * p.ngrp;
-        // relative time of one plane step of a tile of this height
-        const double step = ry == 2 ? 1.8 : 1.0;
+        const double step = ry == 2 ? rule.tall : 1.0;
         const int smin = zseg > 0 ? (nz + zseg - 1) / zseg : 1;
         const int smax = zseg > 0 ? smin : (nz + 3) / 4;
         for (int s = smin; s <= smax; ++s) {
@@ -702,8 +719,9 @@ bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Pla
             p.items = tiles * segs;
             p.partials = kM3Waves * p.items;
             if ((size_t)p.partials > cap || p.partials > 0x7fffffff - 3) break;
-            const double rounds = (double)((p.items + cus - 1) / cus);
-            const double cost = rounds * step * (p.zseg + 2 * (depth - 1) + 3);
+            const int64_t rounds = (p.items + cus - 1) / cus;
+            const double cost = rounds * step * (rounds > 1 ? rule.several : 1.0) *
+                                (p.zseg + 2 * (depth - 1) + 3);
             if (cost < best_cost) {
                 best_cost = cost;
                 best = p;
@@ -711,26 +729,22 @@ bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Pla
             if (rounds > 16) break;
         }
     }
-    // FP64 below depth 5: the row kernel where it is the faster one and its
-    // partials fit.  Depths 1 - 3, from 2^26 cells on: us per pass, it and the
-    // tiles above, 500x480x510 Poisson depth 1 1023 and 1066, depth 2 1105 and 1164,
-    // depth 3 1136 and 1182 (400^3 depth 3 524 and 529, 350x301x260 262 and 233).
-    // Depth 4, where passes are bound by their rounds, by the estimated time: its
-    // tiles run two per CU, 1.85 us per plane step of a round, the tiles above
-    // 1.25 us per unit of cost: 256^3 131 and 144, 350x301x260 266 and 271, 400^3
-    // 510 and 453, 512^3 1090 and 1162.
     M3Plan row;
-    if (sizeof(R) == 8 && rows3d_plan(g, depth, zseg, cap, &row)) {
-        const double rounds = (double)((row.items + 2 * cus - 1) / (2 * cus));
-        const bool faster = depth < 4 ? (double)g.n[0] * g.n[1] * nz >= (double)(1 << 26)
-                                      : row.items > cus &&
-                                            1.85 * rounds * (row.zseg + 2 * (depth - 1)) <
-                                                1.25 * best_cost;
-        if (faster || best_cost >= 1e300) {
+    if (rule.row > 0 && rows3d_plan<R>(g, depth, zseg, cap, &row)) {
+        const double cells = (double)g.n[0] * g.n[1] * nz;
+        const double full = (double)row.items / (2 * cus);
+        const double rounds = cells < rule.whole_below ? (double)((row.items + 2 * cus - 1) / (2 * cus))
+                                                       : full > 1.0 ? full : 1.0;
+        const int planes = row.zseg < nz ? row.zseg : nz;
+        const bool choice =
+            cells >= (store ? rule.least : rule.residual) || (nz <= 32 && cells >= rule.plate);
+        row.cost = rule.row * rounds * (planes + 2 * (depth - 1));
+        if ((choice && row.cost < best_cost) || cells >= rule.always || best_cost >= 1e300) {
             *out = row;
             return true;
         }
     }
+    best.cost = best_cost;
     *out = best;
     return best_cost < 1e300;
 }
@@ -772,16 +786,14 @@ hipError_t launch_march3d_batch(const BatchGrid *grids, const int *prefix, int n
 template <typename R>
 hipError_t launch_march3d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
                           const M3Plan &pl, hipStream_t st, int depth) {
-    if (pl.row)
-        return sizeof(R) == 8 ? launch_rows3d(g, uin, uout, b, res, pl, st, depth)
-                              : hipErrorInvalidValue;
+    if (pl.row) return launch_rows3d<R>(g, uin, uout, b, res, pl, st, depth);
 #define JAC_M3_CASE(F, T) F<R, T>
     JAC_M3_SWITCH(depth, m3_launch_t, g, uin, uout, b, res, pl, st)
 #undef JAC_M3_CASE
 }
 
 #define JAC_M3_DISPATCH(R)                                                                       \
-    template bool march3d_plan<R>(const Geom &, int, int, int, size_t, M3Plan *);                \
+    template bool march3d_plan<R>(const Geom &, int, int, int, size_t, bool, M3Plan *);          \
     template bool march3d_batch_wide<R>(const Geom &);                                           \
     template int64_t march3d_batch_items<R>(const Geom &, int, int);                             \
     template hipError_t launch_march3d_batch<R>(const BatchGrid *, const int *, int, bool, bool, \

@@ -1,5 +1,6 @@
-// FP64 pass kernel of 3D grids with one row per lane: T sweeps per pass, as
-// k_march3d.hip, for the calls where it is the faster of the two.
+// Pass kernel of 3D grids with one row per lane: up to four sweeps per pass, as
+// k_march3d.hip, for the calls where it is the faster of the two (march3d_plan
+// holds the rule).
 //
 // A workgroup of 8 waves holds 32 rows by 16 lanes of 16 bytes (one 16-lane row
 // of a wave per grid row) and marches along z through a segment of planes.
@@ -13,16 +14,18 @@
 // s - 1 cells on every side.  Ring cells, and cells beyond the ring, copy
 // their input at every level.
 //
-// What bounds it: memory (512^3 moves 3.2 GB per pass at depths 2 - 4 in the time
+// What bounds it: memory (FP64 512^3 moves 3.2 GB per pass at depths 2 - 4 in the time
 // of 2.8 TB/s, whatever the depth).  It is kept for what it measured against
 // k_march3d.hip, whose loads per row are as many; the cause was not isolated.
-// us per pass, it and the better of that kernel's tiles: 512^3 Poisson, depth 2
+// us per pass, it and the better of that kernel's tiles: FP64 512^3 Poisson, depth 2
 // 1143 and 1214, depth 3 1147 and 1200, depth 4 1090 and 1162, but depth 5 1448 and
-// 1108; 350x301x260 depths 2 - 3 254 - 262 and 231 - 234.  Deep-halo form, 512^3 in
-// 8^3 blocks, 60 sweeps at depth 4: 28.2 and 39.6 ms.
+// 1108; 350x301x260 depths 2 - 3 254 - 262 and 231 - 234; 1024^2 x 3 depth 4 45 and 61;
+// FP32 640^3 depth 1 Laplace 506 and 555, depth 2 764 and 884.  Deep-halo form,
+// FP64 512^3 in 8^3 blocks, 60 sweeps at depth 4: 28.2 and 39.6 ms.
 #include <hip/hip_runtime.h>
 
 #include "device_util.h"
+#include "grid3d.h"
 #include "jacobi_internal.h"
 #include "kernels.h"
 
@@ -45,28 +48,6 @@ struct R3 {
     static_assert(OW > 0 && OY > 0, "tile too small for this depth");
 };
 
-// Element offset of the z part (block layer and plane) of a global plane z.
-__device__ __forceinline__ int64_t r3_plane_part(const Geom &g, int zblk, int zloc) {
-    return (int64_t)zblk * g.nb[1] * g.nb[0] * g.bstride + (int64_t)(zloc + 1) * g.plane;
-}
-__device__ __forceinline__ int64_t r3_src_plane_part(const Geom &g, int zblk, int zloc) {
-    return (int64_t)zblk * g.nb[1] * g.nb[0] * g.sstride + (int64_t)zloc * g.e[1] * g.e[0];
-}
-// Element offset of the x/y part of node (x, y) inside its z layer: its
-// block column / row and its place in the block's plane (state buffers).
-__device__ __forceinline__ int64_t r3_xy_part(const Geom &g, int x, int y) {
-    int bx, lx, by, ly;
-    owner(x, g.e[0], g.nb[0], bx, lx);
-    owner(y, g.e[1], g.nb[1], by, ly);
-    return ((int64_t)by * g.nb[0] + bx) * g.bstride + (int64_t)(ly + 1) * g.pitch + g.ax + lx;
-}
-__device__ __forceinline__ int64_t r3_src_xy_part(const Geom &g, int x, int y) {
-    int bx, lx, by, ly;
-    owner(x, g.e[0], g.nb[0], bx, lx);
-    owner(y, g.e[1], g.nb[1], by, ly);
-    return ((int64_t)by * g.nb[0] + bx) * g.sstride + (int64_t)ly * g.e[0] + lx;
-}
-
 // Plane cursor: global plane q (any integer), advanced one plane at a time;
 // off / soff are the element offsets of plane q clamped to [-1, n_z] in the
 // state buffers and (0 for the ring planes) in the source (the ring planes
@@ -75,8 +56,8 @@ struct R3Cur {
     int q, blk, loc;
     int64_t off, soff;
     __device__ __forceinline__ void set(const Geom &g) {
-        off = r3_plane_part(g, blk, loc);
-        soff = q >= 0 && q < g.n[2] ? r3_src_plane_part(g, blk, loc) : 0;
+        off = plane_part(g, blk, loc);
+        soff = q >= 0 && q < g.n[2] ? src_plane_part(g, blk, loc) : 0;
     }
     __device__ __forceinline__ void init(const Geom &g, int q0) {
         q = q0;
@@ -94,7 +75,7 @@ struct R3Cur {
                 set(g);
             } else {
                 off += g.plane;
-                soff = q >= 0 && q < g.n[2] ? (q == 0 ? r3_src_plane_part(g, blk, loc)
+                soff = q >= 0 && q < g.n[2] ? (q == 0 ? src_plane_part(g, blk, loc)
                                                       : soff + (int64_t)g.e[1] * g.e[0])
                                             : 0;
             }
@@ -105,8 +86,8 @@ struct R3Cur {
 // Per-lane constants of a work item.
 struct R3Lane {
     int64_t c_off, h_off, e_off, b_off;  // own row, halo row (loaders), edge cell, source
-    int k;                               // LDS row slot of the lane's own row (1 .. 16)
-    int hk;                              // LDS slot of the lane's halo load (0, 17; own slot: none)
+    int k;                               // LDS row slot of the lane's own row (1 .. 32)
+    int hk;                              // LDS slot of the lane's halo load (0, 33; own slot: none)
     bool ld, lde, ldb;                   // lane loads interior/east-ring, edge, source
     bool upd[8];                         // element is an interior cell
     bool mine[8];                        // element is an output cell of this work item
@@ -331,24 +312,24 @@ __device__ __forceinline__ void r3_item(const Geom &g, const R *__restrict__ uin
     // chunk holds interior cells or ring / outside cells at in-bounds addresses
     L.ld = c <= nx;
     const int cl = L.ld ? c : 0;
-    L.c_off = r3_xy_part(g, cl, clampy(yy));
+    L.c_off = xy_part(g, cl, clampy(yy));
     L.hk = L.k;
     L.h_off = L.c_off;
     if (wv == 0 && ry == 0) {
         L.hk = 0;
-        L.h_off = r3_xy_part(g, cl, clampy(y0 - 1));
+        L.h_off = xy_part(g, cl, clampy(y0 - 1));
     } else if (wv == kR3Waves - 1 && ry == 3) {
         L.hk = kR3Rows + 1;
-        L.h_off = r3_xy_part(g, cl, clampy(y0 + kR3Rows));
+        L.h_off = xy_part(g, cl, clampy(y0 + kR3Rows));
     }
     // the first / last lane of each 16-lane row fetch the cells just west /
     // east of the tile; the others re-read their own first cell
     const int xe = cx == 0 ? a - 1 : cx == 15 ? a + W : c;
     L.lde = xe >= -1 && xe <= nx && (cx == 0 || cx == 15 || L.ld);
-    L.e_off = r3_xy_part(g, L.lde ? xe : 0, clampy(yy));
+    L.e_off = xy_part(g, L.lde ? xe : 0, clampy(yy));
     const bool row_in = yy >= 0 && yy < ny;
     L.ldb = c >= 0 && c < nx && row_in;
-    L.b_off = r3_src_xy_part(g, L.ldb ? c : 0, L.ldb ? yy : 0);
+    L.b_off = src_xy_part(g, L.ldb ? c : 0, L.ldb ? yy : 0);
     const bool out_row = kk >= T - 1 && kk < T - 1 + M::OY;
     L.out_lane = out_row && cx * V >= M::A0 && cx * V < M::A0 + M::OW;
 #pragma unroll
@@ -366,8 +347,15 @@ __device__ __forceinline__ void r3_item(const Geom &g, const R *__restrict__ uin
         r3_body<R, T, MODE, false, RES>(g, uin, uout, bsrc, slot, L, oz0, oz1, sh);
 }
 
+// FP32 is compiled for four waves per SIMD, two workgroups per CU (left to
+// itself the residual pass takes too many registers for the second).
+template <typename R>
+constexpr int r3_waves_per_simd() {
+    return sizeof(R) == 4 ? 4 : 2;
+}
+
 template <typename R, int T, int MODE, bool RES>
-__global__ __launch_bounds__(kR3Threads) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(kR3Threads) __attribute__((amdgpu_waves_per_eu(r3_waves_per_simd<R>())))
 void k_rows3d(Geom g, const R *__restrict__ uin,
                                                  R *__restrict__ uout,
                                                  const R *__restrict__ bsrc,
@@ -407,51 +395,56 @@ void k_rows3d_batch(const BatchGrid *__restrict__ grids,
                                sh);
 }
 
+template <typename R>
 static void r3_shape(const Geom &g, int depth, int zseg, int &nstrips, int &ngrp, int &nzs) {
     auto of = [&](int ow, int oy) {
         nstrips = (g.n[0] + ow - 1) / ow;
         ngrp = (g.n[1] + oy - 1) / oy;
     };
     switch (depth) {
-    case 1: of(R3<double, 1>::OW, R3<double, 1>::OY); break;
-    case 2: of(R3<double, 2>::OW, R3<double, 2>::OY); break;
-    case 3: of(R3<double, 3>::OW, R3<double, 3>::OY); break;
-    case 4: of(R3<double, 4>::OW, R3<double, 4>::OY); break;
-    default: of(R3<double, 5>::OW, R3<double, 5>::OY); break;
+    case 1: of(R3<R, 1>::OW, R3<R, 1>::OY); break;
+    case 2: of(R3<R, 2>::OW, R3<R, 2>::OY); break;
+    case 3: of(R3<R, 3>::OW, R3<R, 3>::OY); break;
+    case 4: of(R3<R, 4>::OW, R3<R, 4>::OY); break;
+    default: of(R3<R, 5>::OW, R3<R, 5>::OY); break;
     }
     nzs = (g.n[2] + zseg - 1) / zseg;
 }
 
+template <typename R>
 bool rows3d_plan(const Geom &g, int depth, int zseg, size_t cap, M3Plan *p) {
-    if (depth < kRows3dLo || depth > kRows3dHi) return false;
+    if (depth < 1 || depth > kRows3dMaxDepth) return false;
     M3Plan r;
     r.row = true;
     r.wide = true;
     r.ry = 1;
-    r.zseg = zseg > 0 ? zseg : kRows3dZseg;
+    // output planes per work item unless set: shorter segments repeat the
+    // 2 (T - 1) warm-up planes more often, longer ones leave too few work items
+    r.zseg = zseg > 0 ? zseg : sizeof(R) == 4 ? 32 : 64;
     int nzs;
-    r3_shape(g, depth, r.zseg, r.nstrips, r.ngrp, nzs);
+    r3_shape<R>(g, depth, r.zseg, r.nstrips, r.ngrp, nzs);
     r.items = (int64_t)r.nstrips * r.ngrp * nzs;
     r.partials = kR3Waves * r.items;
     if ((size_t)r.partials > cap || r.partials > 0x7fffffff - 3) return false;
     *p = r;
     return true;
 }
+template bool rows3d_plan<float>(const Geom &, int, int, size_t, M3Plan *);
+template bool rows3d_plan<double>(const Geom &, int, int, size_t, M3Plan *);
 
 int64_t rows3d_batch_items(const Geom &g, int zseg, int depth) {
     if (depth < 1 || depth > march3d_max_depth()) return -1;
     int ns, ng, nz;
-    r3_shape(g, depth, zseg, ns, ng, nz);
+    r3_shape<double>(g, depth, zseg, ns, ng, nz);
     return (int64_t)ns * ng * nz;
 }
 
-template <int T>
-static hipError_t r3_launch(const Geom &g, const double *uin, double *uout, const double *b,
-                            double *res, const M3Plan &pl, hipStream_t st) {
+template <typename R, int T>
+static hipError_t r3_launch(const Geom &g, const R *uin, R *uout, const R *b, double *res,
+                            const M3Plan &pl, hipStream_t st) {
 #define JAC_R3(MODEV, RESV)                                                                      \
-    hipLaunchKernelGGL((k_rows3d<double, T, MODEV, RESV>), dim3((unsigned)pl.items),             \
-                       dim3(kR3Threads), 0, st, g, uin, uout, b, res, pl.nstrips, pl.ngrp,       \
-                       pl.zseg, (int)pl.items)
+    hipLaunchKernelGGL((k_rows3d<R, T, MODEV, RESV>), dim3((unsigned)pl.items), dim3(kR3Threads), \
+                       0, st, g, uin, uout, b, res, pl.nstrips, pl.ngrp, pl.zseg, (int)pl.items)
     if (b && res)
         JAC_R3(1, true);
     else if (b)
@@ -464,19 +457,24 @@ static hipError_t r3_launch(const Geom &g, const double *uin, double *uout, cons
     return hipGetLastError();
 }
 
+template <typename R>
 hipError_t launch_rows3d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
                          const M3Plan &pl, hipStream_t st, int depth) {
-    const double *u = (const double *)uin, *s = (const double *)b;
-    double *o = (double *)uout;
-    static_assert(kRows3dLo == 1 && kRows3dHi == 4, "depths below");
+    const R *u = (const R *)uin, *s = (const R *)b;
+    R *o = (R *)uout;
+    static_assert(kRows3dMaxDepth == 4, "depths below");
     switch (depth) {
-    case 1: return r3_launch<1>(g, u, o, s, res, pl, st);
-    case 2: return r3_launch<2>(g, u, o, s, res, pl, st);
-    case 3: return r3_launch<3>(g, u, o, s, res, pl, st);
-    case 4: return r3_launch<4>(g, u, o, s, res, pl, st);
+    case 1: return r3_launch<R, 1>(g, u, o, s, res, pl, st);
+    case 2: return r3_launch<R, 2>(g, u, o, s, res, pl, st);
+    case 3: return r3_launch<R, 3>(g, u, o, s, res, pl, st);
+    case 4: return r3_launch<R, 4>(g, u, o, s, res, pl, st);
     default: return hipErrorInvalidValue;
     }
 }
+template hipError_t launch_rows3d<float>(const Geom &, const void *, void *, const void *, double *,
+                                         const M3Plan &, hipStream_t, int);
+template hipError_t launch_rows3d<double>(const Geom &, const void *, void *, const void *, double *,
+                                          const M3Plan &, hipStream_t, int);
 
 template <int T>
 static hipError_t r3b_launch(const BatchGrid *grids, const int *prefix, int ngrids, bool src,

@@ -142,13 +142,14 @@ struct M3Plan {
     int ry, nstrips, ngrp, zseg;
     int64_t items, partials;
     bool wide;
-    bool row = false;  // FP64: the kernel of k_rows3d.hip
+    bool row = false;  // the kernel of k_rows3d.hip
+    double cost = 0;   // estimated time, in units of march3d_plan's rule
 };
 // Plan of a pass of `depth` sweeps; zseg: output planes per work item (0:
-// chosen here, for `cus` compute units); cap: most residual partials.  false:
-// no such pass.
+// chosen here, for `cus` compute units); cap: most residual partials; store:
+// false for a pass that only sums the residual.  false: no such pass.
 template <typename R>
-bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, M3Plan *out);
+bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, bool store, M3Plan *out);
 int march3d_max_depth();
 // `depth` 3D sweeps in one pass over the whole grid (k_march3d.hip), reading
 // face neighbours' cells from their owning blocks.  uout may be NULL (residual
@@ -170,11 +171,12 @@ int64_t march3d_batch_items(const Geom &g, int zseg, int depth);
 template <typename R>
 bool march3d_batch_wide(const Geom &g);
 
-// FP64 3D passes of one row per lane (k_rows3d.hip), reached through
-// march3d_plan (depths kRows3dLo .. kRows3dHi) and the FP64 batches.
-constexpr int kRows3dLo = 1, kRows3dHi = 4;
-constexpr int kRows3dZseg = 64;  // output planes per work item unless set
+// 3D passes of one row per lane (k_rows3d.hip), reached through march3d_plan
+// and the FP64 batches.
+constexpr int kRows3dMaxDepth = 4;
+template <typename R>
 bool rows3d_plan(const Geom &g, int depth, int zseg, size_t cap, M3Plan *p);
+template <typename R>
 hipError_t launch_rows3d(const Geom &g, const void *uin, void *uout, const void *b, double *res,
                          const M3Plan &pl, hipStream_t st, int depth);
 int64_t rows3d_batch_items(const Geom &g, int zseg, int depth);

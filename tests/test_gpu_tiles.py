@@ -196,3 +196,51 @@ def test_face_exchange_and_sends(device, dtype, case):
         check(U0, f, synthetic.spacing2(max(grid)), 6, 4, blocks, dtype, device,
               "faces %s %s flags %d" % (case, np.dtype(dtype).name, flags), depth=1, rows=rows,
               flags=flags)
+
+
+# Tiles of 64 rows, two rows per lane (grids that fill the GPU with them), whose
+# last group ends just before, at and just beyond the ring: at depth 5 k groups
+# cover 56 k + 8 rows, and an odd number of rows ends inside a lane's pair.
+TILES_3D_64 = [
+    # (nx, ny, nz, bx, by, bz)
+    (513, 232, 160, 5, 4, 2),
+    (514, 233, 150, 3, 5, 3),
+    (511, 231, 155, 4, 3, 2),
+]
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", TILES_3D_64)
+def test_3d_tall_tile_edges(device, dtype, case):
+    nx, ny, nz, bx, by, bz = case
+    rng = np.random.default_rng(8)
+    U0 = rng.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
+    f = rng.uniform(-1, 1, (nz, ny, nx))
+    h2 = synthetic.spacing2(nx)
+    for src, K, R in ((f, 10, 5), (None, 6, 3)):
+        check(U0, src, h2, K, R, (bx, by, bz), dtype, device,
+              "3d tall tiles %s %s K %d" % (case, np.dtype(dtype).name, K))
+
+
+# FP32 passes on the row kernel: depth 1 of plates and from 1.05e8 cells on, depths
+# 2 - 4 from 2^26 cells on where its rounds are the shorter ones.
+ROWS_3D_F32 = [
+    # (nx, ny, nz, bx, by, bz, depth)
+    (1025, 1021, 3, 4, 3, 1, 1),
+    (480, 500, 441, 5, 4, 5, 1),
+    (419, 401, 403, 3, 4, 5, 2),
+    (419, 401, 403, 4, 3, 2, 3),
+    (2000, 600, 60, 9, 4, 2, 4),
+]
+
+
+@pytest.mark.parametrize("case", ROWS_3D_F32)
+def test_3d_rows_fp32(device, case):
+    nx, ny, nz, bx, by, bz, depth = case
+    rng = np.random.default_rng(9)
+    U0 = rng.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
+    f = rng.uniform(-1, 1, (nz, ny, nx))
+    h2 = synthetic.spacing2(max(nx, ny, nz))
+    for src in (f, None):
+        check(U0, src, h2, depth + 1, depth, (bx, by, bz), np.float32, device,
+              "3d rows fp32 %s %s" % (case, "laplace" if src is None else "poisson"), depth=depth)
