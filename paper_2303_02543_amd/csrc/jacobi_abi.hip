@@ -345,6 +345,7 @@ struct jacobi_s {
     // (Laplace, Poisson, adjoint) and depth
     mutable int cus = 0;
     mutable int round_rows[3][17] = {};
+    mutable int depth3 = 0;  // default depth of 3D FP64 passes (0: not chosen yet)
     std::vector<int> h_prefix;
 };
 
@@ -399,10 +400,22 @@ int balanced_rows(const jacobi_s *h, int depth, int mode, int rounds) {
 // a 2D FP32 8192^2 grid with a residual every 50 sweeps (depth 13: passes of
 // 13, 13, 12, 12), with a tile height that fills the GPU in one round of
 // resident waves, and for a 512^3 grid in 64^3 blocks (depth 5, the deepest
-// 3D pass).
+// 3D pass).  FP64 plates run at depth 4 where a sweep of a depth-5 pass is
+// estimated to take 1.35 times as long (its warm-up planes then outnumber the
+// plate's: 1024^2 x 3 16.0 us per sweep at depth 5, 11.2 at depth 4; x 24 55.7 and 53.2).
 int default_depth(const jacobi_s *h) {
-    if (h->g.ndim == 3) return h->halo > 0 && h->dtype == JACOBI_F64 ? 4 : 5;
-    return h->dtype == JACOBI_F32 ? 13 : 4;
+    if (h->g.ndim == 2) return h->dtype == JACOBI_F32 ? 13 : 4;
+    if (h->dtype == JACOBI_F32) return 5;
+    if (h->halo > 0) return 4;
+    if (h->depth3 == 0) {
+        jac::M3Plan p4, p5;
+        const int cus = cu_count(h);
+        const bool four = jac::march3d_plan<double>(h->g, 4, 0, cus, h->lay.part_cap, true, &p4) &&
+                          jac::march3d_plan<double>(h->g, 5, 0, cus, h->lay.part_cap, true, &p5) &&
+                          p5.cost / 5 > 1.35 * (p4.cost / 4);
+        h->depth3 = four ? 4 : 5;
+    }
+    return h->depth3;
 }
 
 // The 2D pass kernels address a lane's chunk as a 32-bit byte offset from a

@@ -244,3 +244,24 @@ def test_3d_rows_fp32(device, case):
     for src in (f, None):
         check(U0, src, h2, depth + 1, depth, (bx, by, bz), np.float32, device,
               "3d rows fp32 %s %s" % (case, "laplace" if src is None else "poisson"), depth=depth)
+
+
+def test_3d_plates_of_double_precision(device):
+    """Plates run four sweeps per pass in FP64 (the launches are counted), with
+    the result of any other schedule."""
+    import torch
+    import paper_2303_02543_amd as jb
+    nx, ny, nz = 1024, 1023, 3
+    rng = np.random.default_rng(10)
+    U0 = rng.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
+    f = rng.uniform(-1, 1, (nz, ny, nx))
+    check(U0, f, synthetic.spacing2(nx), 9, 8, (4, 3, 1), np.float64, device, "plate")
+    s = jb.Solver((nx, ny, nz), (4, 3, 1), torch.float64, device=device)
+    try:
+        s.set_state(torch.zeros(s.state_shape, dtype=torch.float64, device=device))
+        s.profile(True)
+        s.sweep(20)
+        assert s.profile_read(4)["launches"] == 5
+        s.profile(False)
+    finally:
+        s.close()
