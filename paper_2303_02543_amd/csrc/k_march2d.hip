@@ -67,14 +67,19 @@ struct M2 {
     static constexpr int L1 = (A0 + OW) / V;                  // one past the last output lane
     // rows loaded ahead (prefetch distance): row r + P is loaded at step r
     static_assert(P >= 1 && P <= 3, "prefetch distance 1..3");
-    // With a source (without the folded residual, whose pass took 10 us longer that
-    // way, at 3000x2500 as at 6000x5000: 65 and 54 us, 130 and 117), depths 12 and 13
-    // unroll 15 steps, and the source ring
-    // holds 15 rows (12 at depths 10 and 11, whose groups are 12 steps): every
-    // LDS slot is then a compile-time offset from the lane's base, not an
-    // address computed for every level (depth 13: 264 VALU instructions per
-    // step instead of 286, for 260 plain operations).
-    static constexpr bool BIG = MODE == MODE_POISSON && P == 2 && T >= 12;
+    // With a source and without the folded residual, depth 12 unrolls 15 steps and
+    // its source ring holds 15 rows (12 at depths 10 and 11, whose groups are 12
+    // steps): every LDS slot is then a compile-time offset from the lane's base,
+    // not an address computed for every level (depth 12, 3000^2: 41.9 -> 39.7 us,
+    // 4096^2 56.2 -> 52.9).  At depth 13, and with the residual at both, groups of 15
+    // steps were slower: 3500x3200 depth 13 50.0 against 52.3 us, 2000x1500 34.8
+    // against 37.4, 3000x2500 with the residual 54 against 65.
+    static constexpr bool BIG = MODE == MODE_POISSON && P == 2 && T == 12;
+    // Loads and stores through descriptors: passes of 2 - 12 sweeps with a source.
+    // The others are faster with plain ones (us per pass, descriptors and plain:
+    // Laplace 3500x3200 depth 12 37.3 and 36.6, with the residual 49.7 and 48.1, depth 13
+    // 40.6 and 39.4; the residual alone, 9 x 10^6 cells in FP64, 111 and 88).
+    static constexpr bool DESC = (MODE & 1) != 0 && T > 1 && T <= 12;
     static constexpr int LR = BIG ? 5 : P == 1 ? 4 : 6;       // level-0 ring: rows r-2 .. r+P
     static constexpr int BQ = BIG ? 3 : P == 1 ? 2 : P;       // source registers: rows r .. r+P
     // BQ == P: the slot of row r is reused for row r + P, so row r goes to
@@ -215,6 +220,13 @@ struct MLane {
     int oy0, oy1, r1;
 };
 
+// A lane's chunk or cell of a row, through a descriptor or plainly.
+template <bool DESC, typename X, typename R>
+__device__ __forceinline__ X m2_get(const R *row, uint32_t off) {
+    if constexpr (DESC) return buffer_get<X>(row, off);
+    return at<X>(row, off);
+}
+
 // Issue the loads of row lc.y into level-0 slot SL, source register slot SQ
 // and (adjoint pass) accumulator slot SA, then advance the cursor.
 template <typename R, int T, int P, int MODE, int EK, int SL, int SQ, int SA>
@@ -241,13 +253,14 @@ __device__ __forceinline__ void m2_load(const Geom &g, const R *__restrict__ uin
     // keeps at their values
     const bool row_ok = !(EK & 1) || (y >= -1 && y <= ny);
     const R *row = uin + (row_ok ? lc.su : (int64_t)g.pitch);
-    const C c = buffer_get<C>(row, L.lane_b);
+    constexpr bool DESC = M2<R, T, P, MODE>::DESC;
+    const C c = m2_get<DESC, C>(row, L.lane_b);
 #pragma unroll
     for (int v = 0; v < V; ++v) m.l0[SL][v] = c.v[v];
-    m.e0[SL] = buffer_get<R>(row, L.edge_b);
+    m.e0[SL] = m2_get<DESC, R>(row, L.edge_b);
     if constexpr (SRC) {
         const bool brow = !(EK & 1) || (y >= 0 && y < ny);
-        const C cb = buffer_get<C>(bsrc + (brow ? lc.sb : (int64_t)0), L.src_b);
+        const C cb = m2_get<DESC, C>(bsrc + (brow ? lc.sb : (int64_t)0), L.src_b);
 #pragma unroll
         for (int v = 0; v < V; ++v) m.bq[SQ][v] = cb.v[v];
     }
@@ -396,24 +409,43 @@ __device__ __forceinline__ void m2_level(const Geom &g, R *__restrict__ uout,
             m2_accumulate<R, T, P, MODE, EK, (J - S + 2 * M::RA) % M::RA, S == T - 1>(g, gacc, L,
                                                                                      m, y, out);
         } else {
-            const bool on = uout && y >= L.oy0 && y < L.oy1;
-            R *row = uout + sc.su;
-            Chunk<R, V> o;
+            if constexpr (M::DESC) {
+                const bool on = uout && y >= L.oy0 && y < L.oy1;
+                R *row = uout + sc.su;
+                Chunk<R, V> o;
 #pragma unroll
-            for (int v = 0; v < V; ++v) o.v[v] = out[v];
-            // one store on every path, so that the waits for the rows in
-            // flight need not include it
-            if (L.nt)
-                buffer_put16<true>(row, L.st_b, on, o);
-            else
-                buffer_put16<false>(row, L.st_b, on, o);
-            if constexpr ((EK & 2) != 0) {
-                // the lane holding the east ring column and interior columns
-                // before it stores element by element
-                if (on && L.st_part) {
+                for (int v = 0; v < V; ++v) o.v[v] = out[v];
+                // one store on every path, so that the waits for the rows in
+                // flight need not include it
+                if (L.nt)
+                    buffer_put16<true>(row, L.st_b, on, o);
+                else
+                    buffer_put16<false>(row, L.st_b, on, o);
+                if constexpr ((EK & 2) != 0) {
+                    // the lane holding the east ring column and interior columns
+                    // before it stores element by element
+                    if (on && L.st_part) {
 #pragma unroll
-                    for (int v = 0; v < V; ++v)
-                        if (L.st[v]) at_mut<R>(row, L.lane_b + v * (uint32_t)sizeof(R)) = out[v];
+                        for (int v = 0; v < V; ++v)
+                            if (L.st[v]) at_mut<R>(row, L.lane_b + v * (uint32_t)sizeof(R)) = out[v];
+                    }
+                }
+            } else if (uout && y >= L.oy0 && y < L.oy1) {
+                R *row = uout + sc.su;
+                Chunk<R, V> o;
+#pragma unroll
+                for (int v = 0; v < V; ++v) o.v[v] = out[v];
+                if (L.st_b != kNoStore) {
+                    if (L.nt)
+                        store_nt16(&at_mut<Chunk<R, V>>(row, L.lane_b), o);
+                    else
+                        at_mut<Chunk<R, V>>(row, L.lane_b) = o;
+                } else if constexpr ((EK & 2) != 0) {
+                    if (L.st_part) {
+#pragma unroll
+                        for (int v = 0; v < V; ++v)
+                            if (L.st[v]) at_mut<R>(row, L.lane_b + v * (uint32_t)sizeof(R)) = out[v];
+                    }
                 }
             }
         }
@@ -604,11 +636,20 @@ __device__ __forceinline__ void m2_run(const Geom &g, const R *__restrict__ uin,
         m2_body<R, T, P, MODE, 0, RES>(g, uin, uout, bsrc, res_slot, gacc, L, r0);
 }
 
+// Waves per SIMD that the kernels are compiled for: two where the pass has a
+// source (left to itself the pass of 13 sweeps with the folded residual takes
+// registers for one: 92 us against 57, 3000^2), up to the depth whose registers
+// fit half of the file (16 sweeps would spill: 127 us against 81, 3500x3200).
+template <int T, int MODE>
+constexpr int m2_waves_per_simd() {
+    return (MODE & 1) != 0 && T > 1 && T <= 14 ? 2 : 1;
+}
+
 // uout may be NULL (no stores: residual only); res (used when RES) receives
 // one residual partial per work item; gacc is the FP64 accumulator of the
 // adjoint pass (MODE_ADJOINT only).
 template <typename R, int T, int P, int MODE, bool RES>
-__global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_march2d(Geom g, const R *__restrict__ uin,
+__global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(m2_waves_per_simd<T, MODE>()))) void k_march2d(Geom g, const R *__restrict__ uin,
                                                  R *__restrict__ uout,
                                                  const R *__restrict__ bsrc,
                                                  double *__restrict__ res,
@@ -635,7 +676,7 @@ __global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2
 // MODE: Poisson (the batched solver; the deep-halo form with a source) or
 // Laplace (the deep-halo form without one).
 template <typename R, int T, int P, bool RES, int MODE>
-__global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(2))) void k_march2d_batch(const BatchGrid *__restrict__ grids,
+__global__ __launch_bounds__(64 * kM2Waves) __attribute__((amdgpu_waves_per_eu(m2_waves_per_simd<T, MODE>()))) void k_march2d_batch(const BatchGrid *__restrict__ grids,
                                                        const int *__restrict__ prefix, int ngrids,
                                                        const int *__restrict__ active,
                                                        const int *__restrict__ pass_count, int pass,
