@@ -6,6 +6,7 @@
 // allocates no device memory: the caller's workspace holds everything.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -459,24 +460,37 @@ int pick_depth(int dtype, int want) {
 
 // Estimated duration (us) of a marching 2D pass of compiled depth t: 2 t more
 // steps than the tile has rows (8, or what one round of resident waves
-// leaves), each as long as its levels take, or the time its bytes take.  The
-// step times are those of passes timed on MI355X: FP32 13 levels 0.9 - 1.1 us
-// at 130^2 .. 8192^2, FP64 4 levels 0.7, adjoint FP32 7 levels 1.2, FP64 3 levels
-// 0.85.  rows = 0: a lower bound, for tiles of the least height.
+// leaves), each as long as its levels take, or the time its bytes take.
+// FP32 sweeps, fitted to passes of 7 .. 13 sweeps timed on MI355X at 130^2 ..
+// 8192^2 (half of them within 5%; 13 sweeps, 3000^2: Laplace 35.7 us, estimate
+// 37.4, with a source 45.6 and 46.0; 16 sweeps run one wave per SIMD, whose
+// steps are shorter: Laplace 3500x3200 51 us): bytes add a part of their time, the
+// residual a part of each step's.  The others by step times alone: FP64 4
+// levels 0.7 us, adjoint FP32 7 levels 1.2, FP64 3 levels 0.85.  rows = 0: a lower
+// bound, for tiles of the least height.
 template <typename R>
-double march_us(const jacobi_s *h, int t, int mode, int rows) {
-    const double level = sizeof(R) == 4 ? (mode == 2 ? 0.135 : 0.06) : (mode == 2 ? 0.20 : 0.11);
-    const double steps = (rows > 0 ? rows : kMinRows < h->g.n[1] ? kMinRows : h->g.n[1]) + 2 * t;
-    const double us = 2.0 + steps * (0.25 + level * t);
+double march_us(const jacobi_s *h, int t, int mode, bool res, int rows) {
+    const int steps = (rows > 0 ? rows : kMinRows < h->g.n[1] ? kMinRows : h->g.n[1]) + 2 * t;
     const double mem = (double)h->g.n[0] * h->g.n[1] * jac::pass_bytes<R>(mode) / jac::kPassBytesPerUs;
-    return us > mem ? us : mem;
+    if (sizeof(R) == 4 && mode < 2) {
+        const double step = mode == 1 ? (0.19 + 0.039 * t) * (res ? 1.23 : 1.0)
+                                      : (0.10 + 0.033 * t) * (res ? 1.31 : 1.0) * (t > 14 ? 0.75 : 1.0);
+        const double add = (mode == 1 ? 0.26 : 0.31) * mem;
+        return jac::kPassLaunchUs + add + std::max(mem - add, steps * step);
+    }
+    const double level = sizeof(R) == 4 ? 0.135 : mode == 2 ? 0.20 : 0.11;
+    return std::max(2.0 + steps * (0.25 + level * t), mem);
 }
 
 // The next 2D pass of `left` sweeps that remain: its sweeps, and whether it
 // runs on tiles held in registers (tile, tp) or marches.  A caller's depth or
 // tile height is kept: a given depth fixes the split into passes, a given
 // height the marching kernel.  Otherwise tiles run where they are expected to
-// take less time per sweep than marching passes of depth `depth`.
+// take less time per sweep than marching passes of depth `depth` - for FP32
+// sweeps, whose two routes are close at 2000^2 .. 4000^2, 5% less: of 1255
+// timed runs of 8 .. 100 sweeps (42 grids, with and without source and residual)
+// 9 then take 2 - 13% longer than marching alone, where 26 do without that
+// margin; tiles save 15% over all (2500^2, 50 sweeps with a source: 320 us against 360).
 struct Pass2d {
     int t;
     bool tile;
@@ -504,8 +518,9 @@ Pass2d plan2d(const jacobi_s *h, int64_t left, int depth, bool fixed_depth, bool
         }
     }
     if (best == 1e300) return p;
-    if (best >= march_us<R>(h, p.t, mode, 0) / p.t &&
-        best >= march_us<R>(h, p.t, mode, round_rows(h, p.t, mode)) / p.t)
+    if (sizeof(R) == 4 && mode < 2) best *= 1.05;
+    if (best >= march_us<R>(h, p.t, mode, res, 0) / p.t &&
+        best >= march_us<R>(h, p.t, mode, res, round_rows(h, depth, mode)) / p.t)
         return p;
     p.tile = true;
     p.t = p.tp.t;

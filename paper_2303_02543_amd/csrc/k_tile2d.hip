@@ -411,28 +411,32 @@ static int t2_tiles(int n, int hold, int halo) {
     return n <= hold ? 1 : out <= 0 ? 0 : (n - 2 * halo + out - 1) / out;
 }
 
-// Duration of a pass: kLaunchUs + rounds of workgroups over the CUs x (c0 +
-// c1 t) us, at least the time its bytes take.  c0 (load, store) and c1 (a
-// sweep) per shape from passes of 1 .. 16 sweeps timed on MI355X at 130^2 ..
-// 8192^2; e.g. FP32 Poisson, 1000 x 777, 13 sweeps: 128 x 64 tiles 13.3 us,
-// the marching pass 31.7; 2048^2: 256 x 128 tiles 32.4 us, marching 39.2; FP64
+// Duration of a pass: kPassLaunchUs + its rounds of workgroups over the CUs x (c0 +
+// c1 t, + cr with the residual) us, at least the time its bytes take, of which
+// the part `mem` adds.  The figures per shape are fitted to passes of 1 .. 16
+// sweeps timed on MI355X at 130^2 .. 8192^2 (FP32 sweeps: half of them within 6%);
+// e.g. FP32 Poisson, 1000 x 777, 13 sweeps: 128 x 64 tiles 13.3 us,
+// the marching pass 28.9; 2048^2: 256 x 128 tiles 32.4 us, marching 36.0; FP64
 // 2500 x 1701, 13 sweeps: 128 x 128 tiles 51.4 us, marching (4 sweeps) 30.0;
 // adjoint FP32 4096^2, 13 sweeps: 152 us, marching (7 sweeps) 105.7.  Shapes
 // of at most 64 VGPRs run two workgroups per CU, which then take 3/4 of the
-// time of two rounds.
+// time of two rounds; a last round counts in full among the first four
+// (1000 x 777 adjoint, 1.2 workgroups per CU: 13 sweeps on 64 x 64 tiles 22.7 us, on
+// 128 x 64 13.9).
 struct T2Cost {
-    double c0, c1;
+    double mem, c0, c1, cr;
     bool two;
 };
-static const T2Cost kT2Cost[2][2][5] = {
-    // FP32: Laplace / Poisson, adjoint
-    {{{2.2, 0.20, true}, {2.6, 0.35, true}, {3.0, 0.47, true}, {5.9, 0.87, false}, {6.0, 1.43, false}},
-     {{2.6, 0.22, true}, {3.3, 0.29, true}, {3.8, 0.55, false}, {5.9, 1.05, false}, {0, 0, false}}},
+static const T2Cost kT2Cost[2][3][5] = {
+    // FP32: Laplace, Poisson, adjoint
+    {{{1.64, 0.0, 0.19, 1.2, true}, {0.96, 0.0, 0.28, 1.1, true}, {0.21, 1.5, 0.30, 0.9, true}, {0, 2.1, 0.51, 4.1, false}, {0.25, 2.0, 1.14, 4.0, false}},
+     {{1.42, 0.0, 0.19, 1.3, true}, {0.56, 0.3, 0.32, 1.4, true}, {0.21, 1.7, 0.34, 0.9, true}, {0.28, 3.0, 0.68, 2.8, false}, {0.42, 2.2, 1.40, 4.5, false}},
+     {{0, 2.6, 0.22, 0, true}, {0, 3.3, 0.29, 0, true}, {0, 3.8, 0.55, 0, false}, {0, 5.9, 1.05, 0, false}, {0, 0, 0, 0, false}}},
     // FP64
-    {{{2.2, 0.27, true}, {2.8, 0.46, true}, {2.8, 0.62, false}, {4.8, 1.14, false}, {0, 0, false}},
-     {{2.4, 0.30, true}, {3.2, 0.48, true}, {3.2, 0.70, false}, {5.7, 1.28, false}, {0, 0, false}}},
+    {{{0, 2.2, 0.27, 0, true}, {0, 2.8, 0.46, 0, true}, {0, 2.8, 0.62, 0, false}, {0, 4.8, 1.14, 0, false}, {0, 0, 0, 0, false}},
+     {{0, 2.2, 0.27, 0, true}, {0, 2.8, 0.46, 0, true}, {0, 2.8, 0.62, 0, false}, {0, 4.8, 1.14, 0, false}, {0, 0, 0, 0, false}},
+     {{0, 2.4, 0.30, 0, true}, {0, 3.2, 0.48, 0, true}, {0, 3.2, 0.70, 0, false}, {0, 5.7, 1.28, 0, false}, {0, 0, 0, 0, false}}},
 };
-constexpr double kLaunchUs = 4.0;
 
 template <typename R>
 bool tile2d_plan(const Geom &g, int t, int mode, bool res, size_t cap, int cus, Tile2dPlan *out) {
@@ -452,12 +456,13 @@ bool tile2d_plan(const Geom &g, int t, int mode, bool res, size_t cap, int cus, 
         p.ngrp = t2_tiles(g.n[1], kT2Waves * sh[s].ry, t);
         p.items = (int64_t)p.nstrips * p.ngrp;
         if (p.items <= 0 || p.items > 0x7fffffff || (res && (size_t)p.items > cap)) continue;
-        const T2Cost &c = kT2Cost[sizeof(R) == 8][mode == T2_ADJOINT][s];
+        const T2Cost &c = kT2Cost[sizeof(R) == 8][mode][s];
         const double full = (double)p.items / cus;
-        const double rounds = c.two ? (full > 4.0 / 3.0 ? 0.75 * full : 1.0)
-                                    : (double)((p.items + cus - 1) / cus);
-        const double us = rounds * (c.c0 + c.c1 * t);
-        p.us = kLaunchUs + (us > mem ? us : mem);
+        const double whole = (double)((p.items + cus - 1) / cus);
+        const double rounds = !c.two || full <= 1.0 ? whole : 0.75 * (full <= 4.0 ? whole : full);
+        const double us = rounds * (c.c0 + c.c1 * t + (res ? c.cr : 0.0));
+        const double add = c.mem * mem;
+        p.us = kPassLaunchUs + add + (us > mem - add ? us : mem - add);
         if (p.us < out->us) *out = p;
     }
     return out->us < 1e300;

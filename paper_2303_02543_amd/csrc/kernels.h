@@ -103,6 +103,7 @@ double pass_bytes(int mode) {
     return sizeof(R) * (mode == 1 ? 3.0 : 2.0) + (mode == 2 ? 16.0 : 0.0);
 }
 constexpr double kPassBytesPerUs = 4.5e6;
+constexpr double kPassLaunchUs = 4.0;
 
 // 2D pass of t sweeps with the grid's tiles held in registers (k_tile2d.hip).
 struct Tile2dPlan {

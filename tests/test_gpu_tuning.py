@@ -130,6 +130,38 @@ def test_tuning_read_back_gives_the_schedule_again(device, case):
         s.close()
 
 
+@pytest.mark.parametrize("case", [((20000, 500), (20, 1), True, True), ((6000, 2000), (12, 4), True, True),
+                                  ((6000, 2000), (12, 4), False, True), ((4096, 2048), (8, 4), False, True),
+                                  ((1200, 1100), (4, 4), True, False), ((2500, 2500), (5, 5), True, False)])
+def test_2d_single_precision_route(device, case):
+    """FP32 grids on which register tiles are slower march for any number of sweeps
+    (a tile height is reported; 13 sweeps of 20000x500 with a source 48.6 us, on
+    tiles 62.1); smaller ones run on register tiles.  Same states by either."""
+    import torch
+    import paper_2303_02543_amd as jb
+    shape, blocks, src, march = case
+    gen = torch.Generator(device).manual_seed(5)
+    solvers = [jb.Solver(shape, blocks, torch.float32, device=device) for _ in range(2)]
+    try:
+        U = torch.rand(solvers[0].state_shape, dtype=torch.float32, device=device, generator=gen)
+        f = torch.rand(solvers[0].interior_shape, dtype=torch.float32, device=device, generator=gen)
+        for s in solvers:
+            if src:
+                s.set_source(f, 1e-6)
+            s.set_state(U)
+        rows = solvers[0].get_tuning()[1]
+        say("route", case, rows)
+        assert (rows > 0) == march
+        solvers[1].set_tuning(5, 16, 0)
+        for s in solvers:
+            s.sweep(13)
+            s.sweep(50)
+        assert torch.equal(solvers[0].get_state(), solvers[1].get_state())
+    finally:
+        for s in solvers:
+            s.close()
+
+
 @pytest.mark.parametrize("case", [((700, 601), (3, 2), "float64"), ((1200, 1000), (4, 4), "float32"),
                                   ((96, 96, 96), (2, 2, 2), "float32")])
 def test_autotune_is_not_slower_than_the_default(device, monkeypatch, case):
