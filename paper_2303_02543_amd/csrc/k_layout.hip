@@ -26,9 +26,13 @@ namespace jac {
 // a quarter of its lanes busy in each block) and now: scatter 664 us plus 464
 // for the two halo exchanges it now includes -> 604; gather 548 -> 286; source
 // 444 -> 203.  8192^2 FP32 in 512^2 blocks: 167 + 42 -> 154, 125 -> 88, 124 -> 100.
+//
+// Planes of fewer rows than a workgroup's lanes cover share one, as many planes as
+// fit: 256^3 FP32 in 8^3-cell blocks, a plane per workgroup (16 of its 256 threads
+// busy) and now: source 272 -> 48 us, gather 388 -> 155.
 struct RowMap {
-    int lanes, rows;  // lanes per row (a power of two), rows per workgroup and step
-    dim3 grid;        // x: row groups, y: planes, z: blocks (both strided beyond the limits)
+    int lanes, rows;  // lanes per row, rows per plane and step (both powers of two)
+    dim3 grid;        // x: row groups, y: groups of planes, z: blocks (all strided beyond the limits)
 };
 // nrows, nplanes: rows per block plane and planes per block to cover
 template <typename R>
@@ -37,15 +41,38 @@ static RowMap row_map(const Geom &g, int nrows, int nplanes) {
     RowMap m;
     m.lanes = 1;
     while (m.lanes < 256 && m.lanes * V < g.e[0]) m.lanes *= 2;
-    m.rows = 256 / m.lanes;
-    // four steps per workgroup where that still leaves workgroups enough
-    // (a 256^2 gather in one step each: 3.5 us, in four 5.7)
+    m.rows = 1;
+    while (m.rows < 256 / m.lanes && m.rows < nrows) m.rows *= 2;
+    const int per = 256 / (m.lanes * m.rows), pgroups = (nplanes + per - 1) / per;
+    // up to four pieces per thread where that still leaves 1024 workgroups (2000x1500
+    // FP64 gather, a workgroup per row 12.3 us, four rows each 9.5; a 256^2 gather
+    // in one step each 3.5 us, in four 5.7), two in grids beyond the 256 MiB cache
+    // (512^3 FP32 in 64^3 blocks, gather 324 us with four, 305 with two)
     int groups = (nrows + m.rows - 1) / m.rows;
-    if ((double)groups * nplanes * (double)g.nblocks >= 8192.0) groups = (groups + 3) / 4;
-    m.grid = dim3((unsigned)(groups < 1 ? 1 : groups > (1 << 20) ? (1 << 20) : groups), (unsigned)(nplanes < 65535 ? nplanes : 65535),
+    const double cells = (double)g.n[0] * g.n[1] * (g.ndim == 3 ? g.n[2] : 1);
+    const int along = (g.e[0] + m.lanes * V - 1) / (m.lanes * V);
+    const int most = (cells * sizeof(R) >= 268435456.0 ? 2 : 4) / along;
+    const double fit = (double)groups * pgroups * (double)g.nblocks / 1024.0;
+    const int steps = most < 1 || fit < 1.0 ? 1 : fit < most ? (int)fit : most;
+    groups = (groups + steps - 1) / steps;
+    m.grid = dim3((unsigned)(groups < 1 ? 1 : groups > (1 << 20) ? (1 << 20) : groups), (unsigned)(pgroups < 65535 ? pgroups : 65535),
                   (unsigned)(g.nblocks < 65535 ? g.nblocks : 65535));
     return m;
 }
+
+// A thread's lane, row and plane in its workgroup's step.
+struct RowThread {
+    int lane, row, plane;
+    int nrows, nplanes;  // rows and planes that the grid covers in a step
+    __device__ __forceinline__ RowThread(int lanes, int rows) {
+        const int t = (int)threadIdx.x, per = 256 / (lanes * rows);
+        lane = t & (lanes - 1);
+        row = (int)blockIdx.x * rows + ((t / lanes) & (rows - 1));
+        plane = (int)blockIdx.y * per + t / (lanes * rows);
+        nrows = (int)gridDim.x * rows;
+        nplanes = (int)gridDim.y * per;
+    }
+};
 
 // 16 bytes at the full array's alignment
 template <typename R>
@@ -75,24 +102,24 @@ __device__ __forceinline__ BlockPos block_pos(const Geom &g, int64_t blk) {
 template <typename R>
 __global__ __launch_bounds__(256) void k_scatter(Geom g, const R *__restrict__ u,
                                                  R *__restrict__ s0, R *__restrict__ s1, int lanes,
-                                                 int zero_ring) {
+                                                 int rows, int zero_ring) {
     constexpr int V = 16 / (int)sizeof(R);
     const int64_t nx2 = g.n[0] + 2, ny2 = g.n[1] + 2;
-    const int lane = threadIdx.x & (lanes - 1), r0 = threadIdx.x / lanes, rpw = 256 / lanes;
+    const RowThread rt(lanes, rows);
     const int lz0 = g.ndim == 3 ? -1 : 0;
     for (int64_t blk = blockIdx.z; blk < g.nblocks; blk += gridDim.z) {
         const BlockPos p = block_pos(g, blk);
         const int ex = p.ext[0], ey = p.ext[1], hz = g.ndim == 3 ? p.ext[2] : 0;
         const int x0 = p.b[0] * g.e[0], y0 = p.b[1] * g.e[1], z0 = p.b[2] * g.e[2];
-        for (int lz = lz0 + (int)blockIdx.y; lz <= hz; lz += gridDim.y) {
+        for (int lz = lz0 + rt.plane; lz <= hz; lz += rt.nplanes) {
             const int z = z0 + lz;
             const bool zr = g.ndim == 3 && (z < 0 || z >= g.n[2]);
-            for (int ly = -1 + (int)blockIdx.x * rpw + r0; ly <= ey; ly += (int)gridDim.x * rpw) {
+            for (int ly = -1 + rt.row; ly <= ey; ly += rt.nrows) {
                 const int y = y0 + ly;
                 const bool ring = zero_ring && (zr || y < 0 || y >= g.n[1]);
                 const R *src = u + ((g.ndim == 3 ? (int64_t)(z + 1) * ny2 : 0) + y + 1) * nx2 + 1 + x0;
                 const int64_t o = local_offset(g, blk, 0, ly, lz);
-                for (int c = lane * V; c < ex; c += lanes * V) {
+                for (int c = rt.lane * V; c < ex; c += lanes * V) {
                     if (c + V <= ex) {
                         Loose<R> t = *reinterpret_cast<const Loose<R> *>(src + c);
                         Chunk<R, V> w;
@@ -106,12 +133,10 @@ __global__ __launch_bounds__(256) void k_scatter(Geom g, const R *__restrict__ u
                     }
                 }
                 // the cells west and east of the row
-                if (lane < 2 || lanes < 2) {
-                    for (int side = lane; side < 2; side += lanes) {
-                        const int lx = side == 0 ? -1 : ex, x = x0 + lx;
-                        const bool zero = ring || (zero_ring && (x < 0 || x >= g.n[0]));
-                        s0[o + lx] = s1[o + lx] = zero ? (R)0 : src[lx];
-                    }
+                if (rt.lane < 2) {
+                    const int lx = rt.lane == 0 ? -1 : ex, x = x0 + lx;
+                    const bool zero = ring || (zero_ring && (x < 0 || x >= g.n[0]));
+                    s0[o + lx] = s1[o + lx] = zero ? (R)0 : src[lx];
                 }
             }
         }
@@ -122,10 +147,10 @@ __global__ __launch_bounds__(256) void k_scatter(Geom g, const R *__restrict__ u
 // sides, to the full array.
 template <typename R>
 __global__ __launch_bounds__(256) void k_gather(Geom g, const R *__restrict__ s,
-                                                R *__restrict__ u, int lanes) {
+                                                R *__restrict__ u, int lanes, int rows) {
     constexpr int V = 16 / (int)sizeof(R);
     const int64_t nx2 = g.n[0] + 2, ny2 = g.n[1] + 2;
-    const int lane = threadIdx.x & (lanes - 1), r0 = threadIdx.x / lanes, rpw = 256 / lanes;
+    const RowThread rt(lanes, rows);
     for (int64_t blk = blockIdx.z; blk < g.nblocks; blk += gridDim.z) {
         const BlockPos p = block_pos(g, blk);
         const int ex = p.ext[0];
@@ -137,11 +162,11 @@ __global__ __launch_bounds__(256) void k_gather(Geom g, const R *__restrict__ s,
             zlo = p.b[2] == 0 ? -1 : 0;
             zhi = p.ext[2] - (p.b[2] == g.nb[2] - 1 ? 0 : 1);
         }
-        for (int lz = zlo + (int)blockIdx.y; lz <= zhi; lz += gridDim.y) {
-            for (int ly = ylo + (int)blockIdx.x * rpw + r0; ly <= yhi; ly += (int)gridDim.x * rpw) {
+        for (int lz = zlo + rt.plane; lz <= zhi; lz += rt.nplanes) {
+            for (int ly = ylo + rt.row; ly <= yhi; ly += rt.nrows) {
                 R *dst = u + ((g.ndim == 3 ? (int64_t)(z0 + lz + 1) * ny2 : 0) + y0 + ly + 1) * nx2 + 1 + x0;
                 const int64_t o = local_offset(g, blk, 0, ly, lz);
-                for (int c = lane * V; c < ex; c += lanes * V) {
+                for (int c = rt.lane * V; c < ex; c += lanes * V) {
                     if (c + V <= ex) {
                         const Chunk<R, V> w = *reinterpret_cast<const Chunk<R, V> *>(s + o + c);
                         Loose<R> t;
@@ -152,8 +177,8 @@ __global__ __launch_bounds__(256) void k_gather(Geom g, const R *__restrict__ s,
                         for (int v = 0; c + v < ex; ++v) dst[c + v] = s[o + c + v];
                     }
                 }
-                if (lane == 0 && p.b[0] == 0) dst[-1] = s[o - 1];
-                if (lane == 0 && p.b[0] == g.nb[0] - 1) dst[ex] = s[o + ex];
+                if (rt.lane == 0 && p.b[0] == 0) dst[-1] = s[o - 1];
+                if (rt.lane == 0 && p.b[0] == g.nb[0] - 1) dst[ex] = s[o + ex];
             }
         }
     }
@@ -162,19 +187,20 @@ __global__ __launch_bounds__(256) void k_gather(Geom g, const R *__restrict__ s,
 // b = fl_R(h2 * f): the product in FP64, one rounding to R.
 template <typename R>
 __global__ __launch_bounds__(256) void k_scale_source(Geom g, const R *__restrict__ f,
-                                                      R *__restrict__ b, double h2, int lanes) {
+                                                      R *__restrict__ b, double h2, int lanes,
+                                                      int rows) {
     constexpr int V = 16 / (int)sizeof(R);
     const int64_t nx = g.n[0], ny = g.n[1];
-    const int lane = threadIdx.x & (lanes - 1), r0 = threadIdx.x / lanes, rpw = 256 / lanes;
+    const RowThread rt(lanes, rows);
     for (int64_t blk = blockIdx.z; blk < g.nblocks; blk += gridDim.z) {
         const BlockPos p = block_pos(g, blk);
         const int ex = p.ext[0], ey = p.ext[1], ez = p.ext[2];
         const int x0 = p.b[0] * g.e[0], y0 = p.b[1] * g.e[1], z0 = p.b[2] * g.e[2];
-        for (int lz = (int)blockIdx.y; lz < ez; lz += gridDim.y) {
-            for (int ly = (int)blockIdx.x * rpw + r0; ly < ey; ly += (int)gridDim.x * rpw) {
+        for (int lz = rt.plane; lz < ez; lz += rt.nplanes) {
+            for (int ly = rt.row; ly < ey; ly += rt.nrows) {
                 const R *src = f + ((int64_t)(z0 + lz) * ny + y0 + ly) * nx + x0;
                 R *dst = b + blk * g.sstride + ((int64_t)lz * g.e[1] + ly) * g.e[0];
-                for (int c = lane * V; c < ex; c += lanes * V) {
+                for (int c = rt.lane * V; c < ex; c += lanes * V) {
                     if (c + V <= ex) {
                         const Loose<R> t = *reinterpret_cast<const Loose<R> *>(src + c);
                         Chunk<R, V> w;
@@ -319,7 +345,7 @@ hipError_t launch_scatter(const Geom &g, const void *u, void *s0, void *s1, bool
                           hipStream_t st) {
     const RowMap m = row_map<R>(g, g.e[1] + 2, g.ndim == 3 ? g.e[2] + 2 : 1);
     hipLaunchKernelGGL(k_scatter<R>, m.grid, dim3(256), 0, st, g, (const R *)u, (R *)s0, (R *)s1,
-                       m.lanes, zero_ring ? 1 : 0);
+                       m.lanes, m.rows, zero_ring ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -423,7 +449,8 @@ hipError_t launch_adjoint_finish(const Geom &g, const double *gb, double h2, dou
 template <typename R>
 hipError_t launch_gather(const Geom &g, const void *s, void *u, hipStream_t st) {
     const RowMap m = row_map<R>(g, g.e[1] + 2, g.ndim == 3 ? g.e[2] + 2 : 1);
-    hipLaunchKernelGGL(k_gather<R>, m.grid, dim3(256), 0, st, g, (const R *)s, (R *)u, m.lanes);
+    hipLaunchKernelGGL(k_gather<R>, m.grid, dim3(256), 0, st, g, (const R *)s, (R *)u, m.lanes,
+                       m.rows);
     return hipGetLastError();
 }
 
@@ -431,7 +458,7 @@ template <typename R>
 hipError_t launch_scale_source(const Geom &g, const void *f, void *b, double h2, hipStream_t st) {
     const RowMap m = row_map<R>(g, g.e[1], g.ndim == 3 ? g.e[2] : 1);
     hipLaunchKernelGGL(k_scale_source<R>, m.grid, dim3(256), 0, st, g, (const R *)f, (R *)b, h2,
-                       m.lanes);
+                       m.lanes, m.rows);
     return hipGetLastError();
 }
 
