@@ -69,15 +69,15 @@ __device__ __forceinline__ void buffer_put16(void *base, uint32_t off, bool on, 
     __builtin_amdgcn_raw_buffer_store_b128(t, r, off, 0, NT ? 2 : 0);
 }
 
-// 16-byte store with the non-temporal hint (the line is not kept in the
-// caches on its way to memory).
+// Store of 4, 8 or 16 bytes with the non-temporal hint (the line is not kept in
+// the caches on its way to memory).
 template <typename X>
-__device__ __forceinline__ void store_nt16(X *p, const X &v) {
-    static_assert(sizeof(X) == 16, "16-byte stores only");
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    u32x4 t;
-    __builtin_memcpy(&t, &v, 16);
-    __builtin_nontemporal_store(t, reinterpret_cast<u32x4 *>(p));
+__device__ __forceinline__ void store_nt(X *p, const X &v) {
+    static_assert(sizeof(X) == 4 || sizeof(X) == 8 || sizeof(X) == 16, "4, 8 or 16 bytes");
+    typedef unsigned int u32xn __attribute__((ext_vector_type(sizeof(X) / 4)));
+    u32xn t;
+    __builtin_memcpy(&t, &v, sizeof(X));
+    __builtin_nontemporal_store(t, reinterpret_cast<u32xn *>(p));
 }
 
 // Whole-wave lane shifts through DPP (wave_shr:1 / wave_shl:1).  All 64

@@ -760,12 +760,13 @@ int do_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos = true) {
     while (left > 0) {
         // split what is left into the fewest passes of at most `depth`
         // sweeps, as evenly as possible (50 at depth 6: 6,6,6,6,6,5,5,5,5)
-        const Pass2d ps = plan2d<R>(h, left, depth, h->depth > 0, h->rows > 0,
-                                    h->has_source ? 1 : 0, first && res_first);
+        Pass2d ps = plan2d<R>(h, left, depth, h->depth > 0, h->rows > 0,
+                              h->has_source ? 1 : 0, first && res_first);
         const int t = ps.t;
         double *part = nullptr;
         if (ps.tile) {
             if (first && res_first) part = h->partials;
+            ps.tp.nt = h->flags & JACOBI_FLAG_NT_STORES;
             int rc = prof_begin(h);
             if (rc) return rc;
             HIP_TRY(jac::launch_tile2d<R>(h->g, h->u[h->cur], h->u[h->cur ^ 1], b, part, nullptr,

@@ -437,7 +437,7 @@ __device__ __forceinline__ void m2_level(const Geom &g, R *__restrict__ uout,
                 for (int v = 0; v < V; ++v) o.v[v] = out[v];
                 if (L.st_b != kNoStore) {
                     if (L.nt)
-                        store_nt16(&at_mut<Chunk<R, V>>(row, L.lane_b), o);
+                        store_nt(&at_mut<Chunk<R, V>>(row, L.lane_b), o);
                     else
                         at_mut<Chunk<R, V>>(row, L.lane_b) = o;
                 } else if constexpr ((EK & 2) != 0) {

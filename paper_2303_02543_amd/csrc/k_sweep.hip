@@ -362,7 +362,7 @@ __global__ __launch_bounds__(256) void k_sweep_tile(Geom g, const R *__restrict_
             R *orow = uout + (int64_t)blk * g.bstride + (int64_t)(y + 1) * g.pitch;
             if (full) {
                 if (nt)
-                    store_nt16(&at_mut<C>(orow, lane_b), out);
+                    store_nt(&at_mut<C>(orow, lane_b), out);
                 else
                     at_mut<C>(orow, lane_b) = out;
             } else {

@@ -41,6 +41,7 @@ struct alignas(V * sizeof(R)) Cells {
 
 struct T2Args {
     int t, nstrips, ngrp, nitems, acols;
+    int nt;  // store the outputs with the non-temporal hint
 };
 
 template <typename R, int V, int RY>
@@ -164,7 +165,7 @@ __device__ __forceinline__ T2Rows<RY> t2_rows(const Geom &g, int y) {
 template <typename R, int V, int RY>
 __device__ __forceinline__ void t2_store(R *__restrict__ uout, const R (&val)[RY][V],
                                          const T2Lane<R, V, RY> &L, const T2Rows<RY> &rows,
-                                         uint32_t col) {
+                                         uint32_t col, bool nt) {
     if (!uout) return;
 #pragma unroll
     for (int j = 0; j < RY; ++j) {
@@ -174,7 +175,10 @@ __device__ __forceinline__ void t2_store(R *__restrict__ uout, const R (&val)[RY
             Cells<R, V> t;
 #pragma unroll
             for (int v = 0; v < V; ++v) t.v[v] = val[j][v];
-            at_mut<Cells<R, V>>(d, col) = t;
+            if (nt)
+                store_nt(&at_mut<Cells<R, V>>(d, col), t);
+            else
+                at_mut<Cells<R, V>>(d, col) = t;
         } else if (L.out) {
 #pragma unroll
             for (int v = 0; v < V; ++v)
@@ -187,7 +191,7 @@ template <typename R, int V, int RY, int MODE, bool EDGE, bool RES>
 __device__ __forceinline__ void t2_body(const Geom &g, const R *__restrict__ uin,
                                         R *__restrict__ uout, const R *__restrict__ bsrc,
                                         double *__restrict__ gacc, T2Lane<R, V, RY> &L,
-                                        T2Sh<R, V> sh, int t, int a, int c, int y) {
+                                        T2Sh<R, V> sh, int t, int a, int c, int y, bool nt) {
     using C = Cells<R, V>;
     const int nx = g.n[0], ny = g.n[1];
     R p[RY][V], q[RY][V], b[RY][V];
@@ -262,9 +266,9 @@ __device__ __forceinline__ void t2_body(const Geom &g, const R *__restrict__ uin
     }
     if (t & 1) {
         t2_sweep<R, V, RY, MODE, EDGE>(p, q, b, ga, L, sh, 0);
-        t2_store<R, V, RY>(uout, q, L, rows, col);
+        t2_store<R, V, RY>(uout, q, L, rows, col, nt);
     } else {
-        t2_store<R, V, RY>(uout, p, L, rows, col);
+        t2_store<R, V, RY>(uout, p, L, rows, col, nt);
     }
     if constexpr (MODE == T2_ADJOINT) {
 #pragma unroll
@@ -315,9 +319,9 @@ __global__ __launch_bounds__(64 * kT2Waves) void k_tile2d(Geom g, const R *__res
     L.out = c >= xlo && c < xhi;
     L.acc = 0.0;
     if (a == 0 || a + W >= nx || y0 + H > ny)
-        t2_body<R, V, RY, MODE, true, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y);
+        t2_body<R, V, RY, MODE, true, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y, A.nt != 0);
     else
-        t2_body<R, V, RY, MODE, false, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y);
+        t2_body<R, V, RY, MODE, false, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y, A.nt != 0);
     if constexpr (RES) {
         const double s = wave_sum(L.acc);
         if (L.lane == 0) part[L.wv] = s;
@@ -360,6 +364,7 @@ static hipError_t t2_launch_s(const Geom &g, const void *uin, void *uout, const 
     A.nstrips = pl.nstrips;
     A.ngrp = pl.ngrp;
     A.nitems = (int)pl.items;
+    A.nt = pl.nt;
     A.acols = (pl.t + V - 1) / V * V;
 #define JAC_T2(MODEV, RESV)                                                                     \
     hipLaunchKernelGGL((k_tile2d<R, V, RY, MODEV, RESV>), dim3((unsigned)pl.items),             \
@@ -451,6 +456,7 @@ bool tile2d_plan(const Geom &g, int t, int mode, bool res, size_t cap, int cus, 
         Tile2dPlan p;
         p.t = t;
         p.shape = s;
+        p.nt = 0;
         const int acols = (t + sh[s].v - 1) / sh[s].v * sh[s].v;
         p.nstrips = t2_tiles(g.n[0], 64 * sh[s].v, acols);
         p.ngrp = t2_tiles(g.n[1], kT2Waves * sh[s].ry, t);

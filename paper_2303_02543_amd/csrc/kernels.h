@@ -110,6 +110,7 @@ struct Tile2dPlan {
     int t, shape, nstrips, ngrp;
     int64_t items;  // work items = residual partials
     double us;      // estimated duration
+    int nt;         // store with the non-temporal hint (0 from the plan)
 };
 // Best tile shape for a pass of t sweeps in `mode` (0 Laplace, 1 Poisson, 2
 // adjoint) on `cus` compute units; res: residual partials wanted, at most cap.

@@ -331,3 +331,16 @@ def test_small_blocks_keep_the_lanes_busy(device):
     small, large = source_ms(32), source_ms(4)
     say("source into blocks", small, large)
     assert small < 6 * large
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", [(65, 33, 2, 3, 8), (300, 201, 2, 2, 13), (1000, 777, 4, 3, 13),
+                                  (2049, 1030, 8, 8, 16)])
+def test_2d_register_tiles_nontemporal(device, dtype, case):
+    """The outputs of register tiles stored with the non-temporal hint."""
+    from paper_2303_02543_amd import JACOBI_FLAG_NT_STORES
+    nx, ny, bx, by, t = case
+    U0 = RNG.uniform(0, 1, (ny + 2, nx + 2))
+    f = RNG.standard_normal((ny, nx)) * 100
+    check(U0, f, synthetic.spacing2(max(nx, ny)), 2 * t + 1, t, (bx, by), dtype, device,
+          "2d tiles nt %s %s" % (case, np.dtype(dtype).name), flags=JACOBI_FLAG_NT_STORES)
