@@ -344,3 +344,76 @@ def test_2d_register_tiles_nontemporal(device, dtype, case):
     f = RNG.standard_normal((ny, nx)) * 100
     check(U0, f, synthetic.spacing2(max(nx, ny)), 2 * t + 1, t, (bx, by), dtype, device,
           "2d tiles nt %s %s" % (case, np.dtype(dtype).name), flags=JACOBI_FLAG_NT_STORES)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", [((203, 150), (3, 4), 0), ((1200, 1100), (4, 4), 0),
+                                  ((70, 41, 33), (2, 2, 3), 5), ((256, 255, 257), (4, 3, 2), 4),
+                                  ((419, 401, 203), (4, 3, 2), 2)])
+def test_poisoned_workspace_default_schedule(device, dtype, case):
+    """A workspace full of NaN under the schedules that the library picks: register
+    tiles in 2D, tiles or rows in 3D."""
+    import torch
+    import paper_2303_02543_amd as jb
+    grid, blocks, depth = case
+    shape = tuple(reversed(grid))
+    tdt = getattr(torch, np.dtype(dtype).name)
+    U0 = RNG.uniform(0, 1, tuple(n + 2 for n in shape))
+    f = RNG.uniform(-1, 1, shape)
+    h2 = synthetic.spacing2(max(grid))
+    want, _ = oracle_run(U0, f, h2, 9, dtype)
+    s = jb.Solver(grid, blocks, tdt, device=device)
+    try:
+        s.workspace.view(torch.int32).fill_(-1)  # NaN in either type
+        s.set_tuning(depth, 0, 0)
+        s.set_state(torch.from_numpy(U0.astype(dtype)).to(device))
+        s.set_source(torch.from_numpy(f.astype(dtype)).to(device), h2)
+        s.sweep(9)
+        assert bits_equal(s.get_state().cpu().numpy(), want), case
+        assert np.isfinite(s.residual())
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", [((203, 150), (3, 4), 0), ((1200, 1100), (4, 4), 0),
+                                  ((70, 41, 33), (2, 2, 3), 0), ((256, 130, 257), (4, 3, 2), 0),
+                                  ((203, 150), (3, 4), 4), ((70, 41, 33), (2, 2, 3), 2)])
+def test_one_handle_through_every_schedule(device, dtype, case):
+    """Fused passes, explicit exchanges and overlapped sends in turn on one handle
+    (deep halos too): each finds the halos that it reads in order."""
+    import torch
+    import paper_2303_02543_amd as jb
+    grid, blocks, halo = case
+    shape = tuple(reversed(grid))
+    tdt = getattr(torch, np.dtype(dtype).name)
+    U0 = RNG.uniform(0, 1, tuple(n + 2 for n in shape))
+    f = RNG.uniform(-1, 1, shape)
+    h2 = synthetic.spacing2(max(grid))
+    explicit = jb.JACOBI_FLAG_EXPLICIT_HALO
+    turns = [(0, 5), (explicit, 3), (0, 4), (explicit | jb.JACOBI_FLAG_OVERLAP, 3), (0, 1),
+             (explicit, 1), (explicit | jb.JACOBI_FLAG_OVERLAP, 1), (explicit, 2), (0, 6)]
+    if halo:
+        turns = [(fl, k) for fl, k in turns if not fl & jb.JACOBI_FLAG_OVERLAP]
+    want = np.asarray(U0, dtype=dtype)
+    b = oracle.scale_source(f.astype(dtype), h2, dtype)
+    s = jb.Solver(grid, blocks, tdt, device=device, halo=halo)
+    try:
+        s.set_state(torch.from_numpy(want).to(device))
+        s.set_source(torch.from_numpy(f.astype(dtype)).to(device), h2)
+        for flags, k in turns:
+            s.set_tuning(0, 0, flags)
+            s.sweep(k)
+            want = oracle.sweep(want, b, k)
+            assert bits_equal(s.get_state().cpu().numpy(), want), (case, flags, k)
+    finally:
+        s.close()
+
+
+def test_3d_wide_offsets_double_precision(device):
+    """The z layer of more than 4 GiB in FP64."""
+    nx, ny, nz = 256, 256, 345
+    rng = np.random.default_rng(16)
+    U0 = rng.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
+    f = rng.uniform(-1, 1, (nz, ny, nx))
+    check(U0, f, synthetic.spacing2(nz), 5, 4, (32, 256, 1), np.float64, device, "3d wide FP64")
