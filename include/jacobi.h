@@ -335,7 +335,8 @@ int jacobi_batch_get_tuning(jacobi_batch_t b, int *t_depth, int *rows, int *use_
 
 /* Not in the paper (the batched form's autotuner).  Time candidate depths and
  * tile heights on one check interval of
- * check_every sweeps and keep the fastest (all are bit-identical).  Uses the
+ * check_every sweeps and keep the fastest (all are bit-identical).  The default
+ * heights of each depth are among them (rows 0).  Uses the
  * grids' buffers as scratch: every grid must be set again afterwards.
  * Synchronises the stream.  Outputs may be NULL. */
 int jacobi_batch_autotune(jacobi_batch_t b, int64_t check_every, int *t_depth, int *rows);

@@ -199,3 +199,35 @@ def test_default_tile_heights(device):
                 assert bits_equal(B.get_grid(i).cpu().numpy(), want), (R, K, i)
     finally:
         B.close()
+
+
+@pytest.mark.parametrize("case", [([(300, 300)] * 40, np.float64), ([(700, 650), (1500, 1200), (900, 601)], np.float32)])
+def test_autotune_is_not_slower_than_the_default(device, case):
+    """The default heights are among those the autotuner times, so a solve takes
+    at most as long after it (a sixth is left for noise)."""
+    import time
+    import torch
+    sizes, dtype = case
+    B, inputs = make_batch(sizes, dtype, device, block=256)
+    dev = [(torch.from_numpy(U0).to(device), torch.from_numpy(f).to(device), h2) for U0, f, h2 in inputs]
+
+    def seconds():
+        best = 1e9
+        for _ in range(7):
+            for i, (U0, f, h2) in enumerate(dev):
+                B.set_grid(i, U0, f, h2)
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            B.solve(0.0, 200, 50)
+            best = min(best, time.perf_counter() - t)
+        return best
+
+    try:
+        seconds()
+        default = seconds()
+        tuned = B.autotune(50)
+        s = seconds()
+        say("batch autotuned", tuned, "%.3f ms, default %.3f" % (s * 1e3, default * 1e3))
+        assert s <= default * 7 / 6
+    finally:
+        B.close()
