@@ -319,9 +319,11 @@ __global__ __launch_bounds__(64 * kT2Waves) void k_tile2d(Geom g, const R *__res
     L.out = c >= xlo && c < xhi;
     L.acc = 0.0;
     if (a == 0 || a + W >= nx || y0 + H > ny)
-        t2_body<R, V, RY, MODE, true, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y, A.nt != 0);
+        t2_body<R, V, RY, MODE, true, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y,
+                                          MODE != T2_ADJOINT && A.nt != 0);
     else
-        t2_body<R, V, RY, MODE, false, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y, A.nt != 0);
+        t2_body<R, V, RY, MODE, false, RES>(g, uin, uout, bsrc, gacc, L, sh, t, a, c, y,
+                                          MODE != T2_ADJOINT && A.nt != 0);
     if constexpr (RES) {
         const double s = wave_sum(L.acc);
         if (L.lane == 0) part[L.wv] = s;
