@@ -238,7 +238,7 @@ def bench_poisson3d(plain_glups):
         Ud = torch.from_numpy(U0.astype(np_dt)).to(dev)
         s = jb.Solver((n, n, n), (8, 8, 8), t_dt, device=dev)
         try:
-            # the library's default 3D schedule (depth 4; measured fastest)
+            # the library's default 3D schedule (depth 5; measured fastest)
             res = torch.empty(jb.residual_count(K, R), dtype=torch.float64, device=dev)
 
             def step():

@@ -496,8 +496,9 @@ class Solver:
     def adjoint(self, dL_duK, n_iter, h2, chunk=None):
         """Reverse sweeps in one library call (jacobi_adjoint): from dL/du_K
         (full state tensor, ring included) return (dL/df FP64 interior,
-        dL/dU0 FP64 full array: ring = dL/dg, interior = dL/du_0).  chunk:
-        sweeps per adjoint segment (the gradients do not depend on it)."""
+        dL/dU0 FP64 full array: ring = dL/dg, interior = dL/du_0).  chunk: the
+        forward run's checkpoint interval; the adjoint reads no checkpoint
+        and is one run of n_iter sweeps whatever it is."""
         import torch
         self._check_tensor(dL_duK, self.state_shape, "dL_duK")
         gf = torch.empty(self.interior_shape, dtype=torch.float64, device=self.device)

@@ -8,9 +8,9 @@ state, ring included)
           interior = u_0
   solver  a paper_2303_02543_amd.Solver for this grid (its workspace is reused)
   K       number of sweeps; h2 = h^2 (b = h2 * f)
-  chunk   checkpoint interval C: the forward sweeps run as jacobi_forward_ckpt
-          segments of C and the adjoint sweeps as segments of C; the
-          gradients do not depend on C.
+  chunk   checkpoint interval C: with keep_checkpoints the forward sweeps run
+          in segments of C (without them, and in the adjoint, as one run of K);
+          the gradients do not depend on C.
   keep_checkpoints
           keep the forward states after 0, C, 2C, ... sweeps (one device
           tensor on the context, `checkpoints`), e.g. to restart the forward

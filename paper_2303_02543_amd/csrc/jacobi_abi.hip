@@ -136,8 +136,10 @@ int plan(int ndim, const int64_t *grid, const int64_t *blocks, int dtype, Geom *
     size_t cap = ((size_t)g->n[0] / 32 + 2) * ((size_t)g->n[1] * g->n[2] / kMinRows + 2);
     if (ndim == 3) {
         // 3D pass: 8 partials (one per wave) per work item of (strip of
-        // >= 24 output columns, >= 26 output rows, z segment of >= kMinRows
-        // planes), the smallest tiles of any depth; 4 per 10 rows bounds it
+        // >= 24 output columns, >= 24 output rows: depth 5, z segment), the
+        // smallest tiles of any depth; 4 per 10 rows bounds it for segments of
+        // kMinRows planes, and march3d_plan takes no shorter ones whose
+        // partials would not fit
         const size_t c3 = ((size_t)g->n[0] / 24 + 2) * 4 * ((size_t)g->n[1] / 10 + 2) *
                           ((size_t)g->n[2] / kMinRows + 2);
         if (c3 > cap) cap = c3;
@@ -978,9 +980,11 @@ int do_deep_sweep(jacobi_t h, int64_t n, double *res_first, bool sync_halos) {
 // Adjoint passes: n sweeps of the zero-ring state with the FP64 accumulation.
 template <typename R>
 int do_adjoint(jacobi_t h, int64_t n) {
-    // adjoint passes: depth 7 measured fastest for FP32 on MI355X (4096^2:
-    // 820 GLUP/s vs 586 at depth 4; depth 8 runs out of registers for the
-    // FP64 accumulator ring)
+    // marching passes of the adjoint: depth 7 measured fastest for FP32 on
+    // MI355X (4096^2: 820 GLUP/s vs 586 at depth 4; depth 8 runs out of
+    // registers for the FP64 accumulator ring); register tiles take passes of
+    // up to 16 sweeps where plan2d expects them to be faster (4096^2, 500
+    // sweeps: 11.1 us per sweep in passes of 16 and 15, marching 14.4)
     int depth = h->adj_depth > 0 ? h->adj_depth : (h->dtype == JACOBI_F32 ? 7 : 3);
     int64_t left = n;
     while (left > 0) {

@@ -670,8 +670,9 @@ static bool m3_wide(const Geom &g, size_t es) {
 // The constants are those that pick best among passes timed at 35 grids of 64^3 ..
 // 640^3, plates, and bars, with and without source, and checked at 30 others: passes
 // that are further than 5% behind the row kernel by itself are FP64 at depth 1, 256^3
-// (93 us against 86), 1024^2 x 3 (14.4 and 12.8), FP64 depth 5 of 1024^2 x 128 (1487 and
-// 1386), and FP64 residuals alone (300x280x320 72 and 59).  us per pass, tiles and row
+// (93 us against 86), 256x256x512 Laplace (165 and 148), 1024^2 x 3 (14.4 and 12.8), and
+// FP64 depth 5 of 1024^2 x 128 (1487 and 1386).  FP64 residuals alone, tiles and rows:
+// 300x280x320 Laplace 68 and 54 us, 280^3 47 and 50.  us per pass, tiles and row
 // kernel: FP64 512^3 Poisson depth 2 1200 and 1116, depth 4 1153 and 1071, but 640^3
 // depth 2 1928 and 2307 (one round); 400^3 depth 2 532 and 501, 350x301x260 229 and 256;
 // 1024^2 x 3 depth 4 61 and 45.  FP32 640^3 Laplace depth 1 555 and 506, depth 2 884 and
@@ -689,7 +690,7 @@ static const M3Rule kM3Rule[2][5] = {
      {1.8, 1.0, 1.60, kNever, 1 << 26, kNever, kNever, kNever},
      {1.8, 1.0, 0, 0, kNever, kNever, kNever, kNever}},
     // FP64
-    {{1.8, 1.0, 1.75, 0, 5.5e7, kNever, kNever, 3.5e7},
+    {{1.8, 1.0, 1.75, 0, 5.5e7, kNever, kNever, 2.6e7},
      {1.8, 1.0, 1.40, kNever, 4e7, 0, kNever, kNever},
      {1.8, 1.2, 1.60, kNever, 4e7, 0, kNever, kNever},
      {1.8, 1.0, 1.48, 5e7, 0, 0, kNever, kNever},

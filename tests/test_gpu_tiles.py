@@ -139,6 +139,29 @@ def test_3d_rows(device, case):
               depth=depth, rows=zseg)
 
 
+@pytest.mark.parametrize("src", [False, True])
+def test_3d_rows_residual_alone(device, src):
+    """The residual of a large FP64 grid by itself: the row kernel without stores."""
+    import torch
+    import paper_2303_02543_amd as jb
+    grid, blocks = (300, 299, 321), (3, 3, 3)
+    shape = tuple(reversed(grid))
+    rng = np.random.default_rng(12)
+    U = rng.uniform(0, 1, tuple(n + 2 for n in shape))
+    f = rng.uniform(-1, 1, shape)
+    h2 = synthetic.spacing2(max(grid))
+    s = jb.Solver(grid, blocks, torch.float64, device=device)
+    try:
+        s.set_state(torch.from_numpy(U).to(device))
+        if src:
+            s.set_source(torch.from_numpy(f).to(device), h2)
+        got = s.residual()
+    finally:
+        s.close()
+    want = oracle.residual(U, oracle.scale_source(f, h2, np.float64) if src else None)
+    assert abs(got - want) <= 1e-12 * want
+
+
 def test_3d_wide_offsets(device):
     """A z layer of blocks of more than 4 GiB (8 x 1 x 690 cells in 32 x 256 narrow
     blocks): the pass runs on 64-bit lane offsets."""
