@@ -669,9 +669,8 @@ static bool m3_wide(const Geom &g, size_t es) {
 //
 // The constants are those that pick best among passes timed at 35 grids of 64^3 ..
 // 640^3, plates, and bars, with and without source, and checked at 30 others: passes
-// that are further than 5% behind the row kernel by itself are FP64 at depth 1, 256^3
-// (93 us against 86), 256x256x512 Laplace (165 and 148), 1024^2 x 3 (14.4 and 12.8), and
-// FP64 depth 5 of 1024^2 x 128 (1487 and 1386).  FP64 residuals alone, tiles and rows:
+// that are further than 5% behind the row kernel by itself are FP64 1024^2 x 3 at depth 1
+// (14.4 and 12.8 us), and FP64 depth 5 of 1024^2 x 128 (1487 and 1386).  FP64 residuals alone, tiles and rows:
 // 300x280x320 Laplace 68 and 54 us, 280^3 47 and 50.  us per pass, tiles and row
 // kernel: FP64 512^3 Poisson depth 2 1200 and 1116, depth 4 1153 and 1071, but 640^3
 // depth 2 1928 and 2307 (one round); 400^3 depth 2 532 and 501, 350x301x260 229 and 256;
@@ -684,7 +683,7 @@ struct M3Rule {
 constexpr double kNever = 1e300;
 static const M3Rule kM3Rule[2][5] = {
     // FP32, depths 1 - 5
-    {{1.9, 1.0, 1.85, kNever, 1.05e8, 1 << 21, 1.05e8, 1.05e8},
+    {{1.9, 1.0, 1.85, kNever, 1.05e8, 1 << 21, 1.05e8, 6.2e7},
      {1.8, 1.2, 1.75, kNever, 1 << 26, kNever, kNever, kNever},
      {1.8, 1.1, 1.70, 0, 1 << 26, kNever, kNever, kNever},
      {1.8, 1.0, 1.60, kNever, 1 << 26, kNever, kNever, kNever},
@@ -711,7 +710,8 @@ bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, bool 
         p.wide = wide;
         m3_shape<R>(g, depth, ry, p.nstrips, p.ngrp);
         const int64_t tiles = (int64_t)p.nstrips * p.ngrp;
-        const double step = ry == 2 ? rule.tall : 1.0;
+        // (without stores 1.8: 256^3 FP32 Laplace residual, 32 rows 25.0 us, 64 rows 23.0)
+        const double step = ry == 1 ? 1.0 : store ? rule.tall : 1.8;
         const int smin = zseg > 0 ? (nz + zseg - 1) / zseg : 1;
         const int smax = zseg > 0 ? smin : (nz + 3) / 4;
         for (int s = smin; s <= smax; ++s) {
@@ -740,7 +740,17 @@ bool march3d_plan(const Geom &g, int depth, int zseg, int cus, size_t cap, bool 
         const bool choice =
             cells >= (store ? rule.least : rule.residual) || (nz <= 32 && cells >= rule.plate);
         row.cost = rule.row * rounds * (planes + 2 * (depth - 1));
-        if ((choice && row.cost < best_cost) || cells >= rule.always || best_cost >= 1e300) {
+        // A sweep whose row tiles cover the grid with nothing over and fill a round of
+        // one or of two workgroups per CU (residuals alone: of two) has no better
+        // tiling; us, tiles and rows: FP32 512x256x256 Laplace 89 and 74, 256^3 29.1 and 26.4,
+        // FP64 512x256x256 167 and 147; but with 320 of 512 workgroups, 320x256x256 FP64 119 and
+        // 141, and with 4% over, 253x250x255 FP32 Laplace 32 and 52.
+        const double fill = (double)row.items / cus;
+        const bool whole = depth == 1 &&
+                           (double)row.items * (256.0 / sizeof(R)) * 32 * row.zseg <= 1.02 * cells &&
+                           ((store && fill > 0.875 && fill <= 1.0) ||
+                            (fill > (store ? 1.74 : 1.95) && fill <= 2.0));
+        if (whole || (choice && row.cost < best_cost) || cells >= rule.always || best_cost >= 1e300) {
             *out = row;
             return true;
         }

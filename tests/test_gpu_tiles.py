@@ -269,6 +269,20 @@ def test_3d_rows_fp32(device, case):
               "3d rows fp32 %s %s" % (case, "laplace" if src is None else "poisson"), depth=depth)
 
 
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("case", [(256, 256, 256, 4, 4, 4), (512, 127, 256, 6, 2, 3),
+                                  (512, 256, 255, 8, 3, 4)])
+def test_3d_rows_whole_rounds(device, dtype, case):
+    """Single sweeps of grids that row tiles cover in one round of one or two
+    workgroups per CU, exactly and one row or plane short."""
+    nx, ny, nz, bx, by, bz = case
+    U0 = RNG.uniform(0, 1, (nz + 2, ny + 2, nx + 2))
+    f = RNG.uniform(-1, 1, (nz, ny, nx))
+    for src in (f, None):
+        check(U0, src, synthetic.spacing2(nx), 3, 2, (bx, by, bz), dtype, device,
+              "3d whole rounds %s %s source %s" % (case, np.dtype(dtype).name, src is not None), depth=1)
+
+
 def test_3d_plates_of_double_precision(device):
     """Plates run four sweeps per pass in FP64 (the launches are counted), with
     the result of any other schedule."""
